@@ -104,7 +104,16 @@ enum {
  * identical results. The fallback's kernels are enqueued with every call and
  * return at once when no walk was capped (a few microseconds per call);
  * lr_profile_last reports whether it ran. Under LR_VALIDATE a cycle reached
- * by a walk is reported through the same fallback. */
+ * by a walk is reported through the same fallback.
+ * Independent walks: with the planner's own levels (spacing[0] and base_max 0,
+ * or naming just those), inputs of more than 4096 (weighted 8192) and fewer
+ * than 2^21 (weighted 2^19) elements, and larger inputs' first level of at
+ * most 2^20 (2^19) elements, are not chased: every element walks by itself, a
+ * dozen steps at most, to the next sampled ruler, the last level's rulers are
+ * ranked by pointer doubling over the whole chip, and every element composes
+ * its walk with its ruler's result. An element of an input that needs more than
+ * 32 compositions (an order against the sampling) turns to doubling as well;
+ * lr_profile_last then reports the fallback. */
 /* Ruler spawning (Section 2.2): the first level is chased in two rounds. The
  * walks of the sampled rulers and heads stop after 2k steps, each marking the
  * element it would have taken next; then new rulers are spawned at every such
@@ -142,7 +151,9 @@ typedef struct lr_opts {
                                           LR_NO_LOCAL | LR_SPAWN | LR_VISIT_LOG */
     uint32_t base_max;                 /* largest level solved by the one-workgroup
                                           base case; 0 = default (8192 unweighted,
-                                          4096 weighted) */
+                                          4096 weighted). With the planner's own
+                                          levels the base case is left to inputs of
+                                          up to 4096 (weighted 8192) elements */
     uint32_t spacing[LR_MAX_LEVELS];   /* ruler spacing k per recursion level: one
                                           ruler per k consecutive ids; powers of
                                           two in [2, 4096]; the list ends at the

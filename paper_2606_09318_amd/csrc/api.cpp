@@ -131,6 +131,60 @@ static lr_status plan_levels(uint64_t m0, bool weighted, const lr_opts* o, bool 
     return fill(false);
 }
 
+// Level 0 through the visit log: from LOG_MIN_N elements on, or on request.
+static bool use_log(uint64_t m0, uint32_t levels, const lr_opts* o) {
+    if (levels < 1) return false;
+    return m0 >= LOG_MIN_N || (o && (o->flags & LR_VISIT_LOG) && m0 >= LOG_FORCE_MIN_N);
+}
+
+// Which levels are chased and which are ranked by independent walks: only
+// with the planner's own levels (options that name others are followed level
+// by level down to the base case). input: level 0 is the caller's input.
+static void plan_iw(const lr_opts* o, bool user_spacing, bool capped, bool input, uint32_t max_levels, Plan* p) {
+    p->run = p->levels;
+    p->iw = false;
+    if (o && ((user_spacing && o->spacing[0]) || o->base_max)) {
+        Plan q;
+        if (plan_levels(p->m[0], p->weighted, nullptr, false, &q, max_levels, capped) != LR_OK) return;
+        if (q.levels != p->levels || q.base_max != p->base_max) return;
+        for (uint32_t l = 0; l < q.levels; ++l)
+            if (q.log2k[l] != p->log2k[l]) return;
+    }
+    uint32_t r = 0;
+    if (input) {
+        const bool direct = !use_log(p->m[0], p->levels, o) && p->m[0] > LR_IW_DIRECT_MIN &&
+                            p->m[0] < iw_direct(p->weighted) && (!p->weighted || p->levels);
+        if (!direct) {
+            if (p->levels == 0) return;  // the base case alone
+            r = 1;
+        }
+    }
+    if (r || !input)
+        while (r < p->levels && p->m[r] > iw_max(p->weighted)) ++r;
+    uint32_t t = r;
+    while (t < p->levels && p->m[t] > iw_top(p->weighted)) ++t;
+    p->run = r;
+    p->top = t;
+    p->iw = true;
+}
+
+// Where the independent walks keep their nodes: the input's over the body of
+// the workspace, a level's over its own slot array and what follows it (none
+// of its levels is chased). Levels whose nodes do not fit there are chased
+// down to the base case.
+static void place_iw(size_t body, size_t end, Plan* p) {
+    if (!p->iw) return;
+    const bool input = p->run == 0 && !p->local && !p->spawn;
+    if (!p->weighted && !input && p->top == p->run) return;  // the level's records are the nodes
+    size_t need = 0;
+    for (uint32_t l = p->run; l <= p->top; ++l) need += (size_t)p->m[l] * iw_node_bytes(p->weighted);
+    p->off_nodes = input ? body : (p->run < std::max(p->levels, 1u)) ? p->off_slot[p->run] : end;
+    if (p->off_nodes + need > end) {
+        p->iw = false;
+        p->run = p->levels;
+    }
+}
+
 // Visit log and grouping areas (level 0 in log mode), then per level the
 // slot, walk-record and tile-count arrays. Returns the end offset.
 static size_t layout_levels(Plan* p, size_t off) {
@@ -247,12 +301,6 @@ static size_t layout_spawn(Plan* p, uint64_t n, size_t off) {
     return off;
 }
 
-// Level 0 through the visit log: from LOG_MIN_N elements on, or on request.
-static bool use_log(uint64_t m0, uint32_t levels, const lr_opts* o) {
-    if (levels < 1) return false;
-    return m0 >= LOG_MIN_N || (o && (o->flags & LR_VISIT_LOG) && m0 >= LOG_FORCE_MIN_N);
-}
-
 lr_status make_plans(uint64_t n, bool weighted, const lr_opts* o, uint32_t batch_count, PlanSet* ps) {
     *ps = PlanSet{};
     if (n >= (1ull << 31)) return LR_ERR_UNSUPPORTED;
@@ -277,8 +325,10 @@ lr_status make_plans(uint64_t n, bool weighted, const lr_opts* o, uint32_t batch
     }
     // the input level of the spawning chase keeps its head count in the last
     // Ctrl level entry
-    lr_status s = plan_levels(n, weighted, spawn ? &upper : o, true, p, spawn ? MAXL - 2 : LR_MAX_LEVELS);
+    const uint32_t max_levels = spawn ? MAXL - 2 : LR_MAX_LEVELS;
+    lr_status s = plan_levels(n, weighted, spawn ? &upper : o, true, p, max_levels);
     if (s != LR_OK) return s;
+    plan_iw(spawn ? &upper : o, true, false, !spawn && !force, max_levels, p);
     size_t off = 0;
     p->off_ctrl = off;
     off += align_up(sizeof(Ctrl));
@@ -308,6 +358,7 @@ lr_status make_plans(uint64_t n, bool weighted, const lr_opts* o, uint32_t batch
         for (int l = 0; l < LR_MAX_LEVELS; ++l) lo.spacing[l] = 0;  // user spacing describes the plain levels
         s = plan_levels(local_auto_cap(n), weighted, &lo, false, q, LR_MAX_LEVELS, true);
         if (s != LR_OK) return s;
+        plan_iw(&lo, false, true, false, LR_MAX_LEVELS, q);
         q->off_ctrl = p->off_ctrl;
         q->off_hsum = p->off_hsum;
         q->log0 = use_log(q->m[0], q->levels, o);
@@ -320,6 +371,8 @@ lr_status make_plans(uint64_t n, bool weighted, const lr_opts* o, uint32_t batch
         off = std::max(off, body + 2 * align_up((size_t)n * p->rec_bytes + 16));
         ps->lp.off_fb = body;
     }
+    place_iw(body, off, p);
+    if (ps->autol) place_iw(body, off, &ps->lp);
     if (batch_count) {
         p->batch_count = batch_count;
         p->off_batch_succ = off;
@@ -361,7 +414,7 @@ static thread_local ProfState g_prof;
 
 // The profiled call's path word, for lr_profile_last (plans with walks only).
 static void prof_capped(const RunArgs& a, const Plan& p) {
-    if (a.ev) g_prof.mode = (p.levels >= 1 || p.spawn) ? &reinterpret_cast<const Ctrl*>(a.ws + p.off_ctrl)->mode
+    if (a.ev) g_prof.mode = (p.walks() || p.iw) ? &reinterpret_cast<const Ctrl*>(a.ws + p.off_ctrl)->mode
                                                         : nullptr;
 }
 
@@ -385,16 +438,14 @@ static lr_status finish(hipError_t e, const RunArgs& a, const Plan& p) {
         if (hipMemcpyAsync(&c, a.ws + p.off_ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, a.stream) != hipSuccess)
             return LR_ERR_HIP;
         if (hipStreamSynchronize(a.stream) != hipSuccess) return LR_ERR_HIP;
-        const bool walks = p.levels >= 1 || p.spawn;
-        const uint32_t err = (walks && c.mode == MODE_FALLBACK) ? (c.err & (ERR_INPUT | ERR_FALLBACK_CYCLE)) : c.err;
+        const uint32_t err = (p.walks() && c.mode == MODE_FALLBACK) ? (c.err & (ERR_INPUT | ERR_FALLBACK_CYCLE)) : c.err;
         if (err) return LR_ERR_BAD_LIST;
     }
     return LR_OK;
 }
 
 static lr_status check_base_lds(const Plan& p) {
-    const uint64_t mL = p.m[p.levels];
-    if (base_lds_bytes(mL, p.weighted) > device_max_lds()) return LR_ERR_UNSUPPORTED;
+    if (!p.iw && base_lds_bytes(p.m[p.levels], p.weighted) > device_max_lds()) return LR_ERR_UNSUPPORTED;
     if (p.log0 && ((size_t)1 << p.s2) * (p.weighted ? 16 : 8) > device_max_lds()) return LR_ERR_UNSUPPORTED;
     // the grouping tiles' LDS is sized for at most PLACE_MAX_RANGES ranges per pass
     if (p.log0 && (p.nb1 > PLACE_MAX_RANGES || (1u << (p.s1 - p.s2)) > PLACE_MAX_RANGES)) return LR_ERR_UNSUPPORTED;

@@ -126,13 +126,15 @@ struct LogFmt {
 
 // ---------------------------------------------------------------- values --
 // Unweighted levels carry a link count; weighted levels carry (count, sum).
+// A result is a record whose list has been followed to its end, so an element
+// that composes its record with a solved one is solved itself.
 template <bool W> struct Lay;
 
 template <> struct Lay<false> {
     struct Val { uint32_t c; };
     struct alignas(8) Slot { uint32_t w, c; };
     struct alignas(8) Rec { uint32_t nxt, c; };       // level element / walk end
-    struct alignas(8) Res { uint32_t c, root; };      // solved rank + terminal id
+    using Res = Rec;                                  // solved: nxt = TERM | terminal id, c = rank
     static __device__ __forceinline__ Val zero() { return {0u}; }
     static __device__ __forceinline__ Val one_link(int64_t) { return {1u}; }
     static __device__ __forceinline__ Val add(Val a, Val b) { return {a.c + b.c}; }
@@ -141,8 +143,8 @@ template <> struct Lay<false> {
     static __device__ __forceinline__ Val val(Slot s) { return {s.c}; }
     static __device__ __forceinline__ Rec rec(uint32_t nxt, Val v) { return {nxt, v.c}; }
     static __device__ __forceinline__ Val val(Rec r) { return {r.c}; }
-    static __device__ __forceinline__ Res res(Val v, uint32_t root) { return {v.c, root}; }
-    static __device__ __forceinline__ Val val(Res r) { return {r.c}; }
+    static __device__ __forceinline__ Res res(Val v, uint32_t root) { return {TERM | root, v.c}; }
+    static __device__ __forceinline__ uint32_t root(Res r) { return r.nxt & IDX; }
     static __device__ __forceinline__ Val junk() { return {NONE}; }
 };
 
@@ -150,7 +152,7 @@ template <> struct Lay<true> {
     struct Val { uint32_t c; int64_t s; };
     struct alignas(16) Slot { uint32_t w, c; int64_t s; };
     struct alignas(16) Rec { uint32_t nxt, c; int64_t s; };
-    struct alignas(16) Res { uint32_t c, root; int64_t s; };
+    using Res = Rec;
     static __device__ __forceinline__ Val zero() { return {0u, 0}; }
     static __device__ __forceinline__ Val one_link(int64_t w) { return {1u, w}; }
     static __device__ __forceinline__ Val add(Val a, Val b) { return {a.c + b.c, a.s + b.s}; }
@@ -159,8 +161,8 @@ template <> struct Lay<true> {
     static __device__ __forceinline__ Val val(Slot s) { return {s.c, s.s}; }
     static __device__ __forceinline__ Rec rec(uint32_t nxt, Val v) { return {nxt, v.c, v.s}; }
     static __device__ __forceinline__ Val val(Rec r) { return {r.c, r.s}; }
-    static __device__ __forceinline__ Res res(Val v, uint32_t root) { return {v.c, root, v.s}; }
-    static __device__ __forceinline__ Val val(Res r) { return {r.c, r.s}; }
+    static __device__ __forceinline__ Res res(Val v, uint32_t root) { return {TERM | root, v.c, v.s}; }
+    static __device__ __forceinline__ uint32_t root(Res r) { return r.nxt & IDX; }
     static __device__ __forceinline__ Val junk() { return {NONE, INT64_MIN}; }
 };
 

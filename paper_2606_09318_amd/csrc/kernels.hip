@@ -1012,6 +1012,259 @@ __global__ __launch_bounds__(BASE_TPB) void k_base(Src src, Out out, uint32_t m,
     }
 }
 
+// ----------------------------------------------------- independent walks --
+// Lists of up to about a million elements (the input itself, or a level of a
+// larger one) without heads, marks, slots or a one-workgroup base case:
+//   k_iw_first  every element walks the list by itself, up to `cap` steps, to
+//               the next ruler (the level's stratified sample) or to its end.
+//               That is about k steps per element where the ruling-set chase
+//               takes one, but the reads hit the caches, nothing is scattered,
+//               and no walk is longer than the cap.
+//   k_iw_walk   the same on the rulers, to the rulers of the next level.
+//   k_iw_solve  on the last level: asynchronous pointer doubling, every
+//               element's record composed with the record it points to until
+//               it has reached a terminal; then, level by level downward,
+//               every element composes its record with its ruler's (solved)
+//               one.
+// Nodes: one record (nxt, value) per element of every level, in one array;
+// level j's nodes start at base_j. A record says that following the list from
+// its element for `value` leads to node nxt or, with nxt = TERM | t, to the
+// terminal t. That stays true whatever the others do, so records are updated
+// in place without any barrier: a reader that finds an older record only jumps
+// less far. A walk that stopped at its cap points to an element that is no
+// ruler, whose own record leads on; a reader just takes one more hop.
+//   - In the doubling the records are read and written with device-scope
+//     accesses, which pass the (per-XCD, not coherent) L2s, so the lanes see
+//     each other's progress; an element's record has one writer per kernel.
+//   - No lane waits for another: a lane alone still moves at least one link a
+//     hop, so the kernels end however their workgroups are scheduled.
+//   - On a cycle (input that is not a forest) the count reaches climit, more
+//     links than a list can have, and the lane stops.
+//   - An order built against the sampling leaves long stretches without a
+//     ruler. The downward pass over the input then turns into doubling itself:
+//     after IW_PATIENCE hops (a random order needs 1.5 on average and stays
+//     below 16) a lane stores its progress after every further hop and reads
+//     device-scope, and its stretch's lanes, all of them resident, halve the
+//     rest with every hop. The last level's doubling stops after IW_TOP_CAP
+//     hops for the same reason and leaves the rest to that pass.
+// Bound by latency: cap cached reads, about log2(m) device-scope reads (0.7 us
+// each up to 2^15 lanes, then 50 G/s), a few cached reads, and a launch (4.5
+// us) for each kernel. A cap of 12 steps (random lists of 1.5 * 2^18 elements:
+// 8 steps 73 us, 12 60, 16 59; weighted 1.4 * 2^19: 181, 168, 172).
+constexpr uint32_t IW_PATIENCE = 32;
+constexpr uint32_t IW_TOP_CAP = 128;
+#ifndef LR_IW_CAP
+#define LR_IW_CAP 12
+#endif
+constexpr uint32_t IW_CAP_ALONE = 8;  // steps of a list that the doubling takes alone
+
+__device__ __forceinline__ uint64_t iw_word(uint32_t f, uint32_t v) { return ((uint64_t)v << 32) | f; }
+template <bool DEV>
+__device__ __forceinline__ uint64_t iw_get(const uint64_t* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, DEV ? __HIP_MEMORY_SCOPE_AGENT : __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void iw_put(uint64_t* p, uint64_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A node's record. Unweighted: one word (nxt, count), the layout of a level's
+// records. Weighted: three words (nxt, count), (nxt, low half of the sum),
+// (nxt, high half), stored one by one; a record is taken only if all three
+// name the same nxt (which determines the values), so halves of two records
+// are never combined.
+template <bool W> struct IwRec;
+template <> struct IwRec<false> {
+    using Val = Lay<false>::Val;
+    static constexpr uint32_t WORDS = 1;
+    template <bool DEV>
+    static __device__ __forceinline__ bool load(const uint64_t* p, uint32_t i, uint32_t& nxt, Val& v) {
+        const uint64_t e = iw_get<DEV>(p + i);
+        nxt = (uint32_t)e;
+        v.c = (uint32_t)(e >> 32);
+        return true;
+    }
+    static __device__ __forceinline__ void store(uint64_t* p, uint32_t i, uint32_t nxt, Val v) {
+        iw_put(p + i, iw_word(nxt, v.c));
+    }
+};
+template <> struct IwRec<true> {
+    using Val = Lay<true>::Val;
+    static constexpr uint32_t WORDS = 3;
+    template <bool DEV>
+    static __device__ __forceinline__ bool load(const uint64_t* p, uint32_t i, uint32_t& nxt, Val& v) {
+        const uint64_t* q = p + 3 * (size_t)i;
+        const uint64_t a = iw_get<DEV>(q), b = iw_get<DEV>(q + 1), c = iw_get<DEV>(q + 2);
+        nxt = (uint32_t)a;
+        v.c = (uint32_t)(a >> 32);
+        v.s = (int64_t)((b >> 32) | (c & 0xffffffff00000000ull));
+        return (uint32_t)b == nxt && (uint32_t)c == nxt;
+    }
+    static __device__ __forceinline__ void store(uint64_t* p, uint32_t i, uint32_t nxt, Val v) {
+        uint64_t* q = p + 3 * (size_t)i;
+        iw_put(q, iw_word(nxt, v.c));
+        iw_put(q + 1, iw_word(nxt, (uint32_t)v.s));
+        iw_put(q + 2, iw_word(nxt, (uint32_t)((uint64_t)v.s >> 32)));
+    }
+};
+
+// Level 0 of the nodes from the source's records. SAMPLE = false: no rulers,
+// every element walks `cap` steps (the list is small enough for the doubling
+// alone). set_mode: the input itself, whose first kernel sets the path word.
+template <bool W, bool SAMPLE, class Src>
+__global__ __launch_bounds__(TPB) void k_iw_first(Src src, Sampler smp, uint64_t* __restrict__ nodes, uint32_t base1,
+                                                  uint32_t m, uint32_t cap, Ctrl* ctrl, uint32_t set_mode,
+                                                  const uint32_t* dm, Gate gate) {
+    if (gate.off()) return;
+    if (dm) m = min(dm[0], m);
+    smp.m = src.m = m;
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (set_mode && i == 0) ctrl->mode = MODE_PLAIN;
+    if (i >= m) return;
+    using L = Lay<W>;
+    uint32_t nxt;
+    typename L::Val acc;
+    src.load(i, nxt, acc);
+    bool ruler = false;
+    for (uint32_t t = 1; !(nxt & TERM); ++t) {
+        if constexpr (SAMPLE) ruler = smp.sampled(nxt);
+        if (ruler || t >= cap) break;
+        typename L::Val v;
+        uint32_t nn;
+        src.load(nxt, nn, v);
+        acc = L::add(acc, v);
+        nxt = nn;
+    }
+    uint32_t at = i;
+    if constexpr (SAMPLE) {
+        if (ruler) nxt = base1 + (nxt >> smp.log2k);
+        if (smp.sampled(i)) at = base1 + (i >> smp.log2k);
+    }
+    IwRec<W>::store(nodes, at, nxt, acc);
+}
+
+// Composes (nxt, acc) with the record of node nxt; false: caught between two
+// of its stores (nothing changed), look again device-scope.
+template <bool W, bool DEV>
+__device__ __forceinline__ bool iw_hop(const uint64_t* nodes, uint32_t& nxt, typename Lay<W>::Val& acc) {
+    uint32_t nn;
+    typename Lay<W>::Val v;
+    if (!IwRec<W>::template load<DEV>(nodes, nxt, nn, v)) return false;
+    acc = Lay<W>::add(acc, v);
+    nxt = nn;
+    return true;
+}
+
+// Level j >= 1: every node's record hops on to the next of level j's rulers,
+// which are the nodes of level j + 1. total: nodes in all.
+template <bool W>
+__global__ __launch_bounds__(TPB) void k_iw_walk(uint64_t* __restrict__ nodes, Sampler smp, uint32_t base,
+                                                 uint32_t basen, uint32_t total, uint32_t m, uint32_t cap,
+                                                 const uint32_t* dm, Gate gate) {
+    if (gate.off()) return;
+    if (dm) m = min(dm[0], m);
+    smp.m = m;
+    const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c >= m) return;
+    using L = Lay<W>;
+    uint32_t nxt;
+    typename L::Val acc;
+    while (!IwRec<W>::template load<true>(nodes, base + c, nxt, acc)) {}  // own record: written by the last kernel
+    for (uint32_t t = 1; nxt < total; ++t) {
+        if (nxt >= base && nxt < basen && smp.sampled(nxt - base)) {
+            nxt = basen + ((nxt - base) >> smp.log2k);
+            break;
+        }
+        // another lane may have stored its node's new record already: then nxt
+        // is a ruler's node
+        if (nxt >= basen || t >= cap) break;
+        if (!iw_hop<W, false>(nodes, nxt, acc)) while (!iw_hop<W, true>(nodes, nxt, acc)) {}
+    }
+    IwRec<W>::store(nodes, smp.sampled(c) ? basen + (c >> smp.log2k) : base + c, nxt, acc);
+}
+
+// TOP: the doubling of the last level (nodes [base, base + m)). Otherwise the
+// downward pass of a level: an element that is a ruler takes the record of
+// its node one level up. OUTS: the results go to `out`, else to the nodes.
+// last: the downward pass over the whole list, which must solve every element
+// (any other may leave some of them to it).
+template <bool W, bool TOP, bool OUTS, int PER, class Out>
+__global__ __launch_bounds__(TPB) void k_iw_solve(uint64_t* __restrict__ nodes, Sampler smp, uint32_t base,
+                                                  uint32_t basen, uint32_t total, uint32_t m, uint32_t climit,
+                                                  uint32_t last, uint32_t set_mode, Ctrl* ctrl, Out out,
+                                                  const uint32_t* dm, Gate gate) {
+    if (gate.off()) return;
+    if (dm) m = min(dm[0], m);
+    smp.m = m;
+    using L = Lay<W>;
+    const uint32_t c0 = blockIdx.x * (TPB * PER) + threadIdx.x;
+    if (c0 >= m) return;
+    uint32_t nxt[PER], at[PER];
+    typename L::Val acc[PER];
+    bool ok[PER];
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        const uint32_t c = c0 + r * TPB;
+        nxt[r] = TERM | IDX;
+        at[r] = base + c;
+        if (c < m) {
+            if constexpr (!TOP) {
+                if (smp.sampled(c)) at[r] = basen + (c >> smp.log2k);
+            }
+            ok[r] = IwRec<W>::template load<TOP>(nodes, at[r], nxt[r], acc[r]);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < PER; ++r)
+        if (c0 + r * TPB < m)
+            while (!ok[r]) ok[r] = IwRec<W>::template load<true>(nodes, at[r], nxt[r], acc[r]);
+    const uint32_t cap = last ? NONE : IW_TOP_CAP;
+    for (uint32_t hop = 0; hop < cap; ++hop) {
+        bool any = false;
+#pragma unroll
+        for (int r = 0; r < PER; ++r) any |= !(nxt[r] & TERM);
+        if (!any) break;
+        const bool dbl = TOP || hop >= IW_PATIENCE;
+        if (!TOP && hop == IW_PATIENCE && set_mode) ctrl->mode = MODE_FALLBACK;
+        uint32_t nn[PER];
+        typename L::Val v[PER];
+        // every load of the lane's elements before any is used
+#pragma unroll
+        for (int r = 0; r < PER; ++r) {
+            ok[r] = false;
+            if (nxt[r] < total) ok[r] = dbl ? IwRec<W>::template load<true>(nodes, nxt[r], nn[r], v[r])
+                                            : IwRec<W>::template load<false>(nodes, nxt[r], nn[r], v[r]);
+        }
+#pragma unroll
+        for (int r = 0; r < PER; ++r) {
+            if (nxt[r] & TERM) continue;
+            bool bad = nxt[r] >= total;
+            if (!bad) {
+                if (!ok[r] && !IwRec<W>::template load<true>(nodes, nxt[r], nn[r], v[r])) continue;
+                acc[r] = L::add(acc[r], v[r]);
+                nxt[r] = nn[r];
+                bad = acc[r].c >= climit;
+            }
+            if (bad) {  // more links than the input has: a cycle (or no forest at all)
+                nxt[r] = TERM | IDX;
+                acc[r] = L::junk();
+                atomicOr(&ctrl->err, 16u);
+            }
+            if (dbl) IwRec<W>::store(nodes, at[r], nxt[r], acc[r]);
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < PER; ++r) {
+        const uint32_t c = c0 + r * TPB;
+        if (c >= m) continue;
+        if constexpr (OUTS) {
+            auto cur = out.begin(c);
+            out.store(cur, c, acc[r], nxt[r] & IDX);
+        } else if constexpr (!TOP) {
+            IwRec<W>::store(nodes, base + c, nxt[r], acc[r]);
+        }
+    }
+}
+
 // --------------------------------------------------------------- resolve --
 // Walk S + j of an initial element: its result is its own weight plus the
 // result of the ruler it ended on, or plus nothing when it ended on a
@@ -1033,7 +1286,7 @@ __global__ __launch_bounds__(TPB) void k_resolve(char* __restrict__ eb_raw, uint
             o = L::res(L::val(r), r.nxt & IDX);
         } else if (r.nxt < S) {
             const typename L::Res b = res[r.nxt];
-            o = L::res(L::add(L::val(r), L::val(b)), b.root);
+            o = L::res(L::add(L::val(r), L::val(b)), L::root(b));
         } else {
             o = L::res(L::junk(), NONE);
         }
@@ -1086,7 +1339,7 @@ __global__ __launch_bounds__(TPB) void k_expand(const typename Lay<W>::Slot* __r
             const bool ok = s.w < nw;
             bad |= !ok && (base + j * 64 + lane < m);
             ov[j] = ok ? L::sub(L::val(rv[j]), L::val(s)) : L::junk();
-            orr[j] = ok ? rv[j].root : NONE;
+            orr[j] = ok ? L::root(rv[j]) : NONE;
         }
 #pragma unroll
         for (int j = 0; j < EXPAND_CH; ++j) {
@@ -1327,7 +1580,7 @@ __global__ __launch_bounds__(place_tpb(W, ROOT)) void k_place1(LogArrays<W> lg, 
                     const typename L::Res b = bres[j];
                     const typename L::Val v = L::sub(L::val(b), off);
                     rs[j] = v.c;
-                    ts[j] = b.root;
+                    ts[j] = L::root(b);
                     if constexpr (W) ss[j] = v.s;
                 } else {
                     rs[j] = NONE;
@@ -1750,7 +2003,7 @@ __global__ __launch_bounds__(64) void k_batch_desc(BatchDescArg a, BatchDesc* __
 
 // One workgroup: bases[q] = elements before request q, boff[q] = chunks
 // before it (count + 1 entries each); the header's chunk and element totals;
-// with levels > 0 (device-side sizes) dm[0] = total and dm[l + 1] =
+// dm[0] = total; with levels > 0 (device-side sizes) also dm[l + 1] =
 // ceil(dm[l] / k_l).
 __global__ __launch_bounds__(1024) void k_batch_index(const BatchDesc* __restrict__ d, uint32_t* __restrict__ bases,
                                                       uint32_t* __restrict__ boff, BatchHdr* __restrict__ hdr,
@@ -1780,9 +2033,9 @@ __global__ __launch_bounds__(1024) void k_batch_index(const BatchDesc* __restric
         boff[count] = tc;
         hdr->nchunks = tc;
         hdr->total = tn;
+        uint32_t m = tn;
+        ctrl->dm[0] = m;
         if (levels) {
-            uint32_t m = tn;
-            ctrl->dm[0] = m;
             for (uint32_t l = 0; l < levels; ++l) {
                 m = (m + (1u << ks.lg[l]) - 1u) >> ks.lg[l];
                 ctrl->dm[l + 1] = m;
@@ -2248,7 +2501,7 @@ __global__ __launch_bounds__(TPB) void k_lc_expand(const uint32_t* __restrict__ 
             v.c -= pv[j] & 0xffffu;
             if constexpr (W) v.s -= wv[j];
             ov[j] = ok ? v : L::junk();
-            orr[j] = ok ? rv[j].root : NONE;
+            orr[j] = ok ? L::root(rv[j]) : NONE;
         }
 #pragma unroll
         for (int j = 0; j < EXPAND_CH; ++j) {
@@ -2599,7 +2852,7 @@ __global__ __launch_bounds__(TPB) void k_sp_expand(const typename Lay<W>::Slot* 
             const bool ok = wv[j] < mc;
             bad |= !ok && (base + j * 64 + lane < n);
             ov[j] = ok ? L::sub(L::val(rv[j]), L::val(sv[j])) : L::junk();
-            orr[j] = ok ? rv[j].root : NONE;
+            orr[j] = ok ? L::root(rv[j]) : NONE;
         }
 #pragma unroll
         for (int j = 0; j < EXPAND_CH; ++j) {
@@ -2677,6 +2930,78 @@ static hipError_t launch_base(Src src, Out out, uint32_t m, Ctrl* ctrl, hipStrea
     return hipGetLastError();
 }
 
+// The lists of level p.run and above, by independent walks: levels run ..
+// top - 1 walk, level top is doubled, then downward. The source's results go
+// to `out`; input: the source is the caller's input, whose first kernel sets
+// the path word.
+constexpr int IW_PER = 4;  // elements per lane of the downward pass: all of a list's lanes are resident
+
+template <bool W, class Src, class Out>
+static hipError_t run_iw(const Plan& p, Src src, Out out, uint32_t climit, bool input, Ctrl* ctrl, char* ws,
+                         hipStream_t st, const uint32_t* dm, Gate gate) {
+    uint64_t* nodes = reinterpret_cast<uint64_t*>(ws + p.off_nodes);
+    const uint32_t r0 = p.run, T = p.top;
+    uint32_t base[LR_MAX_LEVELS + 2] = {};
+    for (uint32_t l = r0; l <= T; ++l) base[l + 1] = base[l] + (uint32_t)p.m[l];
+    const uint32_t total = base[T + 1];
+    auto smp = [&](uint32_t l) { return Sampler{(uint32_t)p.m[l], p.log2k[l], p.lseed[l]}; };
+    auto dml = [&](uint32_t l) { return dm ? dm + (l - r0) : nullptr; };
+    auto grid = [](uint64_t m, uint32_t per) { return dim3((uint32_t)((m + TPB * per - 1) / (TPB * per))); };
+    const dim3 b(TPB);
+    const uint32_t m0 = (uint32_t)p.m[r0];
+    if (T == r0) {
+        hipLaunchKernelGGL((k_iw_first<W, false, Src>), grid(m0, 1), b, 0, st, src, Sampler{}, nodes, 0u, m0,
+                           IW_CAP_ALONE, ctrl, (uint32_t)input, dm, gate);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_iw_solve<W, true, true, 1, Out>), grid(m0, 1), b, 0, st, nodes, Sampler{}, 0u, 0u, total,
+                           m0, climit, 1u, 0u, ctrl, out, dm, gate);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL((k_iw_first<W, true, Src>), grid(m0, 1), b, 0, st, src, smp(r0), nodes, base[r0 + 1], m0,
+                       (uint32_t)LR_IW_CAP, ctrl, (uint32_t)input, dm, gate);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    for (uint32_t l = r0 + 1; l < T; ++l) {
+        hipLaunchKernelGGL((k_iw_walk<W>), grid(p.m[l], 1), b, 0, st, nodes, smp(l), base[l], base[l + 1], total,
+                           (uint32_t)p.m[l], (uint32_t)LR_IW_CAP, dml(l), gate);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    const OutLvl<W> none{};
+    hipLaunchKernelGGL((k_iw_solve<W, true, false, 1, OutLvl<W>>), grid(p.m[T], 1), b, 0, st, nodes, Sampler{}, base[T],
+                       total, total, (uint32_t)p.m[T], climit, 0u, 0u, ctrl, none, dml(T), gate);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    for (uint32_t l = T - 1; l > r0; --l) {
+        hipLaunchKernelGGL((k_iw_solve<W, false, false, 1, OutLvl<W>>), grid(p.m[l], 1), b, 0, st, nodes, smp(l),
+                           base[l], base[l + 1], total, (uint32_t)p.m[l], climit, 0u, 0u, ctrl, none, dml(l), gate);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    if (m0 <= (1u << 18))
+        hipLaunchKernelGGL((k_iw_solve<W, false, true, 1, Out>), grid(m0, 1), b, 0, st, nodes, smp(r0), 0u,
+                           base[r0 + 1], total, m0, climit, 1u, (uint32_t)input, ctrl, out, dm, gate);
+    else
+        hipLaunchKernelGGL((k_iw_solve<W, false, true, IW_PER, Out>), grid(m0, IW_PER), b, 0, st, nodes, smp(r0), 0u,
+                           base[r0 + 1], total, m0, climit, 1u, (uint32_t)input, ctrl, out, dm, gate);
+    return hipGetLastError();
+}
+
+// A level's records, ranked in place. Unweighted records that the doubling
+// takes at once are their own nodes.
+template <bool W>
+static hipError_t run_iw_level(const Plan& p, typename Lay<W>::Rec* rec, uint32_t climit, Ctrl* ctrl, char* ws,
+                               hipStream_t st, const uint32_t* dm, Gate gate) {
+    const uint32_t m = (uint32_t)p.m[p.run];
+    if constexpr (!W) {
+        if (p.top == p.run) {
+            hipLaunchKernelGGL((k_iw_solve<false, true, false, 1, OutLvl<false>>), dim3((m + TPB - 1) / TPB), dim3(TPB),
+                               0, st, reinterpret_cast<uint64_t*>(rec), Sampler{}, 0u, 0u, m, m, climit, 1u, 0u, ctrl,
+                               OutLvl<false>{}, dm, gate);
+            return hipGetLastError();
+        }
+    }
+    return run_iw<W>(p, SrcLvl<W>{rec, m}, OutLvl<W>{rec}, climit, false, ctrl, ws, st, dm, gate);
+}
+
 template <bool W>
 static LogArrays<W> log_arrays(char* ws, const Plan& p) {
     LogArrays<W> a{};
@@ -2705,7 +3030,7 @@ static hipError_t launch_chase(const Plan& p, int l, Src src, Sampler smp, Ctrl*
     const uint32_t S = (uint32_t)p.m[l + 1];
     auto* slot = reinterpret_cast<typename L::Slot*>(ws + p.off_slot[l]);
     auto* eb = reinterpret_cast<typename L::Rec*>(ws + p.off_eb[l]);
-    uint8_t* hp_next = (l + 1 < (int)p.levels) ? reinterpret_cast<uint8_t*>(ws + p.off_slot[l + 1]) : nullptr;
+    uint8_t* hp_next = (l + 1 < (int)p.run) ? reinterpret_cast<uint8_t*>(ws + p.off_slot[l + 1]) : nullptr;
     LogArrays<W> lg = LOG != 0 ? log_arrays<W>(ws, p) : LogArrays<W>{};
     hipLaunchKernelGGL(kern, dim3(grid), dim3(CHASE_TPB), 0, st, src, smp, S, ctrl, l, slot, eb, hp_next,
                        p.refill, lg, p.max_chunks, dm, gate);
@@ -2946,8 +3271,9 @@ static hipError_t run_srs_t(const RunArgs& a, Out0 out0) {
         rec_ev(a, EV_START);
         if (a.validate) LR_TRY(run_validate(a, p, n));
     }
-    if (p.levels == 0) {
-        LR_TRY((launch_base<W>(src0, out0, n, ctrl, st, dm_at(0), g)));
+    if (p.run == 0) {
+        if (p.iw) LR_TRY((run_iw<W>(p, src0, out0, n, true, ctrl, ws, st, dm_at(0), g)));
+        else LR_TRY((launch_base<W>(src0, out0, n, ctrl, st, dm_at(0), g)));
         for (int i = EV_DETECT; i < EV_COUNT; ++i) rec_ev(a, i);
         return hipSuccess;
     }
@@ -2968,13 +3294,13 @@ static hipError_t run_srs_t(const RunArgs& a, Out0 out0) {
         }
     }
     rec_ev(a, EV_DETECT);
-    for (uint32_t l = 0; l < p.levels; ++l) {
+    for (uint32_t l = 0; l < p.run; ++l) {
         const uint32_t m = (uint32_t)p.m[l];
         const uint32_t S = (uint32_t)p.m[l + 1];
         const Sampler smp{m, p.log2k[l], p.lseed[l]};
         const uint8_t* hp = reinterpret_cast<const uint8_t*>(ws + p.off_slot[l]);
         uint32_t* tile = reinterpret_cast<uint32_t*>(ws + p.off_tile[l]);
-        const bool more = l + 1 < p.levels;
+        const bool more = l + 1 < p.run;
         uint32_t* zp = more ? reinterpret_cast<uint32_t*>(ws + p.off_slot[l + 1]) : nullptr;
         const uint32_t zw = more ? (S + 3) / 4 : 0;
         const uint32_t gt = std::min<uint32_t>(p.ntiles[l], (uint32_t)device_cus() * 8);
@@ -3021,13 +3347,17 @@ static hipError_t run_srs_t(const RunArgs& a, Out0 out0) {
         }
     }
     {
-        const uint32_t L_ = p.levels;
+        const uint32_t L_ = p.run;
         const uint32_t mL = (uint32_t)p.m[L_];
-        SrcLvl<W> src{reinterpret_cast<const typename L::Rec*>(ws + p.off_eb[L_ - 1]), mL};
-        OutLvl<W> out{reinterpret_cast<typename L::Res*>(ws + p.off_eb[L_ - 1])};
-        LR_TRY((launch_base<W>(src, out, mL, ctrl, st, dm_at(L_), g)));
+        auto* top = reinterpret_cast<typename L::Rec*>(ws + p.off_eb[L_ - 1]);
+        if (p.iw) {
+            LR_TRY((run_iw_level<W>(p, top, n, ctrl, ws, st, dm_at(L_), g)));
+        } else {
+            SrcLvl<W> src{top, mL};
+            LR_TRY((launch_base<W>(src, OutLvl<W>{top}, mL, ctrl, st, dm_at(L_), g)));
+        }
     }
-    for (int l = (int)p.levels - 1; l >= 0; --l) {
+    for (int l = (int)p.run - 1; l >= 0; --l) {
         const uint32_t m = (uint32_t)p.m[l];
         const uint32_t S = (uint32_t)p.m[l + 1];
         hipLaunchKernelGGL(k_resolve<W>, dim3(grid_for(m, TPB * 4, 4)), dim3(TPB), 0, st, ws + p.off_eb[l], S,
@@ -3065,7 +3395,7 @@ static hipError_t run_clevels(const RunArgs& a, const Plan& p, typename Lay<W>::
     using L = Lay<W>;
     char* ws = a.ws;
     hipStream_t st = a.stream;
-    const uint32_t Lv = p.levels;
+    const uint32_t Lv = p.run;
     for (uint32_t l = 0; l < Lv; ++l) {
         const uint32_t* dm = &ctrl->dm[l];
         const Sampler smp{(uint32_t)p.m[l], p.log2k[l], p.lseed[l]};
@@ -3101,9 +3431,13 @@ static hipError_t run_clevels(const RunArgs& a, const Plan& p, typename Lay<W>::
     }
     {
         auto* top = Lv ? reinterpret_cast<typename L::Rec*>(ws + p.off_eb[Lv - 1]) : lrec;
-        SrcLvl<W> src{top, (uint32_t)p.m[Lv]};
-        OutLvl<W> out{reinterpret_cast<typename L::Res*>(top)};
-        LR_TRY((launch_base<W>(src, out, (uint32_t)p.m[Lv], ctrl, st, &ctrl->dm[Lv], g)));
+        if (p.iw) {
+            const uint32_t climit = (uint32_t)(p.spawn ? p.sp_n : p.lc_n);
+            LR_TRY((run_iw_level<W>(p, top, climit, ctrl, ws, st, &ctrl->dm[Lv], g)));
+        } else {
+            SrcLvl<W> src{top, (uint32_t)p.m[Lv]};
+            LR_TRY((launch_base<W>(src, OutLvl<W>{top}, (uint32_t)p.m[Lv], ctrl, st, &ctrl->dm[Lv], g)));
+        }
     }
     for (int l = (int)Lv - 1; l >= 0; --l) {
         const uint32_t m = (uint32_t)p.m[l];
@@ -3141,7 +3475,7 @@ static hipError_t run_local_t(const RunArgs& a, Out0 out0) {
     const Gate g = a.gate;
     Ctrl* ctrl = reinterpret_cast<Ctrl*>(ws + p.off_ctrl);
     const uint32_t n = (uint32_t)p.lc_n;
-    const uint32_t Lv = p.levels;
+    const uint32_t Lv = p.run;
     if (a.prologue) {
         rec_ev(a, EV_START);
         if (a.validate) LR_TRY(run_validate(a, p, n));
@@ -3162,8 +3496,8 @@ static hipError_t run_local_t(const RunArgs& a, Out0 out0) {
                        stage, pos, wd, ctrl, gpre);
     LR_TRY(hipGetLastError());
     LevelShifts ks{};
-    for (uint32_t l = 0; l < Lv; ++l) ks.lg[l] = (uint8_t)p.log2k[l];
-    hipLaunchKernelGGL(k_lc_scan, dim3(1), dim3(1024), 0, st, cnt, p.lc_ntiles, ctrl, Lv, ks, (uint32_t)p.m[0],
+    for (uint32_t l = 0; l < p.levels; ++l) ks.lg[l] = (uint8_t)p.log2k[l];
+    hipLaunchKernelGGL(k_lc_scan, dim3(1), dim3(1024), 0, st, cnt, p.lc_ntiles, ctrl, p.levels, ks, (uint32_t)p.m[0],
                        (uint32_t)a.prologue, gpre);
     LR_TRY(hipGetLastError());
     rec_ev(a, EV_DETECT);
@@ -3199,7 +3533,7 @@ static hipError_t run_spawn_t(const RunArgs& a, Out0 out0) {
     const Gate g = a.gate;
     Ctrl* ctrl = reinterpret_cast<Ctrl*>(ws + p.off_ctrl);
     const uint32_t n = (uint32_t)p.sp_n;
-    const uint32_t Lv = p.levels;
+    const uint32_t Lv = p.run;
     if (a.prologue) {
         rec_ev(a, EV_START);
         if (a.validate) LR_TRY(run_validate(a, p, n));
@@ -3271,8 +3605,8 @@ static hipError_t run_spawn_t(const RunArgs& a, Out0 out0) {
         LR_TRY(hipGetLastError());
     }
     LevelShifts ks{};
-    for (uint32_t l = 0; l < Lv; ++l) ks.lg[l] = (uint8_t)p.log2k[l];
-    hipLaunchKernelGGL(k_sp_publish, dim3(1), dim3(64), 0, st, ctrl, S0, (uint32_t)p.m[0], Lv, ks, g);
+    for (uint32_t l = 0; l < p.levels; ++l) ks.lg[l] = (uint8_t)p.log2k[l];
+    hipLaunchKernelGGL(k_sp_publish, dim3(1), dim3(64), 0, st, ctrl, S0, (uint32_t)p.m[0], p.levels, ks, g);
     LR_TRY(hipGetLastError());
     rec_ev(a, EV_CHASE0);
     LR_TRY(run_clevels<W>(a, p, lrec, ctrl, g, false));
@@ -3359,13 +3693,12 @@ static hipError_t run_fallback_t(const RunArgs& a, Out0 out0) {
 // walk stops at its cap, every other kernel is bounded whatever its input),
 // and the fallback then overwrites its outputs. Under automatic contraction
 // both paths are gated on the mode anyway, so they stop at once. A plan
-// without levels (the base case alone) has no walks and no fallback.
+// without chased levels (the base case, or independent walks) has no fallback.
 template <bool W, int WT, class Out0>
 static hipError_t run_any_t(const RunArgs& a, Out0 out0) {
     const Plan& p = *a.plan;
-    const bool walks = p.levels >= 1 || p.spawn;
     LR_TRY((run_path_t<W, WT>(a, out0)));
-    return walks ? run_fallback_t<W, WT>(a, out0) : hipSuccess;
+    return p.walks() ? run_fallback_t<W, WT>(a, out0) : hipSuccess;
 }
 
 template <int WT>
@@ -3552,8 +3885,8 @@ hipError_t run_debug_check(const RunArgs& a, const Plan& p) {
     uint32_t levels = 0;
     if (plain) {
         size_t off = p.off_dbg;
-        levels = p.levels;
-        for (uint32_t l = 0; l < p.levels; ++l) {
+        levels = p.run;
+        for (uint32_t l = 0; l < p.run; ++l) {
             d.slot[l] = reinterpret_cast<uint32_t*>(a.ws + off);
             d.mark[l] = d.slot[l] + p.m[l];
             sz.m[l] = (uint32_t)p.m[l];

@@ -144,9 +144,58 @@ constexpr uint32_t BATCH_CHUNK = 4096;
 constexpr uint32_t BATCH_ARG_DESC = 96;  // request descriptors passed by value per table-writer launch
 inline size_t batch_table_bytes(uint32_t count) { return 2 * ((size_t)count + 1) * 4; }
 
+// Independent walks (k_iw_*): with the planner's own plan a call chases its
+// levels only until one holds at most iw_max elements; that one and the
+// levels above it are ranked by independent walks, from the first level of at
+// most iw_top elements on by asynchronous doubling. Inputs of more than
+// IW_DIRECT_MIN (weighted: of more than the base case takes) and fewer than
+// iw_direct elements are not chased at all.
+// Measured (random lists, rank and root; weighted: int64, every output; us a
+// call, same box), the other side of each line first:
+//   chase and base case -> independent walks: 2^15 83 -> 27, 2^18 117 -> 41,
+//     2^20 185 -> 89, 1.5 * 2^20 150 (one chased level) -> 130; weighted 2^17
+//     113 -> 59, 2^18 136 -> 79, 1.4 * 2^18 133 (one chased level) -> 101, but
+//     1.4 * 2^19 152 -> 168: a weighted step reads two arrays
+//   iw_max 2^18 -> 2^20: 1.5 * 2^22 459 -> 414, 1.5 * 2^24 1398 -> 1350
+//   iw_top 2^14 -> 2^16: 1.5 * 2^17 46 -> 39, forest 2^16 20 -> 16; above, the
+//     doubling's device-scope reads saturate (2^16 33 alone, 27 below one level
+//     of walks); weighted (three words a record) 1.4 * 2^14 41 at 2^14, 44 at 2^15
+// iw_direct stays below the automatic contraction's first size.
+#ifndef LR_IW_MAX_LOG2
+#define LR_IW_MAX_LOG2 20
+#endif
+#ifndef LR_IW_MAX_LOG2_W
+#define LR_IW_MAX_LOG2_W 19
+#endif
+#ifndef LR_IW_DIRECT_LOG2
+#define LR_IW_DIRECT_LOG2 21
+#endif
+#ifndef LR_IW_DIRECT_LOG2_W
+#define LR_IW_DIRECT_LOG2_W 19
+#endif
+#ifndef LR_IW_DIRECT_MIN
+#define LR_IW_DIRECT_MIN 4096
+#endif
+#ifndef LR_IW_TOP_LOG2
+#define LR_IW_TOP_LOG2 16
+#endif
+#ifndef LR_IW_TOP_LOG2_W
+#define LR_IW_TOP_LOG2_W 14
+#endif
+constexpr uint64_t iw_max(bool weighted) { return 1ull << (weighted ? LR_IW_MAX_LOG2_W : LR_IW_MAX_LOG2); }
+constexpr uint64_t iw_direct(bool weighted) { return 1ull << (weighted ? LR_IW_DIRECT_LOG2_W : LR_IW_DIRECT_LOG2); }
+constexpr uint64_t iw_top(bool weighted) { return 1ull << (weighted ? LR_IW_TOP_LOG2_W : LR_IW_TOP_LOG2); }
+constexpr size_t iw_node_bytes(bool weighted) { return weighted ? 24 : 8; }
+static_assert(LR_IW_MAX_LOG2 <= 21 && LR_IW_MAX_LOG2_W <= 21, "every lane of the downward pass is resident at once");
+static_assert(iw_direct(false) <= LOCAL_AUTO_MIN_N && iw_direct(true) <= LOCAL_AUTO_MIN_N,
+              "an input ranked by independent walks alone has no contracted path beside it");
+
 struct Plan {
     bool weighted = false;
     uint32_t levels = 0;                   // ruling-set levels before the base case
+    uint32_t run = 0;                      // levels that are chased (fewer than `levels` with iw)
+    bool iw = false;                       // levels from `run` on by independent walks, `top` by doubling
+    uint32_t top = 0;
     uint32_t base_max = 0;
     uint64_t m[LR_MAX_LEVELS + 1] = {};
     uint32_t log2k[LR_MAX_LEVELS] = {};
@@ -201,8 +250,10 @@ struct Plan {
     size_t off_sp_slot = 0;  // per element: walk id (flagged for spawned rulers) and offset
     size_t off_sp_hp = 0;    // per element: has-a-predecessor byte
     size_t off_sp_tile = 0;  // head counts per tile, scanned in place
+    size_t off_nodes = 0;    // nodes of the independent walks: over arrays of the levels that are not chased
     size_t off_dbg = 0;      // debug builds: per level, slot then mark write counters (4 B each)
     size_t total = 0;
+    bool walks() const { return run >= 1 || spawn; }  // some walk may reach its cap
 };
 
 // The plans of one call: p runs alone, or, with automatic contraction

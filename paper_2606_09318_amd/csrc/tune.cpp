@@ -214,12 +214,21 @@ lr_status lr_autotune(const uint32_t* succ, const void* weight, lr_wtype w, uint
         }
         return true;
     };
-    // stage 1: spacing of the first two levels; stage 2: the base case size;
+    // stage 1: the planner's plan, then other spacings of the first two levels; stage 2: the base case size;
     // stage 3: walks per lane and refill threshold (each stage keeps the best
     // so far and varies one group)
     const uint32_t k0s[] = {16, 32, 64, 128};
     const uint32_t k1s[] = {8, 16, 32};
+    {  // the planner's own plan
+        lr_opts o = b;
+        for (int l = 0; l < LR_MAX_LEVELS; ++l) o.spacing[l] = 0;
+        o.base_max = 0;
+        if (!o.lane_walks) o.lane_walks = 1;  // a plan option set: the cache is not consulted
+        float t;
+        (void)trial(o, &t);
+    }
     for (uint32_t k0 : k0s) {
+        if (result != LR_OK) break;
         for (uint32_t k1 : k1s) {
             lr_opts o = b;
             for (int l = 0; l < LR_MAX_LEVELS; ++l) o.spacing[l] = 0;
