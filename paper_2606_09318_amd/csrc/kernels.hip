@@ -1021,11 +1021,11 @@ __global__ __launch_bounds__(BASE_TPB) void k_base(Src src, Out out, uint32_t m,
 //               takes one, but the reads hit the caches, nothing is scattered,
 //               and no walk is longer than the cap.
 //   k_iw_walk   the same on the rulers, to the rulers of the next level.
-//   k_iw_solve  on the last level: asynchronous pointer doubling, every
+//   k_iw_double on the last level: asynchronous pointer doubling, every
 //               element's record composed with the record it points to until
-//               it has reached a terminal; then, level by level downward,
-//               every element composes its record with its ruler's (solved)
-//               one.
+//               it has reached a terminal.
+//   k_iw_down   then, level by level downward, every element composes its
+//               record with its ruler's (solved) one.
 // Nodes: one record (nxt, value) per element of every level, in one array;
 // level j's nodes start at base_j. A record says that following the list from
 // its element for `value` leads to node nxt or, with nxt = TERM | t, to the
@@ -1182,75 +1182,117 @@ __global__ __launch_bounds__(TPB) void k_iw_walk(uint64_t* __restrict__ nodes, S
     IwRec<W>::store(nodes, smp.sampled(c) ? basen + (c >> smp.log2k) : base + c, nxt, acc);
 }
 
-// TOP: the doubling of the last level (nodes [base, base + m)). Otherwise the
-// downward pass of a level: an element that is a ruler takes the record of
-// its node one level up. OUTS: the results go to `out`, else to the nodes.
-// last: the downward pass over the whole list, which must solve every element
-// (any other may leave some of them to it).
-template <bool W, bool TOP, bool OUTS, int PER, class Out>
-__global__ __launch_bounds__(TPB) void k_iw_solve(uint64_t* __restrict__ nodes, Sampler smp, uint32_t base,
-                                                  uint32_t basen, uint32_t total, uint32_t m, uint32_t climit,
-                                                  uint32_t last, uint32_t set_mode, Ctrl* ctrl, Out out,
-                                                  const uint32_t* dm, Gate gate) {
+// The doubling of the last level, nodes [base, base + m). OUTS: the results go
+// to `out`, else they stay in the nodes. cap: hops after which an element is
+// left to the downward pass. A hop's stores are awaited before the next hop's
+// load: a load that runs ahead of the others' stores finds the records of the
+// round before, and its element needs a hop more (2^16 elements 28 us, 31
+// without the wait; weighted 100,003 43 against 49). Single-wave workgroups
+// spread a few hundred waves over all CUs (weighted 100,003 elements 43 us, 51
+// with 256 lanes; unweighted 1 us).
+constexpr uint32_t IW_DBL_TPB = 64;
+template <bool W, bool OUTS, class Out>
+__global__ __launch_bounds__(IW_DBL_TPB) void k_iw_double(uint64_t* __restrict__ nodes, uint32_t base, uint32_t total,
+                                                          uint32_t m, uint32_t climit, uint32_t cap, Ctrl* ctrl,
+                                                          Out out, const uint32_t* dm, Gate gate) {
+    if (gate.off()) return;
+    if (dm) m = min(dm[0], m);
+    using L = Lay<W>;
+    const uint32_t c = blockIdx.x * IW_DBL_TPB + threadIdx.x;
+    if (c >= m) return;
+    uint32_t nxt;
+    typename L::Val acc;
+    while (!IwRec<W>::template load<true>(nodes, base + c, nxt, acc)) {}
+    for (uint32_t hop = 0; !(nxt & TERM) && hop < cap; ++hop) {
+        bool bad = nxt >= total;
+        if (!bad) {
+            if (!iw_hop<W, true>(nodes, nxt, acc)) continue;
+            bad = acc.c >= climit;
+        }
+        if (bad) {  // more links than the input has: a cycle (or no forest at all)
+            nxt = TERM | IDX;
+            acc = L::junk();
+            atomicOr(&ctrl->err, 16u);
+        }
+        IwRec<W>::store(nodes, base + c, nxt, acc);
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
+    }
+    if constexpr (OUTS) {
+        auto cur = out.begin(c);
+        out.store(cur, c, acc, nxt & IDX);
+    }
+}
+
+// The downward pass of a level: every element composes its record with its
+// ruler's solved one; an element that is a ruler takes the record of its node
+// one level up. OUTS: the results go to `out`, else to the nodes. last: the
+// pass over the whole list, which must solve every element (any other may
+// leave some of them to it). PER elements a lane, the loads of all issued
+// before any is used.
+template <bool W, bool OUTS, int PER, class Out>
+__global__ __launch_bounds__(TPB) void k_iw_down(uint64_t* __restrict__ nodes, Sampler smp, uint32_t base,
+                                                 uint32_t basen, uint32_t total, uint32_t m, uint32_t climit,
+                                                 uint32_t last, uint32_t set_mode, Ctrl* ctrl, Out out,
+                                                 const uint32_t* dm, Gate gate) {
     if (gate.off()) return;
     if (dm) m = min(dm[0], m);
     smp.m = m;
     using L = Lay<W>;
     const uint32_t c0 = blockIdx.x * (TPB * PER) + threadIdx.x;
     if (c0 >= m) return;
-    uint32_t nxt[PER], at[PER];
-    typename L::Val acc[PER];
+    uint32_t nxt[PER], at[PER], nn[PER];
+    typename L::Val acc[PER], v[PER];
     bool ok[PER];
 #pragma unroll
     for (int r = 0; r < PER; ++r) {
         const uint32_t c = c0 + r * TPB;
         nxt[r] = TERM | IDX;
         at[r] = base + c;
+        ok[r] = true;
         if (c < m) {
-            if constexpr (!TOP) {
-                if (smp.sampled(c)) at[r] = basen + (c >> smp.log2k);
-            }
-            ok[r] = IwRec<W>::template load<TOP>(nodes, at[r], nxt[r], acc[r]);
+            if (smp.sampled(c)) at[r] = basen + (c >> smp.log2k);
+            ok[r] = IwRec<W>::template load<false>(nodes, at[r], nxt[r], acc[r]);
         }
     }
 #pragma unroll
     for (int r = 0; r < PER; ++r)
-        if (c0 + r * TPB < m)
-            while (!ok[r]) ok[r] = IwRec<W>::template load<true>(nodes, at[r], nxt[r], acc[r]);
+        while (!ok[r]) ok[r] = IwRec<W>::template load<true>(nodes, at[r], nxt[r], acc[r]);
+    // the record each element looks at next
+    auto look = [&](int r, bool dbl) {
+        ok[r] = false;
+        if (nxt[r] < total) ok[r] = dbl ? IwRec<W>::template load<true>(nodes, nxt[r], nn[r], v[r])
+                                        : IwRec<W>::template load<false>(nodes, nxt[r], nn[r], v[r]);
+    };
     const uint32_t cap = last ? NONE : IW_TOP_CAP;
+#pragma unroll
+    for (int r = 0; r < PER; ++r) look(r, false);
     for (uint32_t hop = 0; hop < cap; ++hop) {
         bool any = false;
 #pragma unroll
         for (int r = 0; r < PER; ++r) any |= !(nxt[r] & TERM);
         if (!any) break;
-        const bool dbl = TOP || hop >= IW_PATIENCE;
-        if (!TOP && hop == IW_PATIENCE && set_mode) ctrl->mode = MODE_FALLBACK;
-        uint32_t nn[PER];
-        typename L::Val v[PER];
-        // every load of the lane's elements before any is used
-#pragma unroll
-        for (int r = 0; r < PER; ++r) {
-            ok[r] = false;
-            if (nxt[r] < total) ok[r] = dbl ? IwRec<W>::template load<true>(nodes, nxt[r], nn[r], v[r])
-                                            : IwRec<W>::template load<false>(nodes, nxt[r], nn[r], v[r]);
-        }
+        const bool dbl = hop >= IW_PATIENCE;
+        if (hop == IW_PATIENCE && set_mode) ctrl->mode = MODE_FALLBACK;
 #pragma unroll
         for (int r = 0; r < PER; ++r) {
             if (nxt[r] & TERM) continue;
             bool bad = nxt[r] >= total;
+            // caught between two of its stores (weighted): look again
+            if (!bad && !ok[r] && !IwRec<W>::template load<true>(nodes, nxt[r], nn[r], v[r])) continue;
             if (!bad) {
-                if (!ok[r] && !IwRec<W>::template load<true>(nodes, nxt[r], nn[r], v[r])) continue;
                 acc[r] = L::add(acc[r], v[r]);
                 nxt[r] = nn[r];
                 bad = acc[r].c >= climit;
             }
-            if (bad) {  // more links than the input has: a cycle (or no forest at all)
+            if (bad) {
                 nxt[r] = TERM | IDX;
                 acc[r] = L::junk();
                 atomicOr(&ctrl->err, 16u);
             }
             if (dbl) IwRec<W>::store(nodes, at[r], nxt[r], acc[r]);
         }
+#pragma unroll
+        for (int r = 0; r < PER; ++r) look(r, dbl);
     }
 #pragma unroll
     for (int r = 0; r < PER; ++r) {
@@ -1259,7 +1301,7 @@ __global__ __launch_bounds__(TPB) void k_iw_solve(uint64_t* __restrict__ nodes, 
         if constexpr (OUTS) {
             auto cur = out.begin(c);
             out.store(cur, c, acc[r], nxt[r] & IDX);
-        } else if constexpr (!TOP) {
+        } else {
             IwRec<W>::store(nodes, base + c, nxt[r], acc[r]);
         }
     }
@@ -2947,6 +2989,7 @@ static hipError_t run_iw(const Plan& p, Src src, Out out, uint32_t climit, bool 
     auto smp = [&](uint32_t l) { return Sampler{(uint32_t)p.m[l], p.log2k[l], p.lseed[l]}; };
     auto dml = [&](uint32_t l) { return dm ? dm + (l - r0) : nullptr; };
     auto grid = [](uint64_t m, uint32_t per) { return dim3((uint32_t)((m + TPB * per - 1) / (TPB * per))); };
+    auto gtop = [](uint64_t m) { return dim3((uint32_t)((m + IW_DBL_TPB - 1) / IW_DBL_TPB)); };
     const dim3 b(TPB);
     const uint32_t m0 = (uint32_t)p.m[r0];
     if (T == r0) {
@@ -2954,8 +2997,8 @@ static hipError_t run_iw(const Plan& p, Src src, Out out, uint32_t climit, bool 
                            IW_CAP_ALONE, ctrl, (uint32_t)input, dm, gate);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_iw_solve<W, true, true, 1, Out>), grid(m0, 1), b, 0, st, nodes, Sampler{}, 0u, 0u, total,
-                           m0, climit, 1u, 0u, ctrl, out, dm, gate);
+        hipLaunchKernelGGL((k_iw_double<W, true, Out>), gtop(m0), dim3(IW_DBL_TPB), 0, st, nodes, 0u, total, m0, climit,
+                           NONE, ctrl, out, dm, gate);
         return hipGetLastError();
     }
     hipLaunchKernelGGL((k_iw_first<W, true, Src>), grid(m0, 1), b, 0, st, src, smp(r0), nodes, base[r0 + 1], m0,
@@ -2968,19 +3011,19 @@ static hipError_t run_iw(const Plan& p, Src src, Out out, uint32_t climit, bool 
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     const OutLvl<W> none{};
-    hipLaunchKernelGGL((k_iw_solve<W, true, false, 1, OutLvl<W>>), grid(p.m[T], 1), b, 0, st, nodes, Sampler{}, base[T],
-                       total, total, (uint32_t)p.m[T], climit, 0u, 0u, ctrl, none, dml(T), gate);
+    hipLaunchKernelGGL((k_iw_double<W, false, OutLvl<W>>), gtop(p.m[T]), dim3(IW_DBL_TPB), 0, st, nodes, base[T], total,
+                       (uint32_t)p.m[T], climit, IW_TOP_CAP, ctrl, none, dml(T), gate);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     for (uint32_t l = T - 1; l > r0; --l) {
-        hipLaunchKernelGGL((k_iw_solve<W, false, false, 1, OutLvl<W>>), grid(p.m[l], 1), b, 0, st, nodes, smp(l),
+        hipLaunchKernelGGL((k_iw_down<W, false, 1, OutLvl<W>>), grid(p.m[l], 1), b, 0, st, nodes, smp(l),
                            base[l], base[l + 1], total, (uint32_t)p.m[l], climit, 0u, 0u, ctrl, none, dml(l), gate);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (m0 <= (1u << 18))
-        hipLaunchKernelGGL((k_iw_solve<W, false, true, 1, Out>), grid(m0, 1), b, 0, st, nodes, smp(r0), 0u,
+        hipLaunchKernelGGL((k_iw_down<W, true, 1, Out>), grid(m0, 1), b, 0, st, nodes, smp(r0), 0u,
                            base[r0 + 1], total, m0, climit, 1u, (uint32_t)input, ctrl, out, dm, gate);
     else
-        hipLaunchKernelGGL((k_iw_solve<W, false, true, IW_PER, Out>), grid(m0, IW_PER), b, 0, st, nodes, smp(r0), 0u,
+        hipLaunchKernelGGL((k_iw_down<W, true, IW_PER, Out>), grid(m0, IW_PER), b, 0, st, nodes, smp(r0), 0u,
                            base[r0 + 1], total, m0, climit, 1u, (uint32_t)input, ctrl, out, dm, gate);
     return hipGetLastError();
 }
@@ -2993,8 +3036,8 @@ static hipError_t run_iw_level(const Plan& p, typename Lay<W>::Rec* rec, uint32_
     const uint32_t m = (uint32_t)p.m[p.run];
     if constexpr (!W) {
         if (p.top == p.run) {
-            hipLaunchKernelGGL((k_iw_solve<false, true, false, 1, OutLvl<false>>), dim3((m + TPB - 1) / TPB), dim3(TPB),
-                               0, st, reinterpret_cast<uint64_t*>(rec), Sampler{}, 0u, 0u, m, m, climit, 1u, 0u, ctrl,
+            hipLaunchKernelGGL((k_iw_double<false, false, OutLvl<false>>), dim3((m + IW_DBL_TPB - 1) / IW_DBL_TPB),
+                               dim3(IW_DBL_TPB), 0, st, reinterpret_cast<uint64_t*>(rec), 0u, m, m, climit, NONE, ctrl,
                                OutLvl<false>{}, dm, gate);
             return hipGetLastError();
         }
