@@ -357,4 +357,71 @@ __device__ __forceinline__ uint32_t mbcnt(uint64_t mask) {
                                      __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u));
 }
 
+// Exclusive block scan (all lanes get their prefix; *total = block sum).
+__device__ __forceinline__ uint32_t block_exscan(uint32_t v, uint32_t* sh, uint32_t* total) {
+    const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    uint32_t inc = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t y = __shfl_up(inc, o);
+        if (lane >= (uint32_t)o) inc += y;
+    }
+    if (lane == 63) sh[wv] = inc;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+    const uint32_t nw = blockDim.x / 64;
+    for (uint32_t i = 0; i < nw; ++i) {
+        const uint32_t s = sh[i];
+        if (i < wv) before += s;
+        all += s;
+    }
+    *total = all;
+    return before + inc - v;
+}
+
+// In-place exclusive scan of a[0, n) by one workgroup of 1024 lanes; returns
+// the total to every lane. Each lane owns a contiguous run of a multiple of 4
+// entries, read and written as 16-byte vectors, so both passes issue all of a
+// lane's loads at once (a must be 16-byte aligned).
+__device__ __forceinline__ uint32_t wg_exscan_inplace(uint32_t* __restrict__ a, uint32_t n, uint32_t* sh) {
+    const uint32_t per = (((n + blockDim.x - 1u) / blockDim.x) + 3u) & ~3u;
+    const uint32_t lo = min(threadIdx.x * per, n);
+    const uint32_t hi = min(lo + per, n);
+    const uint32_t nv = (hi - lo) >> 2;  // whole vectors; the rest one by one
+    uint4* av = reinterpret_cast<uint4*>(a + lo);
+    uint32_t s = 0;
+    for (uint32_t k = 0; k < nv; ++k) {
+        const uint4 v = av[k];
+        s += v.x + v.y + v.z + v.w;
+    }
+    for (uint32_t i = lo + 4 * nv; i < hi; ++i) s += a[i];
+    uint32_t total;
+    uint32_t run = block_exscan(s, sh, &total);
+    for (uint32_t k = 0; k < nv; ++k) {
+        const uint4 v = av[k];
+        uint4 o;
+        o.x = run;
+        o.y = o.x + v.x;
+        o.z = o.y + v.y;
+        o.w = o.z + v.z;
+        run = o.w + v.w;
+        av[k] = o;
+    }
+    for (uint32_t i = lo + 4 * nv; i < hi; ++i) {
+        const uint32_t v = a[i];
+        a[i] = run;
+        run += v;
+    }
+    return total;
+}
+
+// 32 mark bytes (0 or 1, two vectors in id order) -> 32 bits.
+__device__ __forceinline__ uint32_t mark_bits(uint4 a, uint4 b) {
+    const uint32_t w[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    uint32_t bits = 0;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) bits |= ((w[k] * 0x10204080u) >> 28) << (4 * k);  // the four bytes' low bits
+    return bits;
+}
+
 }  // namespace lr

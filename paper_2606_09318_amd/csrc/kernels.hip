@@ -374,64 +374,6 @@ __device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t* sh) {
     return t;
 }
 
-// Exclusive block scan (all lanes get their prefix; *total = block sum).
-__device__ __forceinline__ uint32_t block_exscan(uint32_t v, uint32_t* sh, uint32_t* total) {
-    const uint32_t lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    uint32_t inc = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const uint32_t y = __shfl_up(inc, o);
-        if (lane >= (uint32_t)o) inc += y;
-    }
-    if (lane == 63) sh[wv] = inc;
-    __syncthreads();
-    uint32_t before = 0, all = 0;
-    const uint32_t nw = blockDim.x / 64;
-    for (uint32_t i = 0; i < nw; ++i) {
-        const uint32_t s = sh[i];
-        if (i < wv) before += s;
-        all += s;
-    }
-    *total = all;
-    return before + inc - v;
-}
-
-// In-place exclusive scan of a[0, n) by one workgroup of 1024 lanes; returns
-// the total to every lane. Each lane owns a contiguous run of a multiple of 4
-// entries, read and written as 16-byte vectors, so both passes issue all of a
-// lane's loads at once (a must be 16-byte aligned).
-__device__ uint32_t wg_exscan_inplace(uint32_t* __restrict__ a, uint32_t n, uint32_t* sh) {
-    const uint32_t per = (((n + blockDim.x - 1u) / blockDim.x) + 3u) & ~3u;
-    const uint32_t lo = min(threadIdx.x * per, n);
-    const uint32_t hi = min(lo + per, n);
-    const uint32_t nv = (hi - lo) >> 2;  // whole vectors; the rest one by one
-    uint4* av = reinterpret_cast<uint4*>(a + lo);
-    uint32_t s = 0;
-    for (uint32_t k = 0; k < nv; ++k) {
-        const uint4 v = av[k];
-        s += v.x + v.y + v.z + v.w;
-    }
-    for (uint32_t i = lo + 4 * nv; i < hi; ++i) s += a[i];
-    uint32_t total;
-    uint32_t run = block_exscan(s, sh, &total);
-    for (uint32_t k = 0; k < nv; ++k) {
-        const uint4 v = av[k];
-        uint4 o;
-        o.x = run;
-        o.y = o.x + v.x;
-        o.z = o.y + v.y;
-        o.w = o.z + v.z;
-        run = o.w + v.w;
-        av[k] = o;
-    }
-    for (uint32_t i = lo + 4 * nv; i < hi; ++i) {
-        const uint32_t v = a[i];
-        a[i] = run;
-        run += v;
-    }
-    return total;
-}
-
 constexpr int SPL = MAXL - 1;  // Ctrl level entry of the spawning path's input level
 
 // Counts, per tile of TILE elements, the initial elements that are not
@@ -1827,14 +1769,13 @@ __global__ __launch_bounds__(TPB) void k_pair(const uint32_t* __restrict__ succ,
 // placement passes (ids only) and each range of 2^s2 ids writes its marks
 // from LDS in order. Every id is the target of at most one link, so no range
 // receives more targets than it has ids.
-// TGT: the input is a plain list of nin target ids below n (entry `skip`
-// excluded) instead of a successor array of n entries.
+// TGT: the input is a plain list of nin target ids (those not below n are
+// skipped) instead of a successor array of n entries.
 template <bool VEC, bool TGT = false>
 __global__ __launch_bounds__(place_tpb(false, false)) void k_mark1(const uint32_t* __restrict__ succ, uint32_t n, uint32_t s1,
                                                             uint32_t nb1, uint32_t* __restrict__ fill1,
                                                             PlaceArrays<false> out, Ctrl* ctrl, Gate gate,
-                                                            uint32_t nin = 0, uint32_t skip = NONE,
-                                                            const uint32_t* dm = nullptr) {
+                                                            const uint32_t* dm, uint32_t nin = 0) {
     if (gate.off()) return;
     extern __shared__ __align__(16) unsigned char lds[];
     constexpr int PER = place_per<false, false>();
@@ -1861,8 +1802,8 @@ __global__ __launch_bounds__(place_tpb(false, false)) void k_mark1(const uint32_
         for (int j = 0; j < PER; ++j) {
             const uint32_t i = tile * T + j * TPB_ + threadIdx.x;
             const uint32_t s = ns[j];
-            if constexpr (TGT) xs[j] = (i != skip && s < n) ? s : NONE;  // a target id
-            else xs[j] = (s != i && s < n) ? s : NONE;                  // the target of a link
+            if constexpr (TGT) xs[j] = s < n ? s : NONE;  // a target id
+            else xs[j] = (s != i && s < n) ? s : NONE;    // the target of a link
             bs[j] = xs[j] >> s1;
         }
         if (tile + gridDim.x < tiles) load_tile(tile + gridDim.x);
@@ -1872,13 +1813,10 @@ __global__ __launch_bounds__(place_tpb(false, false)) void k_mark1(const uint32_
 
 // One workgroup per fine range: the range's targets set bytes in LDS, then
 // the range's marks are written in order (all n bytes get written).
-// WEIGHTS: write +1 for a marked id and -1 for the others (as int8) instead
-// of 1 / 0.
-template <bool WEIGHTS = false>
 __global__ __launch_bounds__(place_tpb(false, false)) void k_mark3(const uint32_t* __restrict__ tx, uint32_t n, uint32_t s2,
                                                             uint32_t nb2, const uint32_t* __restrict__ fill2,
                                                             uint8_t* __restrict__ hp, Gate gate,
-                                                            const uint32_t* dm = nullptr) {
+                                                            const uint32_t* dm) {
     if (gate.off()) return;
     extern __shared__ __align__(16) unsigned char lds[];
     uint32_t* mk = reinterpret_cast<uint32_t*>(lds);
@@ -1907,14 +1845,52 @@ __global__ __launch_bounds__(place_tpb(false, false)) void k_mark3(const uint32_
         __syncthreads();
         if ((len & 3) == 0) {
             uint32_t* hw = reinterpret_cast<uint32_t*>(hp + base);
-            // bytes 1 -> 0x01 and 0 -> 0xFF: each byte times 0xFE stays in its byte
-            for (uint32_t i = threadIdx.x; i < len / 4; i += TPB_)
-                hw[i] = WEIGHTS ? 0xFFFFFFFFu - mk[i] * 0xFEu : mk[i];
+            for (uint32_t i = threadIdx.x; i < len / 4; i += TPB_) hw[i] = mk[i];
         } else {
-            for (uint32_t i = threadIdx.x; i < len; i += TPB_)
-                hp[base + i] = WEIGHTS ? (mb[i] ? 0x01 : 0xFF) : mb[i];
+            for (uint32_t i = threadIdx.x; i < len; i += TPB_) hp[base + i] = mb[i];
         }
         __syncthreads();
+    }
+}
+
+// One workgroup per fine range, as k_mark3, but the range's marks become a
+// bitmap with running counts: word w of `dir` holds the bits of ids [32 w, 32 w
+// + 32) and the marked ids before them in their range; cnt[f] the range's.
+__global__ __launch_bounds__(place_tpb(false, false)) void k_mark_dir(const uint32_t* __restrict__ tx, uint32_t n,
+                                                                      uint32_t nb2, const uint32_t* __restrict__ fill2,
+                                                                      uint2* __restrict__ dir,
+                                                                      uint32_t* __restrict__ cnt) {
+    constexpr int TPB_ = place_tpb(false, false);
+    constexpr uint32_t R = 1u << PLACE_FINE_SHIFT;
+    static_assert(R / 32 <= TPB_, "one word a lane");
+    __shared__ uint4 mk4[R / 16];
+    __shared__ uint32_t sh[TPB_ / 64];
+    uint8_t* mb = reinterpret_cast<uint8_t*>(mk4);
+    for (uint32_t f = blockIdx.x; f < nb2; f += gridDim.x) {
+        const uint32_t base = f << PLACE_FINE_SHIFT;
+        const uint32_t len = min(R, n - base);
+        for (uint32_t i = threadIdx.x; i < R / 16; i += TPB_) mk4[i] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+        const uint32_t c = min(fill2[f], len);
+        for (uint32_t i0 = threadIdx.x; i0 < c; i0 += 4 * TPB_) {  // four loads in flight per lane
+            uint32_t kk[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t i = i0 + u * TPB_;
+                kk[u] = (i < c) ? tx[base + i] - base : NONE;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (kk[u] < len) mb[kk[u]] = 1;
+        }
+        __syncthreads();
+        uint32_t bits = 0;
+        if (threadIdx.x < R / 32) bits = mark_bits(mk4[2 * threadIdx.x], mk4[2 * threadIdx.x + 1]);
+        uint32_t total;
+        const uint32_t pre = block_exscan(__popc(bits), sh, &total);
+        if (threadIdx.x < (len + 31) / 32) dir[(base >> 5) + threadIdx.x] = make_uint2(bits, pre);
+        if (threadIdx.x == 0) cnt[f] = total;
+        __syncthreads();  // LDS is reused by the next range
     }
 }
 
@@ -3178,11 +3154,11 @@ static hipError_t run_marks(const RunArgs& a, const Plan& p, uint8_t* hp0, Ctrl*
     if (vec) {
         LR_TRY(allow_lds(k_mark1<true>, l1));
         hipLaunchKernelGGL(k_mark1<true>, dim3(grid_for(n, T)), tpb, l1, st, a.succ, n, p.s1, p.nb1, fill1, P, ctrl, mg,
-                           0u, NONE, dm);
+                           dm);
     } else {
         LR_TRY(allow_lds(k_mark1<false>, l1));
         hipLaunchKernelGGL(k_mark1<false>, dim3(grid_for(n, T)), tpb, l1, st, a.succ, n, p.s1, p.nb1, fill1, P, ctrl,
-                           mg, 0u, NONE, dm);
+                           mg, dm);
     }
     LR_TRY(hipGetLastError());
     const size_t l2 = place_lds_bytes(false, false, 1u << (p.s1 - p.s2), false);
@@ -3190,25 +3166,29 @@ static hipError_t run_marks(const RunArgs& a, const Plan& p, uint8_t* hp0, Ctrl*
     hipLaunchKernelGGL((k_place2<false, false, false>), dim3(grid_for(n, T)), tpb, l2, st, P, ctrl, n, p.s1, p.s2,
                        fill2, Q, dm, fill1, mg);
     LR_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_mark3<false>, dim3(std::min<uint32_t>(p.nb2, (uint32_t)device_cus() * 8)), tpb,
+    hipLaunchKernelGGL(k_mark3, dim3(std::min<uint32_t>(p.nb2, (uint32_t)device_cus() * 8)), tpb,
                        (size_t)1 << p.s2, st, Q.x, n, p.s2, p.nb2, fill2, hp0, mg, dm);
     return hipGetLastError();
 }
 
-// Euler-tour arc weights (+1 for the down arcs named in `down`, -1 for the
-// rest) without one random byte store per vertex: the down arcs' ids are
-// grouped by range with the predecessor-mark passes and every 8192-id range
-// writes its weights from LDS in order. Uses the grouping arrays of the
-// workspace of the prefix sum that follows (weighted, m elements), which are
-// free until that call; *done stays false when its plan has none (no visit
-// log at this size) and the caller scatters instead.
-hipError_t tree_arc_weights(const uint32_t* down, uint32_t V, uint32_t root, int8_t* w, uint32_t m, void* ws,
-                            const lr_opts* opts, hipStream_t st, bool* done) {
-    *done = false;
-    PlanSet ps;
-    if (make_plans(m, true, opts, 0, &ps) != LR_OK) return hipSuccess;
-    const Plan& p = ps.p;
-    if (!p.log0 || p.levels == 0) return hipSuccess;
+// Bitmap with running counts of the `count` positions below m in pos (each at
+// most once), without a random store per position: they are grouped by range
+// with the predecessor-mark passes. Uses the grouping arrays of the workspace
+// of a rank call over m elements, free once that call has run; where its plan
+// has none (no visit log at this size) position_dir_groups is false.
+static bool position_dir_plan(uint32_t m, const lr_opts* opts, Plan* p) {
+    return make_plan(m, false, opts, 0, p) == LR_OK && p->log0 && !p->local && !p->spawn;
+}
+
+bool position_dir_groups(uint32_t m, const lr_opts* opts) {
+    Plan p;
+    return position_dir_plan(m, opts, &p);
+}
+
+hipError_t position_dir(const uint32_t* pos, uint32_t count, uint32_t m, uint2* dir, uint32_t* cnt, void* ws,
+                        const lr_opts* opts, hipStream_t st) {
+    Plan p;
+    if (!position_dir_plan(m, opts, &p)) return hipErrorInvalidValue;
     char* base = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(ws) + ALIGN - 1) / ALIGN * ALIGN);
     Ctrl* ctrl = reinterpret_cast<Ctrl*>(base + p.off_ctrl);
     uint32_t* fill1 = reinterpret_cast<uint32_t*>(base + p.off_fill);
@@ -3220,19 +3200,17 @@ hipError_t tree_arc_weights(const uint32_t* down, uint32_t V, uint32_t root, int
     const dim3 tpb(place_tpb(false, false));
     const size_t l1 = place_lds_bytes(false, false, p.nb1, false);
     LR_TRY(allow_lds(k_mark1<false, true>, l1));
-    hipLaunchKernelGGL((k_mark1<false, true>), dim3(grid_for(V, T)), tpb, l1, st, down, m, p.s1, p.nb1, fill1, P, ctrl,
-                       Gate{}, V, root);
+    hipLaunchKernelGGL((k_mark1<false, true>), dim3(grid_for(count, T)), tpb, l1, st, pos, m, p.s1, p.nb1, fill1, P,
+                       ctrl, Gate{}, nullptr, count);
     LR_TRY(hipGetLastError());
     const size_t l2 = place_lds_bytes(false, false, 1u << (p.s1 - p.s2), false);
     LR_TRY(allow_lds(k_place2<false, false, false>, l2));
     hipLaunchKernelGGL((k_place2<false, false, false>), dim3(grid_for(m, T)), tpb, l2, st, P, ctrl, m, p.s1, p.s2,
                        fill2, Q, nullptr, fill1, Gate{});
     LR_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_mark3<true>, dim3(std::min<uint32_t>(p.nb2, (uint32_t)device_cus() * 8)), tpb,
-                       (size_t)1 << p.s2, st, Q.x, m, p.s2, p.nb2, fill2, reinterpret_cast<uint8_t*>(w), Gate{});
-    LR_TRY(hipGetLastError());
-    *done = true;
-    return hipSuccess;
+    hipLaunchKernelGGL(k_mark_dir, dim3(std::min<uint32_t>(p.nb2, (uint32_t)device_cus() * 8)), tpb, 0, st, Q.x, m,
+                       p.nb2, fill2, dir, cnt);
+    return hipGetLastError();
 }
 
 // Validation of the input (LR_VALIDATE): range and in-degree counts.

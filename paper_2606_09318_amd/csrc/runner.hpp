@@ -69,10 +69,11 @@ hipError_t run_wyllie(const RunArgs& a, uint64_t n, bool weighted);
 hipError_t run_batch_table(const lr_request* reqs, uint32_t count, const Plan& p, char* ws, bool dev_sizes,
                            uint32_t max_chunks, hipStream_t st);
 
-// Euler-tour arc weights by grouping (see kernels.hip); *done false: the
-// caller scatters the weights itself.
-hipError_t tree_arc_weights(const uint32_t* down, uint32_t V, uint32_t root, int8_t* w, uint32_t m, void* ws,
-                            const lr_opts* opts, hipStream_t st, bool* done);
+// Bitmap with running counts (per range of 2^PLACE_FINE_SHIFT ids) of a set of
+// positions by grouping (see kernels.hip), where position_dir_groups.
+bool position_dir_groups(uint32_t m, const lr_opts* opts);
+hipError_t position_dir(const uint32_t* pos, uint32_t count, uint32_t m, uint2* dir, uint32_t* cnt, void* ws,
+                        const lr_opts* opts, hipStream_t st);
 
 // Validation pass before ranking: range and in-degree check on the input.
 hipError_t run_validate_input(const uint32_t* succ, uint32_t n, uint32_t* counts, uint32_t* err,

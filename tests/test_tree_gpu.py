@@ -118,3 +118,38 @@ def test_validate():
     # without validation the same inputs return without faults
     for X in (bad, oob, cut):
         assert gpu_tree(X, 0, None)[0] == lr.LR_OK
+
+
+@pytest.mark.parametrize("V,what", [(V, w) for V in (4096, 4097, 4098, 65537, (1 << 20) + 1, (1 << 20) + 2)
+                                    for w in ("all", "depth", "size")] +
+                         [((1 << 24) + 1, "all"), ((1 << 24) + 2, "all")])
+def test_from_ranks_alone_at_the_edges(V, what):
+    """Tours ranked without weights (above 8192 arcs): around the rule's line,
+    the tiles of the positions' bitmap (32 and 8192 arcs, 256 tiles) and the
+    sizes whose positions are grouped; the weighted way (LR_VALIDATE) gives
+    the same. Trees of two shapes, one with V / 2 levels."""
+    print(f"case: tree from ranks V={V} {what}", flush=True)
+    parent = workloads.recursive_tree(V, seed=V % 101)
+    if V < (1 << 20) and what == "all":
+        deep = np.maximum(np.arange(V, dtype=np.int64) - 1, 0)
+        deep[V // 2:] = np.arange(V - V // 2) % (V // 2)
+        parents = [parent, workloads.relabel_tree(deep.astype(np.uint32), 7)]
+    else:
+        parents = [parent]
+    for par in parents:
+        E = workloads.tour_of(par, seed=9)
+        succ, down, up = dev(E.succ), dev(E.down_arc), dev(E.up_arc)
+        outs = []
+        for flags in (0, lr.LR_VALIDATE):
+            o = lr.make_opts(flags=flags)
+            d, p, z = (torch.full((V,), -7, dtype=torch.int32, device="cuda") for _ in range(3))
+            ws = lr.workspace(lr.lr_euler_tree_workspace_bytes(V, o))
+            st = lr.lr_euler_tree(succ, down, up, V, 0, d if what != "size" else None, p if what == "all" else None,
+                                  z if what != "depth" else None, ws, o)
+            torch.cuda.synchronize()
+            assert st == lr.LR_OK, lr.status_string(st)
+            outs.append((d, p, z))
+        for a, b in zip(*outs):
+            assert torch.equal(a, b)
+        if E.depth is not None and what != "size":
+            assert np.array_equal(host_u32(outs[0][0]), E.depth)
