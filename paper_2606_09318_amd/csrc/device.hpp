@@ -19,6 +19,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace lr {
 
 constexpr uint32_t TERM = 0x80000000u;      // record flag: element is a terminal
@@ -205,6 +207,8 @@ struct Sampler {
 // id when x is a terminal) and its value: the link weight for a non-terminal,
 // the terminal's own weight for a terminal (0 on the input level).
 // Out-of-range successors are read as terminals, so no walk leaves the array.
+// fetch only reads, decode tells what was read: work between the two does not
+// wait for the read.
 template <bool W, int WT>  // WT: 0 = every link weighs 1, 1 = int32, 2 = int64, 3 = int8 weights (internal)
 struct SrcIn {
     const uint32_t* succ;
@@ -212,15 +216,23 @@ struct SrcIn {
     uint32_t m;
     using L = Lay<W>;
     static constexpr bool kLinks = true;  // every record is one link: a walk's count is its step count
+    struct Raw { uint32_t s; std::conditional_t<WT == 2, int64_t, int32_t> w; };
+    __device__ __forceinline__ Raw fetch(uint32_t x) const {
+        Raw r;
+        r.s = succ[x];
+        r.w = 1;
+        if constexpr (WT == 1) r.w = static_cast<const int32_t*>(weight)[x];
+        if constexpr (WT == 3) r.w = static_cast<const int8_t*>(weight)[x];
+        if constexpr (WT == 2) r.w = static_cast<const int64_t*>(weight)[x];
+        return r;
+    }
+    __device__ __forceinline__ void decode(uint32_t x, const Raw& r, uint32_t& nxt, typename L::Val& v) const {
+        const bool t = (r.s == x) | (r.s >= m);
+        nxt = t ? (TERM | x) : r.s;
+        v = t ? L::zero() : L::one_link((int64_t)r.w);
+    }
     __device__ __forceinline__ void load(uint32_t x, uint32_t& nxt, typename L::Val& v) const {
-        const uint32_t s = succ[x];
-        int64_t w = 1;
-        if constexpr (WT == 1) w = static_cast<const int32_t*>(weight)[x];
-        if constexpr (WT == 3) w = static_cast<const int8_t*>(weight)[x];
-        if constexpr (WT == 2) w = static_cast<const int64_t*>(weight)[x];
-        const bool t = (s == x) | (s >= m);
-        nxt = t ? (TERM | x) : s;
-        v = t ? L::zero() : L::one_link(w);
+        decode(x, fetch(x), nxt, v);
     }
 };
 
@@ -237,11 +249,15 @@ struct SrcPair {
     uint32_t m;
     using L = Lay<true>;
     static constexpr bool kLinks = true;
-    __device__ __forceinline__ void load(uint32_t x, uint32_t& nxt, typename L::Val& v) const {
-        const PairRec<WT> p = r[x];
+    using Raw = PairRec<WT>;
+    __device__ __forceinline__ Raw fetch(uint32_t x) const { return r[x]; }
+    __device__ __forceinline__ void decode(uint32_t x, const Raw& p, uint32_t& nxt, typename L::Val& v) const {
         const bool t = (p.s == x) | (p.s >= m);
         nxt = t ? (TERM | x) : p.s;
         v = t ? L::zero() : L::one_link((int64_t)p.w);
+    }
+    __device__ __forceinline__ void load(uint32_t x, uint32_t& nxt, typename L::Val& v) const {
+        decode(x, fetch(x), nxt, v);
     }
 };
 
@@ -251,11 +267,15 @@ struct SrcLvl {
     uint32_t m;
     using L = Lay<W>;
     static constexpr bool kLinks = false;  // records are segments: counts exceed step counts
-    __device__ __forceinline__ void load(uint32_t x, uint32_t& nxt, typename L::Val& v) const {
-        const typename L::Rec r = e[x];
+    using Raw = typename L::Rec;
+    __device__ __forceinline__ Raw fetch(uint32_t x) const { return e[x]; }
+    __device__ __forceinline__ void decode(uint32_t, const Raw& r, uint32_t& nxt, typename L::Val& v) const {
         nxt = r.nxt;
         v = L::val(r);
         if (!(nxt & TERM) && nxt >= m) { nxt = TERM | IDX; v = L::zero(); }
+    }
+    __device__ __forceinline__ void load(uint32_t x, uint32_t& nxt, typename L::Val& v) const {
+        decode(x, fetch(x), nxt, v);
     }
 };
 

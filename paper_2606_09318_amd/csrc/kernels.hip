@@ -484,6 +484,14 @@ __device__ __forceinline__ void pad_chunk(const LogArrays<W>& lg, uint32_t cbase
     }
 }
 
+// The record of x is fetched as soon as x is known, at the end of the step
+// before, and decoded only after the step's bookkeeping (refill, log position,
+// stores), so that work runs while the read is in flight; the last walks, with
+// few reads in flight, are bound by that chain (2^28 elements 10.49 -> 10.33 ms a
+// call, 2^24 862 -> 820 us, 3 M 245 -> 235, weighted 600,003 137 -> 127).
+// Fetching before the ruler test as well gains nothing from 2^24 on and loses
+// 3 % at 5 M (one read in k is wasted).
+//
 // Persistent kernel: each lane holds one walk; a wavefront refills its idle
 // lanes from its own range of walk ids (ballot + mbcnt hand out consecutive
 // ids) once `refill` lanes are idle. Each step is
@@ -553,6 +561,7 @@ __global__ __launch_bounds__(CHASE_TPB) __attribute__((amdgpu_num_sgpr(80))) voi
     const LogFmt fmt(m, total, lg.ccap, lg.bocap);
     uint32_t rw[NW], rb[NW];
     uint32_t kbase = 0, kfill = CONT_GRAB;
+    typename Src::Raw raw[NW];  // the record of x, in flight while the step's bookkeeping runs
     for (;;) {
         uint64_t idle[NW];
         uint32_t nidle = 0;
@@ -596,17 +605,14 @@ __global__ __launch_bounds__(CHASE_TPB) __attribute__((amdgpu_num_sgpr(80))) voi
                             eb[w[k]] = L::rec(TERM | IDX, L::zero());
                             atomicOr(&ctrl->err, 8u);
                             w[k] = NONE;
+                        } else {
+                            raw[k] = src.fetch(x[k]);
                         }
                     }
                 }
                 acc += __popcll(idle[k]);
             }
         }
-        uint32_t nxt[NW];
-        Val v[NW];
-#pragma unroll
-        for (int k = 0; k < NW; ++k)
-            if (w[k] != NONE) src.load(x[k], nxt[k], v[k]);
         uint32_t pos[NW];
         if constexpr (LOG != 0) {
             uint64_t act[NW];
@@ -696,11 +702,18 @@ __global__ __launch_bounds__(CHASE_TPB) __attribute__((amdgpu_num_sgpr(80))) voi
                 slot[x[k]] = L::slot(w[k], off[k]);
                 LR_DBG_COUNT(slot, lvl, x[k]);
             }
-            if (nxt[k] & TERM) {                    // x is a terminal: the walk ends on it
-                eb[w[k]] = L::rec(nxt[k], L::add(off[k], v[k]));
+        }
+#pragma unroll
+        for (int k = 0; k < NW; ++k) {
+            if (w[k] == NONE) continue;
+            uint32_t nxt;
+            Val v;
+            src.decode(x[k], raw[k], nxt, v);
+            if (nxt & TERM) {                       // x is a terminal: the walk ends on it
+                eb[w[k]] = L::rec(nxt, L::add(off[k], v));
                 w[k] = NONE;
             } else {
-                off[k] = L::add(off[k], v[k]);
+                off[k] = L::add(off[k], v);
                 // steps so far: on the input level every record is one link,
                 // so the walk's count is its step count and no counter is kept
                 uint32_t walked;
@@ -710,8 +723,8 @@ __global__ __launch_bounds__(CHASE_TPB) __attribute__((amdgpu_num_sgpr(80))) voi
                     eb[w[k]] = L::rec(TERM | IDX, off[k]);
                     ctrl->mode = MODE_FALLBACK;
                     w[k] = NONE;
-                } else if (smp.sampled(nxt[k])) {   // reached the next ruler
-                    const uint32_t c = nxt[k] >> smp.log2k;
+                } else if (smp.sampled(nxt)) {      // reached the next ruler
+                    const uint32_t c = nxt >> smp.log2k;
                     eb[w[k]] = L::rec(c, off[k]);
                     if (hp_next && w[k] < S) {
                         hp_next[c] = 1;
@@ -719,7 +732,8 @@ __global__ __launch_bounds__(CHASE_TPB) __attribute__((amdgpu_num_sgpr(80))) voi
                     }
                     w[k] = NONE;
                 } else {
-                    x[k] = nxt[k];
+                    x[k] = nxt;
+                    raw[k] = src.fetch(nxt);
                 }
             }
         }
