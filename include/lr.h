@@ -106,9 +106,9 @@ enum {
  * lr_profile_last reports whether it ran. Under LR_VALIDATE a cycle reached
  * by a walk is reported through the same fallback.
  * Independent walks: with the planner's own levels (spacing[0] and base_max 0,
- * or naming just those), inputs of more than 4096 (weighted 8192) and fewer
+ * or naming just those), inputs of more than 8192 and fewer
  * than 2^21 (weighted 2^19) elements, and larger inputs' first level of at
- * most 2^20 (2^19) elements, are not chased: every element walks by itself, a
+ * most 2^21 elements (at spacing 16 and above 1.25 * 2^20), are not chased: every element walks by itself, a
  * dozen steps at most, to the next sampled ruler, the last level's rulers are
  * ranked by pointer doubling over the whole chip, and every element composes
  * its walk with its ruler's result. An element of an input that needs more than
@@ -153,7 +153,7 @@ typedef struct lr_opts {
                                           base case; 0 = default (8192 unweighted,
                                           4096 weighted). With the planner's own
                                           levels the base case is left to inputs of
-                                          up to 4096 (weighted 8192) elements */
+                                          up to 8192 elements */
     uint32_t spacing[LR_MAX_LEVELS];   /* ruler spacing k per recursion level: one
                                           ruler per k consecutive ids; powers of
                                           two in [2, 4096]; the list ends at the

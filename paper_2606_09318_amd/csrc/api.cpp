@@ -160,7 +160,7 @@ static void plan_iw(const lr_opts* o, bool user_spacing, bool capped, bool input
         }
     }
     if (r || !input)
-        while (r < p->levels && p->m[r] > iw_max(p->weighted)) ++r;
+        while (r < p->levels && p->m[r] > iw_max(p->log2k[r])) ++r;
     uint32_t t = r;
     while (t < p->levels && p->m[t] > iw_top(p->weighted)) ++t;
     p->run = r;

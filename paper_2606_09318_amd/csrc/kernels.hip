@@ -743,146 +743,206 @@ __global__ __launch_bounds__(CHASE_TPB) __attribute__((amdgpu_num_sgpr(80))) voi
     }
 }
 
+// A record (nxt, count) as one word.
+__device__ __forceinline__ uint64_t iw_word(uint32_t f, uint32_t v) { return ((uint64_t)v << 32) | f; }
+
 // ------------------------------------------------------------------ base --
 // Pointer doubling (Wyllie) on <= 16384 elements in LDS by one workgroup.
-// d[i] is the weight from i up to (not including) f[i]; terminals point to
-// themselves with d = 0, so a round d[i] += d[f[i]], f[i] = f[f[i]] leaves
-// them fixed, and after ceil(log2 len) rounds f[i] is i's terminal. The
-// result adds the terminal's own value (its weight at this level).
 //
-// Unweighted levels: lane t holds slots t + j * BASE_TPB for j < COLS (4, 8
-// or 16 columns, the fewest that cover the planned size) as (d << 32) | f
-// words in registers, and publishes them to LDS after every round. Slots
-// past m hold self-loops (0, i), which never change, so a round has no
-// per-lane branch: the lane's COLS gathers are in flight together. The
-// round is bound by the LDS gathers (random 8 B words); the branch-free
-// form took 18-28 % off calls of 2^10-2^13 elements (the base case alone).
-template <int COLS, class Src>
-__device__ __forceinline__ void base_pd_unweighted(Src& src, uint32_t m, unsigned char* lds, uint32_t* f_,
-                                                   uint32_t* dc_) {
+// Unweighted levels: a record (nxt, count) per element, 8 B in LDS, as in the
+// independent walks: nxt = TERM | t once the list's end is reached, its count
+// then including the terminal's own value. Lane t holds the records of slots
+// t + j * BASE_TPB for j < COLS (1, 2, 4, 8 or 16 columns, the fewest that
+// cover the planned size) in registers and composes them, in place and without
+// barriers, until all have ended: a record stays true whatever the others do, so
+// a neighbour's older record only jumps less far, and no wavefront waits for
+// another. On a cycle the count reaches climit. Slots past m hold ended records
+// and ended slots read themselves, so a round has no per-lane branch and the
+// lane's COLS gathers are in flight together.
+// Bound by the launch, a global read and the LDS rounds. A call against
+// synchronised rounds (two barriers each): 1000 elements 11.2 -> 8.7 us, which is
+// the rate the host enqueues at, 4096 13.7 -> 8.5; 8192 take 12.5 (independent
+// walks 16.6), 16384 24.7 (18), which is why the planner's line lies between.
+template <int COLS, class Src, class Out>
+__global__ __launch_bounds__(BASE_TPB) void k_base_unweighted(Src src, Out out, uint32_t m, uint32_t climit, Ctrl* ctrl,
+                                                              const uint32_t* dm, Gate gate) {
+    if (gate.off()) return;
     using Val = typename Lay<false>::Val;
+    extern __shared__ __align__(16) unsigned char lds[];
+    if (dm) m = src.m = min(dm[0], m);  // a device-side size is at most the planned one
     uint64_t* fd = reinterpret_cast<uint64_t*>(lds);
     const uint32_t t = threadIdx.x;
-    uint64_t e_[COLS];
+    auto get = [&](uint32_t i) { return __hip_atomic_load(fd + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
+    auto put = [&](uint32_t i, uint64_t v) {
+        __hip_atomic_store(fd + i, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    uint64_t e[COLS];
 #pragma unroll
     for (int j = 0; j < COLS; ++j) {
         const uint32_t i = t + j * BASE_TPB;
-        e_[j] = (uint64_t)i;
+        e[j] = TERM | IDX;
         if (i < m) {
             uint32_t nxt;
             Val v;
             src.load(i, nxt, v);
-            if (!((nxt & TERM) || nxt >= m)) e_[j] = ((uint64_t)v.c << 32) | nxt;
+            e[j] = iw_word(nxt, v.c);
         }
-        fd[i] = e_[j];
     }
-    __syncthreads();
-    for (int round = 0; round < 40; ++round) {
-        uint32_t changed = 0;
-        uint64_t w_[COLS];
 #pragma unroll
-        for (int j = 0; j < COLS; ++j) w_[j] = fd[(uint32_t)e_[j]];
+    for (int j = 0; j < COLS; ++j) put(t + j * BASE_TPB, e[j]);
+    __syncthreads();
+    for (;;) {
+        uint32_t open = 0;
+#pragma unroll
+        for (int j = 0; j < COLS; ++j) open |= ~(uint32_t)e[j] & TERM;
+        if (!open) break;
+        uint64_t w[COLS];
+#pragma unroll
+        for (int j = 0; j < COLS; ++j) w[j] = get(((uint32_t)e[j] & TERM) ? t + j * BASE_TPB : (uint32_t)e[j]);
 #pragma unroll
         for (int j = 0; j < COLS; ++j) {
-            changed |= (uint32_t)w_[j] ^ (uint32_t)e_[j];
-            e_[j] = ((uint64_t)((uint32_t)(e_[j] >> 32) + (uint32_t)(w_[j] >> 32)) << 32) | (uint32_t)w_[j];
+            const uint32_t c = (uint32_t)(e[j] >> 32) + (uint32_t)(w[j] >> 32);
+            // more links than the input has: a cycle
+            const uint64_t n = c >= climit ? ~0ull : iw_word((uint32_t)w[j], c);
+            e[j] = ((uint32_t)e[j] & TERM) ? e[j] : n;
+            put(t + j * BASE_TPB, e[j]);
         }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < COLS; ++j) fd[t + j * BASE_TPB] = e_[j];
-        if (!__syncthreads_or(changed != 0)) break;
     }
 #pragma unroll
     for (int j = 0; j < COLS; ++j) {
-        f_[j] = (uint32_t)e_[j];
-        dc_[j] = (uint32_t)(e_[j] >> 32);
+        const uint32_t i = t + j * BASE_TPB;
+        if (i < m) {
+            if (e[j] == ~0ull) atomicOr(&ctrl->err, 16u);
+            auto cur = out.begin(i);
+            out.store(cur, i, Val{(uint32_t)(e[j] >> 32)}, (uint32_t)e[j] & IDX);
+        }
     }
 }
 
-// Weighted levels of at most 8192 elements, the same way: a (d << 32) | f
-// word and the 8 B sum per slot, two gathers per element and round.
-template <int COLS, class Src>
-__device__ __forceinline__ void base_pd_weighted(Src& src, uint32_t m, unsigned char* lds, uint32_t* f_,
-                                                 uint32_t* dc_, int64_t* ds_) {
-    using Val = typename Lay<true>::Val;
-    uint64_t* fd = reinterpret_cast<uint64_t*>(lds);
-    int64_t* sd = reinterpret_cast<int64_t*>(lds + 8 * (size_t)(COLS * BASE_TPB));
+// Weighted levels of at most 8192 elements, the same way with two words per
+// element (16 B): the count, the 64-bit sum and, in both words, the slot they
+// lead to. A record is taken only if both words name the same slot (which
+// determines the values), so halves of two records are never combined.
+//   word 0: slot and ended bit (14 bits) | count (31) | sum bits 0-18
+//   word 1: slot and ended bit (14 bits) | sum bits 19-63
+// An ended record names its terminal's slot, whose own value and id are read
+// from the source again at the end.
+// Bound as above (against synchronised rounds: 600 elements 14.5 -> 8.9 us a
+// call, 3000 20.5 -> 12.2, 8192 33.8 -> 28.2).
+constexpr uint32_t BW_END = 1u << 13;
+template <int COLS, class Src, class Out>
+__global__ __launch_bounds__(BASE_TPB) void k_base_weighted(Src src, Out out, uint32_t m, uint32_t climit, Ctrl* ctrl,
+                                                            const uint32_t* dm, Gate gate) {
+    if (gate.off()) return;
+    using L = Lay<true>;
+    using Val = typename L::Val;
+    static_assert(COLS * BASE_TPB <= BW_END, "13-bit slots");
+    extern __shared__ __align__(16) unsigned char lds[];
+    if (dm) m = src.m = min(dm[0], m);  // a device-side size is at most the planned one
+    uint64_t* w0 = reinterpret_cast<uint64_t*>(lds);
+    uint64_t* w1 = w0 + COLS * BASE_TPB;
     const uint32_t t = threadIdx.x;
-    uint64_t e_[COLS];
-    int64_t s_[COLS];
+    auto get = [&](const uint64_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
+    auto put = [&](uint32_t i, uint32_t f, uint32_t c, uint64_t s) {
+        __hip_atomic_store(w0 + i, (uint64_t)f | ((uint64_t)c << 14) | (s << 45), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_store(w1 + i, (uint64_t)f | ((s >> 19) << 14), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    uint32_t f[COLS], c[COLS];
+    uint64_t s[COLS];
+    uint32_t cyc = 0;  // columns that never reached a terminal
 #pragma unroll
     for (int j = 0; j < COLS; ++j) {
         const uint32_t i = t + j * BASE_TPB;
-        e_[j] = (uint64_t)i;
-        s_[j] = 0;
+        f[j] = BW_END | i;
+        c[j] = 0;
+        s[j] = 0;
         if (i < m) {
             uint32_t nxt;
             Val v;
             src.load(i, nxt, v);
-            if (!((nxt & TERM) || nxt >= m)) {
-                e_[j] = ((uint64_t)v.c << 32) | nxt;
-                s_[j] = v.s;
+            if (!(nxt & TERM) && nxt < m) {
+                f[j] = nxt;
+                c[j] = v.c;
+                s[j] = (uint64_t)v.s;
             }
         }
-        fd[i] = e_[j];
-        sd[i] = s_[j];
     }
+#pragma unroll
+    for (int j = 0; j < COLS; ++j) put(t + j * BASE_TPB, f[j], c[j], s[j]);
     __syncthreads();
-    for (int round = 0; round < 40; ++round) {
-        uint32_t changed = 0;
-        uint64_t w_[COLS];
-        int64_t v_[COLS];
+    for (;;) {
+        uint32_t open = 0;
+#pragma unroll
+        for (int j = 0; j < COLS; ++j) open |= ~f[j] & BW_END;
+        if (!open) break;
+        uint64_t a[COLS], b[COLS];
 #pragma unroll
         for (int j = 0; j < COLS; ++j) {
-            w_[j] = fd[(uint32_t)e_[j]];
-            v_[j] = sd[(uint32_t)e_[j]];
+            const uint32_t q = f[j] & (BW_END - 1);
+            a[j] = get(w0 + q);
+            b[j] = get(w1 + q);
         }
 #pragma unroll
         for (int j = 0; j < COLS; ++j) {
-            changed |= (uint32_t)w_[j] ^ (uint32_t)e_[j];
-            e_[j] = ((uint64_t)((uint32_t)(e_[j] >> 32) + (uint32_t)(w_[j] >> 32)) << 32) | (uint32_t)w_[j];
-            s_[j] += v_[j];
+            const uint32_t i = t + j * BASE_TPB;
+            const uint32_t fa = (uint32_t)a[j] & (2 * BW_END - 1);
+            if ((f[j] & BW_END) || fa != ((uint32_t)b[j] & (2 * BW_END - 1))) continue;  // ended, or caught half stored
+            c[j] += (uint32_t)(a[j] >> 14) & IDX;
+            s[j] += (a[j] >> 45) | ((b[j] >> 14) << 19);
+            f[j] = fa;
+            if (c[j] >= climit) {  // more links than the input has: a cycle
+                cyc |= 1u << j;
+                f[j] = BW_END | i;
+                c[j] = 0;
+            }
+            put(i, f[j], c[j], s[j]);
         }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < COLS; ++j) {
-            fd[t + j * BASE_TPB] = e_[j];
-            sd[t + j * BASE_TPB] = s_[j];
-        }
-        if (!__syncthreads_or(changed != 0)) break;
     }
+    Val rv[COLS];
+    uint32_t rr[COLS];
 #pragma unroll
     for (int j = 0; j < COLS; ++j) {
-        f_[j] = (uint32_t)e_[j];
-        dc_[j] = (uint32_t)(e_[j] >> 32);
-        ds_[j] = s_[j];
+        if (t + j * BASE_TPB >= m) continue;
+        uint32_t nxt;
+        Val v;
+        src.load(f[j] & (BW_END - 1), nxt, v);
+        rv[j] = L::add(Val{c[j], (int64_t)s[j]}, v);
+        rr[j] = nxt & IDX;
+        if (!(nxt & TERM) || ((cyc >> j) & 1u)) {
+            rv[j] = L::junk();
+            rr[j] = NONE;
+            atomicOr(&ctrl->err, 16u);
+        }
+    }
+    __syncthreads();  // every read of the level's records happens before any in-place write
+#pragma unroll
+    for (int j = 0; j < COLS; ++j) {
+        const uint32_t i = t + j * BASE_TPB;
+        if (i < m) {
+            auto cur = out.begin(i);
+            out.store(cur, i, rv[j], rr[j]);
+        }
     }
 }
 
-template <bool W, class Src, class Out>
-__global__ __launch_bounds__(BASE_TPB) void k_base(Src src, Out out, uint32_t m, Ctrl* ctrl, const uint32_t* dm, Gate gate) {
+// Larger weighted levels (a user base size above 8192), in rounds: d[i] is the
+// weight from i up to (not including) f[i]; terminals point to themselves with
+// d = 0, so a round d[i] += d[f[i]], f[i] = f[f[i]] leaves them fixed, and after
+// ceil(log2 len) rounds f[i] is i's terminal. 8 B sum, 4 B count and 2 B
+// successor arrays.
+template <class Src, class Out>
+__global__ __launch_bounds__(BASE_TPB) void k_base_weighted_large(Src src, Out out, uint32_t m, Ctrl* ctrl,
+                                                                  const uint32_t* dm, Gate gate) {
     if (gate.off()) return;
-    using L = Lay<W>;
+    using L = Lay<true>;
     using Val = typename L::Val;
     extern __shared__ __align__(16) unsigned char lds[];
-    const uint32_t mcap = m;            // LDS is carved for the planned size
-    if (dm) m = src.m = min(dm[0], m);  // a device-side size is at most that
+    if (dm) m = src.m = min(dm[0], m);  // a device-side size is at most the planned one
     const uint32_t t = threadIdx.x;
-    // each lane keeps its own elements' (f, d) in registers and writes them
-    // to LDS after every round, where the other lanes gather them
     uint32_t f_[BASE_PER], dc_[BASE_PER];
     int64_t ds_[BASE_PER];
-    if constexpr (!W) {
-        if (mcap <= 4 * BASE_TPB) base_pd_unweighted<4>(src, m, lds, f_, dc_);
-        else if (mcap <= 8 * BASE_TPB) base_pd_unweighted<8>(src, m, lds, f_, dc_);
-        else base_pd_unweighted<16>(src, m, lds, f_, dc_);
-    } else if (mcap <= 4 * BASE_TPB) {
-        base_pd_weighted<4>(src, m, lds, f_, dc_, ds_);
-    } else if (mcap <= 8 * BASE_TPB) {
-        base_pd_weighted<8>(src, m, lds, f_, dc_, ds_);
-    } else {
-        // larger weighted levels (a user base size above 8192): 8 B sum,
-        // 4 B count and 2 B successor arrays
+    {
         int64_t* ds = reinterpret_cast<int64_t*>(lds);
         uint32_t* dc = reinterpret_cast<uint32_t*>(lds + 8 * (size_t)m);
         uint16_t* f = reinterpret_cast<uint16_t*>(lds + 12 * (size_t)m);
@@ -946,7 +1006,7 @@ __global__ __launch_bounds__(BASE_TPB) void k_base(Src src, Out out, uint32_t m,
             src.load(ti, nxt, v);
             Val d;
             d.c = dc_[j];
-            if constexpr (W) d.s = ds_[j];
+            d.s = ds_[j];
             if (nxt & TERM) {
                 rv[j] = L::add(d, v);
                 rr[j] = nxt & IDX;
@@ -1014,7 +1074,6 @@ constexpr uint32_t IW_TOP_CAP = 128;
 #endif
 constexpr uint32_t IW_CAP_ALONE = 8;  // steps of a list that the doubling takes alone
 
-__device__ __forceinline__ uint64_t iw_word(uint32_t f, uint32_t v) { return ((uint64_t)v << 32) | f; }
 template <bool DEV>
 __device__ __forceinline__ uint64_t iw_get(const uint64_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, DEV ? __HIP_MEMORY_SCOPE_AGENT : __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -2949,17 +3008,43 @@ static inline void rec_ev(const RunArgs& a, int i) {
     if (a.ev) (void)hipEventRecord(a.ev[i], a.stream);
 }
 
-template <bool W, class Src, class Out>
-static hipError_t launch_base(Src src, Out out, uint32_t m, Ctrl* ctrl, hipStream_t st,
-                             const uint32_t* dm = nullptr, Gate gate = Gate{}) {
-    const size_t lds = base_lds_bytes(m, W);
-    auto kern = k_base<W, Src, Out>;
+template <int COLS, bool W, class Src, class Out>
+static hipError_t launch_base_cols(Src src, Out out, uint32_t m, uint32_t climit, Ctrl* ctrl, hipStream_t st,
+                                   const uint32_t* dm, Gate gate) {
+    constexpr size_t lds = (size_t)COLS * BASE_TPB * (W ? 16 : 8);
+    void (*kern)(Src, Out, uint32_t, uint32_t, Ctrl*, const uint32_t*, Gate);
+    if constexpr (W) kern = k_base_weighted<COLS, Src, Out>;
+    else kern = k_base_unweighted<COLS, Src, Out>;
     if (lds > 65536) {
         hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(kern, dim3(1), dim3(BASE_TPB), lds, st, src, out, m, ctrl, dm, gate);
+    hipLaunchKernelGGL(kern, dim3(1), dim3(BASE_TPB), lds, st, src, out, m, climit, ctrl, dm, gate);
     return hipGetLastError();
+}
+
+// climit: elements of the input (no list has as many links).
+template <bool W, class Src, class Out>
+static hipError_t launch_base(Src src, Out out, uint32_t m, uint32_t climit, Ctrl* ctrl, hipStream_t st,
+                              const uint32_t* dm, Gate gate) {
+    if constexpr (!W) {
+        if (m <= BASE_TPB) return launch_base_cols<1, false>(src, out, m, climit, ctrl, st, dm, gate);
+        if (m <= 2 * BASE_TPB) return launch_base_cols<2, false>(src, out, m, climit, ctrl, st, dm, gate);
+        if (m <= 4 * BASE_TPB) return launch_base_cols<4, false>(src, out, m, climit, ctrl, st, dm, gate);
+        if (m <= 8 * BASE_TPB) return launch_base_cols<8, false>(src, out, m, climit, ctrl, st, dm, gate);
+        return launch_base_cols<16, false>(src, out, m, climit, ctrl, st, dm, gate);
+    } else {
+        if (m <= BASE_TPB) return launch_base_cols<1, true>(src, out, m, climit, ctrl, st, dm, gate);
+        if (m <= 2 * BASE_TPB) return launch_base_cols<2, true>(src, out, m, climit, ctrl, st, dm, gate);
+        if (m <= 4 * BASE_TPB) return launch_base_cols<4, true>(src, out, m, climit, ctrl, st, dm, gate);
+        if (m <= 8 * BASE_TPB) return launch_base_cols<8, true>(src, out, m, climit, ctrl, st, dm, gate);
+        const size_t lds = base_lds_bytes(m, true);
+        auto kern = k_base_weighted_large<Src, Out>;
+        hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kern, dim3(1), dim3(BASE_TPB), lds, st, src, out, m, ctrl, dm, gate);
+        return hipGetLastError();
+    }
 }
 
 // The lists of level p.run and above, by independent walks: levels run ..
@@ -3308,7 +3393,7 @@ static hipError_t run_srs_t(const RunArgs& a, Out0 out0) {
     }
     if (p.run == 0) {
         if (p.iw) LR_TRY((run_iw<W>(p, src0, out0, n, true, ctrl, ws, st, dm_at(0), g)));
-        else LR_TRY((launch_base<W>(src0, out0, n, ctrl, st, dm_at(0), g)));
+        else LR_TRY((launch_base<W>(src0, out0, n, n, ctrl, st, dm_at(0), g)));
         for (int i = EV_DETECT; i < EV_COUNT; ++i) rec_ev(a, i);
         return hipSuccess;
     }
@@ -3389,7 +3474,7 @@ static hipError_t run_srs_t(const RunArgs& a, Out0 out0) {
             LR_TRY((run_iw_level<W>(p, top, n, ctrl, ws, st, dm_at(L_), g)));
         } else {
             SrcLvl<W> src{top, mL};
-            LR_TRY((launch_base<W>(src, OutLvl<W>{top}, mL, ctrl, st, dm_at(L_), g)));
+            LR_TRY((launch_base<W>(src, OutLvl<W>{top}, mL, n, ctrl, st, dm_at(L_), g)));
         }
     }
     for (int l = (int)p.run - 1; l >= 0; --l) {
@@ -3466,12 +3551,12 @@ static hipError_t run_clevels(const RunArgs& a, const Plan& p, typename Lay<W>::
     }
     {
         auto* top = Lv ? reinterpret_cast<typename L::Rec*>(ws + p.off_eb[Lv - 1]) : lrec;
+        const uint32_t climit = (uint32_t)(p.spawn ? p.sp_n : p.lc_n);
         if (p.iw) {
-            const uint32_t climit = (uint32_t)(p.spawn ? p.sp_n : p.lc_n);
             LR_TRY((run_iw_level<W>(p, top, climit, ctrl, ws, st, &ctrl->dm[Lv], g)));
         } else {
             SrcLvl<W> src{top, (uint32_t)p.m[Lv]};
-            LR_TRY((launch_base<W>(src, OutLvl<W>{top}, (uint32_t)p.m[Lv], ctrl, st, &ctrl->dm[Lv], g)));
+            LR_TRY((launch_base<W>(src, OutLvl<W>{top}, (uint32_t)p.m[Lv], climit, ctrl, st, &ctrl->dm[Lv], g)));
         }
     }
     for (int l = (int)Lv - 1; l >= 0; --l) {

@@ -148,24 +148,25 @@ inline size_t batch_table_bytes(uint32_t count) { return 2 * ((size_t)count + 1)
 // levels only until one holds at most iw_max elements; that one and the
 // levels above it are ranked by independent walks, from the first level of at
 // most iw_top elements on by asynchronous doubling. Inputs of more than
-// IW_DIRECT_MIN (weighted: of more than the base case takes) and fewer than
-// iw_direct elements are not chased at all.
+// IW_DIRECT_MIN (what the base case takes) and fewer than iw_direct elements
+// are not chased at all.
 // Measured (random lists, rank and root; weighted: int64, every output; us a
 // call, same box), the other side of each line first:
 //   chase and base case -> independent walks: 2^15 83 -> 27, 2^18 117 -> 41,
 //     2^20 185 -> 89, 1.5 * 2^20 150 (one chased level) -> 130; weighted 2^17
 //     113 -> 59, 2^18 136 -> 79, 1.4 * 2^18 133 (one chased level) -> 101, but
 //     1.4 * 2^19 152 -> 168: a weighted step reads two arrays
-//   iw_max 2^18 -> 2^20: 1.5 * 2^22 459 -> 414, 1.5 * 2^24 1398 -> 1350
+//   iw_max 2^18 -> 2^20: 1.5 * 2^22 459 -> 414, 1.5 * 2^24 1398 -> 1350; -> 2^21:
+//     block lists of 2^22 (a contracted list of capacity 1.3 M) 155 -> 121, 5 M
+//     forest 386 -> 378, weighted 1.2 * 10^7 forest 1198 -> 1153. At spacing 16
+//     (inputs from 2^25 on) a walk takes twice the steps: 1.1 M elements 1976 ->
+//     1903 (64 lists, 36 M in all), 1.56 M 2160 -> 2182, 2.1 M 2698 -> 2768
 //   iw_top 2^14 -> 2^16: 1.5 * 2^17 46 -> 39, forest 2^16 20 -> 16; above, the
 //     doubling's device-scope reads saturate (2^16 33 alone, 27 below one level
 //     of walks); weighted (three words a record) 1.4 * 2^14 41 at 2^14, 44 at 2^15
 // iw_direct stays below the automatic contraction's first size.
 #ifndef LR_IW_MAX_LOG2
-#define LR_IW_MAX_LOG2 20
-#endif
-#ifndef LR_IW_MAX_LOG2_W
-#define LR_IW_MAX_LOG2_W 19
+#define LR_IW_MAX_LOG2 21
 #endif
 #ifndef LR_IW_DIRECT_LOG2
 #define LR_IW_DIRECT_LOG2 21
@@ -174,7 +175,7 @@ inline size_t batch_table_bytes(uint32_t count) { return 2 * ((size_t)count + 1)
 #define LR_IW_DIRECT_LOG2_W 19
 #endif
 #ifndef LR_IW_DIRECT_MIN
-#define LR_IW_DIRECT_MIN 4096
+#define LR_IW_DIRECT_MIN 8192
 #endif
 #ifndef LR_IW_TOP_LOG2
 #define LR_IW_TOP_LOG2 16
@@ -182,11 +183,11 @@ inline size_t batch_table_bytes(uint32_t count) { return 2 * ((size_t)count + 1)
 #ifndef LR_IW_TOP_LOG2_W
 #define LR_IW_TOP_LOG2_W 14
 #endif
-constexpr uint64_t iw_max(bool weighted) { return 1ull << (weighted ? LR_IW_MAX_LOG2_W : LR_IW_MAX_LOG2); }
+constexpr uint64_t iw_max(uint32_t log2k) { return log2k >= 4 ? (5ull << 18) : (1ull << LR_IW_MAX_LOG2); }
 constexpr uint64_t iw_direct(bool weighted) { return 1ull << (weighted ? LR_IW_DIRECT_LOG2_W : LR_IW_DIRECT_LOG2); }
 constexpr uint64_t iw_top(bool weighted) { return 1ull << (weighted ? LR_IW_TOP_LOG2_W : LR_IW_TOP_LOG2); }
 constexpr size_t iw_node_bytes(bool weighted) { return weighted ? 24 : 8; }
-static_assert(LR_IW_MAX_LOG2 <= 21 && LR_IW_MAX_LOG2_W <= 21, "every lane of the downward pass is resident at once");
+static_assert(LR_IW_MAX_LOG2 <= 21, "every lane of the downward pass is resident at once");
 static_assert(iw_direct(false) <= LOCAL_AUTO_MIN_N && iw_direct(true) <= LOCAL_AUTO_MIN_N,
               "an input ranked by independent walks alone has no contracted path beside it");
 
@@ -278,13 +279,12 @@ bool tune_lookup(uint64_t n, bool weighted, lr_opts* o);
 
 // Base-case shared memory bytes for m elements.
 inline size_t base_lds_bytes(uint64_t m, bool weighted) {
-    // one 8 B (count, successor) word per slot, 4096, 8192 or 16384 slots
-    // (whole columns of the 1024-lane workgroup), weighted with an 8 B sum
-    // per slot as well; weighted levels above 8192 elements: 8 B sum, 4 B
-    // count and 2 B successor arrays
+    // one 8 B (count, successor) word per slot, in whole columns of the
+    // 1024-lane workgroup, weighted with an 8 B sum per slot as well; weighted
+    // levels above 8192 elements: 8 B sum, 4 B count and 2 B successor arrays
     const uint64_t slots = (m <= 4096) ? 4096 : (m <= 8192) ? 8192 : 16384;
     if (weighted) return m <= 8192 ? (size_t)slots * 16 + 64 : (size_t)m * 14 + 64;
-    return (size_t)(m > slots ? m : slots) * 8 + 64;
+    return (size_t)slots * 8;
 }
 
 }  // namespace lr
