@@ -636,7 +636,9 @@ lr_status batch_enqueue(const lr_request* reqs, uint32_t count, void* ws, size_t
     uint32_t chunks = 0;
     for (uint32_t i = 0; i < count; ++i) chunks += (uint32_t)((reqs[i].n + BATCH_CHUNK - 1) / BATCH_CHUNK);
     char* w = carve(ws);
-    if (run_batch_table(reqs, count, p, w, false, chunks, st) != hipSuccess) return LR_ERR_HIP;
+    const bool validate = opts && (opts->flags & LR_VALIDATE);
+    if (run_batch_table(reqs, count, p, w, false, chunks, !batch_direct(p, validate), st) != hipSuccess)
+        return LR_ERR_HIP;
     RunArgs a;
     a.plan = &p;
     a.lplan = ps.autol ? &ps.lp : nullptr;
@@ -649,7 +651,7 @@ lr_status batch_enqueue(const lr_request* reqs, uint32_t count, void* ws, size_t
     for (uint32_t i = 0; i < count; ++i) a.any_root |= reqs[i].root != nullptr;
     a.ws = w;
     a.stream = st;
-    a.validate = opts && (opts->flags & LR_VALIDATE);
+    a.validate = validate;
     a.ev = prof_events(opts && (opts->flags & LR_PROFILE));
     prof_capped(a, p);
     if (LR_DEBUG_WRITES) {
@@ -777,7 +779,8 @@ lr_status lr_batch_graph_launch(lr_batch_graph* g, const lr_request* reqs, uint3
     if (N > g->max_elements) return LR_ERR_WORKSPACE;
     if (N == 0) return LR_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (run_batch_table(reqs, count, g->plan, g->ws, true, g->max_chunks, st) != hipSuccess) return LR_ERR_HIP;
+    if (run_batch_table(reqs, count, g->plan, g->ws, true, g->max_chunks, !batch_direct(g->plan, false), st) != hipSuccess)
+        return LR_ERR_HIP;
     return hipGraphLaunch(g->exec, st) == hipSuccess ? LR_OK : LR_ERR_HIP;
 }
 

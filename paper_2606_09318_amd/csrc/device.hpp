@@ -215,6 +215,7 @@ struct SrcIn {
     const void* weight;
     uint32_t m;
     using L = Lay<W>;
+    __device__ __forceinline__ const SrcIn& bind(uint32_t) const { return *this; }
     static constexpr bool kLinks = true;  // every record is one link: a walk's count is its step count
     struct Raw { uint32_t s; std::conditional_t<WT == 2, int64_t, int32_t> w; };
     __device__ __forceinline__ Raw fetch(uint32_t x) const {
@@ -248,6 +249,7 @@ struct SrcPair {
     const PairRec<WT>* r;
     uint32_t m;
     using L = Lay<true>;
+    __device__ __forceinline__ const SrcPair& bind(uint32_t) const { return *this; }
     static constexpr bool kLinks = true;
     using Raw = PairRec<WT>;
     __device__ __forceinline__ Raw fetch(uint32_t x) const { return r[x]; }
@@ -266,6 +268,7 @@ struct SrcLvl {
     const typename Lay<W>::Rec* e;
     uint32_t m;
     using L = Lay<W>;
+    __device__ __forceinline__ const SrcLvl& bind(uint32_t) const { return *this; }
     static constexpr bool kLinks = false;  // records are segments: counts exceed step counts
     using Raw = typename L::Rec;
     __device__ __forceinline__ Raw fetch(uint32_t x) const { return e[x]; }
@@ -343,6 +346,31 @@ __device__ __forceinline__ uint32_t batch_find(const uint32_t* bases, uint32_t c
     }
     return lo;
 }
+
+// A batch's requests as one source over the concatenated ids, without copying
+// them together: bind finds the request of an element, whose list never leaves
+// it.
+struct SrcBatch {
+    const BatchDesc* d;
+    const uint32_t* bases;
+    const BatchHdr* hdr;
+    uint32_t m;
+    struct Req {
+        const uint32_t* succ;
+        uint32_t lo, n;
+        __device__ __forceinline__ void load(uint32_t x, uint32_t& nxt, Lay<false>::Val& v) const {
+            const uint32_t s = succ[x - lo];
+            const bool t = (s == x - lo) | (s >= n);
+            nxt = t ? (TERM | x) : lo + s;
+            v.c = t ? 0u : 1u;
+        }
+    };
+    __device__ __forceinline__ Req bind(uint32_t x) const {
+        const uint32_t q = batch_find(bases, hdr->count, x);
+        const uint32_t lo = bases[q];
+        return {d[q].succ, lo, bases[q + 1] - lo};
+    }
+};
 
 struct OutBatch {
     const BatchDesc* d;

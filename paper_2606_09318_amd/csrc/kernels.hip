@@ -784,7 +784,7 @@ __global__ __launch_bounds__(BASE_TPB) void k_base_unweighted(Src src, Out out, 
         if (i < m) {
             uint32_t nxt;
             Val v;
-            src.load(i, nxt, v);
+            src.bind(i).load(i, nxt, v);
             e[j] = iw_word(nxt, v.c);
         }
     }
@@ -1136,16 +1136,17 @@ __global__ __launch_bounds__(TPB) void k_iw_first(Src src, Sampler smp, uint64_t
     if (set_mode && i == 0) ctrl->mode = MODE_PLAIN;
     if (i >= m) return;
     using L = Lay<W>;
+    const auto sr = src.bind(i);
     uint32_t nxt;
     typename L::Val acc;
-    src.load(i, nxt, acc);
+    sr.load(i, nxt, acc);
     bool ruler = false;
     for (uint32_t t = 1; !(nxt & TERM); ++t) {
         if constexpr (SAMPLE) ruler = smp.sampled(nxt);
         if (ruler || t >= cap) break;
         typename L::Val v;
         uint32_t nn;
-        src.load(nxt, nn, v);
+        sr.load(nxt, nn, v);
         acc = L::add(acc, v);
         nxt = nn;
     }
@@ -1309,16 +1310,14 @@ __global__ __launch_bounds__(TPB) void k_iw_down(uint64_t* __restrict__ nodes, S
 #pragma unroll
         for (int r = 0; r < PER; ++r) look(r, dbl);
     }
+    [[maybe_unused]] typename Out::Cur cur{};
+    if constexpr (OUTS) cur = out.begin(c0);
 #pragma unroll
     for (int r = 0; r < PER; ++r) {
         const uint32_t c = c0 + r * TPB;
         if (c >= m) continue;
-        if constexpr (OUTS) {
-            auto cur = out.begin(c);
-            out.store(cur, c, acc[r], nxt[r] & IDX);
-        } else {
-            IwRec<W>::store(nodes, base + c, nxt[r], acc[r]);
-        }
+        if constexpr (OUTS) out.store(cur, c, acc[r], nxt[r] & IDX);
+        else IwRec<W>::store(nodes, base + c, nxt[r], acc[r]);
     }
 }
 
@@ -2096,11 +2095,10 @@ __global__ __launch_bounds__(64) void k_batch_desc(BatchDescArg a, BatchDesc* __
 // before it (count + 1 entries each); the header's chunk and element totals;
 // dm[0] = total; with levels > 0 (device-side sizes) also dm[l + 1] =
 // ceil(dm[l] / k_l).
-__global__ __launch_bounds__(1024) void k_batch_index(const BatchDesc* __restrict__ d, uint32_t* __restrict__ bases,
-                                                      uint32_t* __restrict__ boff, BatchHdr* __restrict__ hdr,
-                                                      Ctrl* ctrl, uint32_t levels, LevelShifts ks) {
+__device__ __forceinline__ void batch_index(const BatchDesc* d, uint32_t count, uint32_t* __restrict__ bases,
+                                            uint32_t* __restrict__ boff, BatchHdr* __restrict__ hdr,
+                                            Ctrl* ctrl, uint32_t levels, const LevelShifts& ks) {
     __shared__ uint32_t sh[2 * (1024 / 64)];
-    const uint32_t count = hdr->count;
     const uint32_t per = (count + 1023u) >> 10;
     const uint32_t lo = min(threadIdx.x * per, count), hi = min(lo + per, count);
     uint32_t sn = 0, sc = 0;
@@ -2133,6 +2131,24 @@ __global__ __launch_bounds__(1024) void k_batch_index(const BatchDesc* __restric
             }
         }
     }
+}
+
+__global__ __launch_bounds__(1024) void k_batch_index(const BatchDesc* __restrict__ d, uint32_t* __restrict__ bases,
+                                                      uint32_t* __restrict__ boff, BatchHdr* __restrict__ hdr,
+                                                      Ctrl* ctrl, uint32_t levels, LevelShifts ks) {
+    batch_index(d, hdr->count, bases, boff, hdr, ctrl, levels, ks);
+}
+
+// k_batch_desc and k_batch_index in one launch, for a table of at most
+// BATCH_ARG_DESC requests.
+__global__ __launch_bounds__(1024) void k_batch_table(BatchDescArg a, BatchDesc* __restrict__ dst,
+                                                      uint32_t* __restrict__ bases, uint32_t* __restrict__ boff,
+                                                      BatchHdr* __restrict__ hdr, Ctrl* ctrl, uint32_t levels,
+                                                      LevelShifts ks) {
+    if (threadIdx.x < a.cnt) dst[threadIdx.x] = a.d[threadIdx.x];
+    if (threadIdx.x == 0) hdr->count = a.count;
+    __syncthreads();
+    batch_index(dst, a.count, bases, boff, hdr, ctrl, levels, ks);
 }
 
 // One workgroup per chunk of BATCH_CHUNK ids of one request:
@@ -3391,6 +3407,15 @@ static hipError_t run_srs_t(const RunArgs& a, Out0 out0) {
         rec_ev(a, EV_START);
         if (a.validate) LR_TRY(run_validate(a, p, n));
     }
+    if constexpr (std::is_same_v<Out0, OutBatch>) {
+        if (batch_direct(p, a.validate)) {  // the requests were not copied together
+            SrcBatch srcb{a.desc, a.bases, a.bhdr, n};
+            if (p.iw) LR_TRY((run_iw<W>(p, srcb, out0, n, true, ctrl, ws, st, dm_at(0), g)));
+            else LR_TRY((launch_base<W>(srcb, out0, n, n, ctrl, st, dm_at(0), g)));
+            for (int i = EV_DETECT; i < EV_COUNT; ++i) rec_ev(a, i);
+            return hipSuccess;
+        }
+    }
     if (p.run == 0) {
         if (p.iw) LR_TRY((run_iw<W>(p, src0, out0, n, true, ctrl, ws, st, dm_at(0), g)));
         else LR_TRY((launch_base<W>(src0, out0, n, n, ctrl, st, dm_at(0), g)));
@@ -3895,12 +3920,15 @@ hipError_t run_wyllie(const RunArgs& a, uint64_t n, bool weighted) {
 }
 
 hipError_t run_batch_table(const lr_request* reqs, uint32_t count, const Plan& p, char* ws, bool dev_sizes,
-                           uint32_t max_chunks, hipStream_t st) {
+                           uint32_t max_chunks, bool gather, hipStream_t st) {
     auto* desc = reinterpret_cast<BatchDesc*>(ws + p.off_batch_desc);
     auto* bases = reinterpret_cast<uint32_t*>(ws + p.off_batch_bases);
     uint32_t* boff = bases + p.batch_count + 1;
     auto* hdr = reinterpret_cast<BatchHdr*>(ws + p.off_batch_hdr);
     Ctrl* ctrl = reinterpret_cast<Ctrl*>(ws + p.off_ctrl);
+    LevelShifts ks{};
+    for (uint32_t l = 0; l < p.levels; ++l) ks.lg[l] = (uint8_t)p.log2k[l];
+    const uint32_t levels = dev_sizes ? p.levels : 0u;
     BatchDescArg arg{};
     arg.count = count;
     for (uint32_t first = 0; first < count || first == 0; first += BATCH_ARG_DESC) {
@@ -3910,15 +3938,19 @@ hipError_t run_batch_table(const lr_request* reqs, uint32_t count, const Plan& p
             const lr_request& r = reqs[first + i];
             arg.d[i] = BatchDesc{r.succ, r.rank, r.root, r.n};
         }
+        if (count <= BATCH_ARG_DESC) {
+            hipLaunchKernelGGL(k_batch_table, dim3(1), dim3(1024), 0, st, arg, desc, bases, boff, hdr, ctrl, levels, ks);
+            LR_TRY(hipGetLastError());
+            break;
+        }
         hipLaunchKernelGGL(k_batch_desc, dim3(1), dim3(64), 0, st, arg, desc, hdr);
         LR_TRY(hipGetLastError());
-        if (count == 0) break;
     }
-    LevelShifts ks{};
-    for (uint32_t l = 0; l < p.levels; ++l) ks.lg[l] = (uint8_t)p.log2k[l];
-    hipLaunchKernelGGL(k_batch_index, dim3(1), dim3(1024), 0, st, desc, bases, boff, hdr, ctrl,
-                       dev_sizes ? p.levels : 0u, ks);
-    LR_TRY(hipGetLastError());
+    if (count > BATCH_ARG_DESC) {
+        hipLaunchKernelGGL(k_batch_index, dim3(1), dim3(1024), 0, st, desc, bases, boff, hdr, ctrl, levels, ks);
+        LR_TRY(hipGetLastError());
+    }
+    if (!gather) return hipSuccess;
     const uint32_t grid = std::max(1u, std::min<uint32_t>(max_chunks, (uint32_t)device_cus() * 16));
     hipLaunchKernelGGL(k_batch_gather, dim3(grid), dim3(TPB), 0, st, desc, bases, boff, hdr,
                        reinterpret_cast<uint32_t*>(ws + p.off_batch_succ),

@@ -19,8 +19,7 @@ pytestmark = pytest.mark.gpu
 
 def make(kind, n, seed):
     if kind == "forest":
-        F = workloads.forest(n, mean=5, n_long=1, long_len=n // 3, seed=seed)
-        return F.succ
+        return workloads.forest(n, mean=5, n_long=1, long_len=n // 3, seed=seed).succ
     if kind == "identity":
         return workloads.identity_list(n).succ
     if kind == "reversed":
@@ -44,8 +43,8 @@ def check(succ_np, weight_np=None, opts=None):
     assert np.array_equal(host_u32(r), er) and np.array_equal(host_u32(t), et), n
 
 
-# base case | doubling alone | one level of walks | two levels | chased above
-SIZES = [4096, 4097, 65535, 65536, 65537, 131072 + 5, (1 << 18) - 1, (1 << 19) + 255, (1 << 19) + 257, (1 << 20) + 1,
+# base case (its columns) | doubling alone | one level of walks | two levels | chased above
+SIZES = [1, 1024, 1025, 2049, 4096, 4097, 8192, 8193, 65535, 65536, 65537, 131072 + 5, (1 << 18) - 1, (1 << 19) + 255, (1 << 19) + 257, (1 << 20) + 1,
          (1 << 21) - 1, 1 << 21, (1 << 21) + 1, (1 << 23) - 1, 1 << 23]
 
 
@@ -55,13 +54,13 @@ def test_rank_at_the_edges(kind, n):
     print(f"case: independent walks {kind} n={n}", flush=True)
     succ = make(kind, n, n % 97)
     check(succ)
-    if n < (1 << 20):
-        check(succ, opts=lr.make_opts(spacing=(4, 2)))
+    if 1 < n < (1 << 20):
+        check(succ, opts=lr.make_opts(spacing=(4, 2), base_max=8192))
 
 
 @pytest.mark.parametrize("dtype", [np.int32, np.int64])
 @pytest.mark.parametrize("kind", ["random", "forest", "identity"])
-@pytest.mark.parametrize("n", [8192, 8193, 16384, 16385, 32768, 131072 + 7, (1 << 18) + 1, (1 << 19) - 1, 1 << 19,
+@pytest.mark.parametrize("n", [1, 1025, 2049, 4097, 8192, 8193, 16384, 16385, 32768, 131072 + 7, (1 << 18) + 1, (1 << 19) - 1, 1 << 19,
                                (1 << 22) + 3])
 def test_prefix_sums_at_the_edges(n, kind, dtype):
     print(f"case: independent walks sums {kind} {dtype.__name__} n={n}", flush=True)
@@ -120,6 +119,29 @@ def test_plans_named_by_their_own_spacings_take_the_same_route():
     assert [q.spacing[i] for i in range(q.levels)] == [p.spacing[i] for i in range(p.levels)]
 
 
+def run_batch(inputs, launch):
+    items = [(dev(a), torch.full((a.size,), -1, dtype=torch.int32, device="cuda"),
+              torch.full((a.size,), -1, dtype=torch.int32, device="cuda")) for a in inputs]
+    reqs = lr.requests(items)
+    torch.cuda.synchronize()
+    assert launch(reqs, len(items)) == lr.LR_OK
+    torch.cuda.synchronize()
+    for a, (_, r, t) in zip(inputs, items):
+        _, er, et, _ = oracle.rank(a)
+        assert np.array_equal(host_u32(r), er) and np.array_equal(host_u32(t), et)
+
+
+@pytest.mark.parametrize("count,n", [(1, 1), (1, 8192), (2, 4097), (96, 80), (97, 90), (200, 41), (96, 700), (97, 10_007)])
+def test_batches_read_in_place(count, n):
+    """Batches that are ranked from their requests' arrays, around the table
+    sizes of one launch (96 requests), with an empty request among them."""
+    print(f"case: independent walks, batch of {count} x {n}", flush=True)
+    inputs = [make("forest" if i % 3 == 2 and n > 100 else "random", n + i % 5, i) for i in range(count)]
+    if count > 2:
+        inputs[1] = np.zeros(0, np.uint32)
+    run_batch(inputs, lambda reqs, k: lr.lr_rank_batch(reqs, k, lr.workspace(lr.lr_batch_workspace_bytes(reqs, k))))
+
+
 @pytest.mark.parametrize("cap", [3000, 20_000, 120_000, 900_000])
 def test_batch_graph_sizes_from_the_device(cap):
     """A graph planned for `cap` elements replayed with fewer."""
@@ -128,13 +150,5 @@ def test_batch_graph_sizes_from_the_device(cap):
     g = lr.BatchGraph(cfg, lr.workspace(lr.lr_batch_graph_workspace_bytes(cfg)))
     for k, sizes in enumerate([[cap], [1, cap // 3, cap // 2], [2], [cap // 5, 7, cap // 4 + 1]]):
         inputs = [make("forest" if (i + k) % 3 == 2 and n > 100 else "random", n, 31 * k + i) for i, n in enumerate(sizes)]
-        items = [(dev(a), torch.full((a.size,), -1, dtype=torch.int32, device="cuda"),
-                  torch.full((a.size,), -1, dtype=torch.int32, device="cuda")) for a in inputs]
-        reqs = lr.requests(items)
-        torch.cuda.synchronize()
-        assert g.launch(reqs, len(items)) == lr.LR_OK
-        torch.cuda.synchronize()
-        for a, (_, r, t) in zip(inputs, items):
-            _, er, et, _ = oracle.rank(a)
-            assert np.array_equal(host_u32(r), er) and np.array_equal(host_u32(t), et)
+        run_batch(inputs, g.launch)
     g.close()
