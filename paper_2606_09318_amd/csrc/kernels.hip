@@ -2300,7 +2300,7 @@ __global__ __launch_bounds__(1024) void k_batch_heads(const uint2* __restrict__ 
 //   expand   every element from its chain start's result
 // Elements are owned lane-strided (element j * LC_TPB + lane), so every
 // global access of the tile kernels is coalesced.
-constexpr int LC_TPB = 512;
+constexpr int LC_TPB = 512;  // 2^26 ids 589 us a call; 256 lanes 624, 1024 the same (weighted 25 % slower)
 #ifndef LR_LC_GRID_PER_CU
 #define LR_LC_GRID_PER_CU 64  // chain kernel workgroups per CU, each looping over tiles; 0 = one per tile
 #endif
@@ -2356,9 +2356,9 @@ __global__ __launch_bounds__(LC_TPB) void k_lc_chain(const uint32_t* __restrict_
                 if constexpr (WT == 1) wv[j] = static_cast<const int32_t*>(weight)[b + i];
                 if constexpr (WT == 3) wv[j] = static_cast<const int8_t*>(weight)[b + i];
                 if constexpr (WT == 2) wv[j] = static_cast<const int64_t*>(weight)[b + i];
-                PD[i] = i;
                 if constexpr (W) WS[i] = 0;
             }
+            PD[i] = i;
         }
         __syncthreads();
 #pragma unroll
@@ -2401,26 +2401,36 @@ __global__ __launch_bounds__(LC_TPB) void k_lc_chain(const uint32_t* __restrict_
             }
             if (lane == 63) cnt[tile] = inc;
         }
-        for (int round = 0; round < LC_ROUNDS; ++round) {
-            int changed = 0;
-            if constexpr (!W) {
-                // in place: a 32-bit entry always holds a consistent (target, count)
-                // pair, so reading a neighbour's newer value only jumps further
+        if constexpr (!W) {
+            // in place and without barriers: a 32-bit entry always holds a
+            // consistent (target, count) pair, so an older one only jumps less
+            // far, and a wavefront stops when its own elements have reached
+            // their starts (entries that point to themselves) or, on a cycle
+            // inside the tile, counted more links than a tile has. Bound by the
+            // LDS gathers (2^26 ids: 342 us with two barriers a round, 285 so)
+            for (;;) {
+                uint32_t u[LC_PER];
+                bool open = false;
+#pragma unroll
+                for (int j = 0; j < LC_PER; ++j)
+                    u[j] = __hip_atomic_load(&PD[v[j] & LC_TGT], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 #pragma unroll
                 for (int j = 0; j < LC_PER; ++j) {
-                    const uint32_t i = j * LC_TPB + threadIdx.x;
-                    const uint32_t p = v[j] & LC_TGT;
-                    if (i < len && p != i) {
-                        const uint32_t u = PD[p];
-                        const uint32_t q = u & LC_TGT;
-                        if (q != p) {
-                            v[j] = q | (((v[j] >> 16) + (u >> 16)) << 16);
-                            PD[i] = v[j];
-                            changed = 1;
-                        }
+                    const uint32_t q = u[j] & LC_TGT;
+                    const bool move = q != (v[j] & LC_TGT) && (v[j] >> 16) < LC_T;
+                    if (move) {
+                        v[j] = q | (((v[j] >> 16) + (u[j] >> 16)) << 16);
+                        __hip_atomic_store(&PD[j * LC_TPB + threadIdx.x], v[j], __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WORKGROUP);
+                        open = true;
                     }
                 }
-            } else {
+                if (!__any(open)) break;
+            }
+            __syncthreads();  // DIR, and the starts' entries, before the next use
+        } else {
+            for (int round = 0; round < LC_ROUNDS; ++round) {
+                int changed = 0;
                 // target, count and weight live in two words: read all, then write all
                 uint32_t nv[LC_PER];
                 int64_t nw[LC_PER];
@@ -2451,8 +2461,8 @@ __global__ __launch_bounds__(LC_TPB) void k_lc_chain(const uint32_t* __restrict_
                         changed = 1;
                     }
                 }
+                if (!__syncthreads_or(changed)) break;
             }
-            if (!__syncthreads_or(changed)) break;
         }
         if (threadIdx.x < (len + 31) / 32) dir[(b >> 5) + threadIdx.x] = DIR[threadIdx.x];
 #pragma unroll
