@@ -301,6 +301,23 @@ static size_t layout_spawn(Plan* p, uint64_t n, size_t off) {
     return off;
 }
 
+// The contracted path's plan for a short list (see PlanSet): only where its own
+// plan is the planner's and chases a level. Its nodes lie over the arrays of the
+// levels that are then not chased.
+static bool plan_small(const Plan& local, size_t end, Plan* sp) {
+    if (!local.iw || local.run == 0) return false;
+    if (plan_levels(std::min(local.m[0], LOCAL_SMALL_MAX), local.weighted, nullptr, false, sp) != LR_OK) return false;
+    sp->iw = true;
+    sp->run = 0;
+    sp->top = 0;
+    while (sp->top < sp->levels && sp->m[sp->top] > iw_top(sp->weighted)) ++sp->top;
+    size_t need = 0;
+    for (uint32_t l = 0; l <= sp->top; ++l) need += (size_t)sp->m[l] * iw_node_bytes(sp->weighted);
+    sp->off_nodes = local.off_slot[0];
+    constexpr uint32_t sizes = sizeof(Ctrl::dms) / sizeof(uint32_t);
+    return sp->top < sizes && sp->off_nodes + need <= end;
+}
+
 lr_status make_plans(uint64_t n, bool weighted, const lr_opts* o, uint32_t batch_count, PlanSet* ps) {
     *ps = PlanSet{};
     if (n >= (1ull << 31)) return LR_ERR_UNSUPPORTED;
@@ -373,6 +390,7 @@ lr_status make_plans(uint64_t n, bool weighted, const lr_opts* o, uint32_t batch
     }
     place_iw(body, off, p);
     if (ps->autol) place_iw(body, off, &ps->lp);
+    if (force || ps->autol) ps->small = plan_small(force ? *p : ps->lp, off, &ps->sp);
     if (batch_count) {
         p->batch_count = batch_count;
         p->off_batch_succ = off;
@@ -465,6 +483,7 @@ static lr_status rank_common(const uint32_t* succ, const void* weight, int wt, b
     RunArgs a;
     a.plan = &p;
     a.lplan = ps.autol ? &ps.lp : nullptr;
+    a.splan = ps.small ? &ps.sp : nullptr;
     a.succ = succ;
     a.weight = weight;
     a.wt = wt;
@@ -642,6 +661,7 @@ lr_status batch_enqueue(const lr_request* reqs, uint32_t count, void* ws, size_t
     RunArgs a;
     a.plan = &p;
     a.lplan = ps.autol ? &ps.lp : nullptr;
+    a.splan = ps.small ? &ps.sp : nullptr;
     a.succ = reinterpret_cast<const uint32_t*>(w + p.off_batch_succ);
     a.desc = reinterpret_cast<const BatchDesc*>(w + p.off_batch_desc);
     a.bases = reinterpret_cast<const uint32_t*>(w + p.off_batch_bases);

@@ -43,24 +43,28 @@ struct Ctrl {
     uint32_t spn;                           // ruler spawning: number of spawned rulers
     uint32_t conts;                         // packed visit log: continuation ids handed out
     uint32_t hc_done;                       // workgroups of a head-count kernel that have finished
-    uint32_t pad[28];
+    uint32_t dms[4];                        // MODE_LOCAL_SMALL: element count per level
+    uint32_t pad[24];
 };
 static_assert(sizeof(Ctrl) == 256, "Ctrl layout");
 
 // Device-side choice between enqueued kernel sequences: a kernel whose gate
-// is set runs only when the word it points to (Ctrl.mode) holds `want`, and
-// otherwise returns before touching memory. A null gate always runs.
+// is set runs only when the word it points to (Ctrl.mode) holds a value whose
+// bit is in `want`, and otherwise returns before touching memory. A null gate
+// always runs.
 struct Gate {
     const uint32_t* p;
     uint32_t want;
-    __device__ __forceinline__ bool off() const { return p && *p != want; }
+    __device__ __forceinline__ bool off() const { return p && !((want >> *p) & 1u); }
 };
 
 // Values of Ctrl.mode: the path whose kernels run. Each path's first kernels
 // set it (the automatic choice between plain and contracted path included),
 // and a walk that reaches its step cap turns it to MODE_FALLBACK, so every
-// later kernel of the path returns and only the fallback runs.
-enum : uint32_t { MODE_PLAIN = 0, MODE_LOCAL = 1, MODE_FALLBACK = 2, MODE_SPAWN = 3 };
+// later kernel of the path returns and only the fallback runs. MODE_LOCAL_SMALL:
+// the contracted path with a list so short that it is not chased.
+enum : uint32_t { MODE_PLAIN = 0, MODE_LOCAL = 1, MODE_FALLBACK = 2, MODE_SPAWN = 3, MODE_LOCAL_SMALL = 4 };
+constexpr uint32_t mode_bit(uint32_t m) { return 1u << m; }
 
 // Ctrl.err bits (LR_VALIDATE): the input check sets ERR_INPUT (an index out
 // of range, two predecessors); the ranking path's consistency checks set

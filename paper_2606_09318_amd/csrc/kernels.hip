@@ -1124,17 +1124,10 @@ template <> struct IwRec<true> {
 
 // Level 0 of the nodes from the source's records. SAMPLE = false: no rulers,
 // every element walks `cap` steps (the list is small enough for the doubling
-// alone). set_mode: the input itself, whose first kernel sets the path word.
+// alone).
 template <bool W, bool SAMPLE, class Src>
-__global__ __launch_bounds__(TPB) void k_iw_first(Src src, Sampler smp, uint64_t* __restrict__ nodes, uint32_t base1,
-                                                  uint32_t m, uint32_t cap, Ctrl* ctrl, uint32_t set_mode,
-                                                  const uint32_t* dm, Gate gate) {
-    if (gate.off()) return;
-    if (dm) m = min(dm[0], m);
-    smp.m = src.m = m;
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (set_mode && i == 0) ctrl->mode = MODE_PLAIN;
-    if (i >= m) return;
+__device__ __forceinline__ void iw_first(const Src& src, const Sampler& smp, uint64_t* __restrict__ nodes,
+                                         uint32_t base1, uint32_t i, uint32_t cap) {
     using L = Lay<W>;
     const auto sr = src.bind(i);
     uint32_t nxt;
@@ -1158,6 +1151,18 @@ __global__ __launch_bounds__(TPB) void k_iw_first(Src src, Sampler smp, uint64_t
     IwRec<W>::store(nodes, at, nxt, acc);
 }
 
+// The input itself: its first kernel sets the path word.
+template <bool W, bool SAMPLE, class Src>
+__global__ __launch_bounds__(TPB) void k_iw_first(Src src, Sampler smp, uint64_t* __restrict__ nodes, uint32_t base1,
+                                                  uint32_t m, uint32_t cap, Ctrl* ctrl, const uint32_t* dm, Gate gate) {
+    if (gate.off()) return;
+    if (dm) m = min(dm[0], m);
+    smp.m = src.m = m;
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) ctrl->mode = MODE_PLAIN;
+    if (i < m) iw_first<W, SAMPLE>(src, smp, nodes, base1, i, cap);
+}
+
 // Composes (nxt, acc) with the record of node nxt; false: caught between two
 // of its stores (nothing changed), look again device-scope.
 template <bool W, bool DEV>
@@ -1173,14 +1178,8 @@ __device__ __forceinline__ bool iw_hop(const uint64_t* nodes, uint32_t& nxt, typ
 // Level j >= 1: every node's record hops on to the next of level j's rulers,
 // which are the nodes of level j + 1. total: nodes in all.
 template <bool W>
-__global__ __launch_bounds__(TPB) void k_iw_walk(uint64_t* __restrict__ nodes, Sampler smp, uint32_t base,
-                                                 uint32_t basen, uint32_t total, uint32_t m, uint32_t cap,
-                                                 const uint32_t* dm, Gate gate) {
-    if (gate.off()) return;
-    if (dm) m = min(dm[0], m);
-    smp.m = m;
-    const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= m) return;
+__device__ __forceinline__ void iw_walk(uint64_t* __restrict__ nodes, const Sampler& smp, uint32_t base, uint32_t basen,
+                                        uint32_t total, uint32_t c, uint32_t cap) {
     using L = Lay<W>;
     uint32_t nxt;
     typename L::Val acc;
@@ -1198,6 +1197,17 @@ __global__ __launch_bounds__(TPB) void k_iw_walk(uint64_t* __restrict__ nodes, S
     IwRec<W>::store(nodes, smp.sampled(c) ? basen + (c >> smp.log2k) : base + c, nxt, acc);
 }
 
+template <bool W>
+__global__ __launch_bounds__(TPB) void k_iw_walk(uint64_t* __restrict__ nodes, Sampler smp, uint32_t base,
+                                                 uint32_t basen, uint32_t total, uint32_t m, uint32_t cap,
+                                                 const uint32_t* dm, Gate gate) {
+    if (gate.off()) return;
+    if (dm) m = min(dm[0], m);
+    smp.m = m;
+    const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
+    if (c < m) iw_walk<W>(nodes, smp, base, basen, total, c, cap);
+}
+
 // The doubling of the last level, nodes [base, base + m). OUTS: the results go
 // to `out`, else they stay in the nodes. cap: hops after which an element is
 // left to the downward pass. A hop's stores are awaited before the next hop's
@@ -1207,17 +1217,11 @@ __global__ __launch_bounds__(TPB) void k_iw_walk(uint64_t* __restrict__ nodes, S
 // spread a few hundred waves over all CUs (weighted 100,003 elements 43 us, 51
 // with 256 lanes; unweighted 1 us).
 constexpr uint32_t IW_DBL_TPB = 64;
-template <bool W, bool OUTS, class Out>
-__global__ __launch_bounds__(IW_DBL_TPB) void k_iw_double(uint64_t* __restrict__ nodes, uint32_t base, uint32_t total,
-                                                          uint32_t m, uint32_t climit, uint32_t cap, Ctrl* ctrl,
-                                                          Out out, const uint32_t* dm, Gate gate) {
-    if (gate.off()) return;
-    if (dm) m = min(dm[0], m);
+template <bool W>
+__device__ __forceinline__ void iw_double(uint64_t* __restrict__ nodes, uint32_t base, uint32_t total, uint32_t c,
+                                          uint32_t climit, uint32_t cap, Ctrl* ctrl, uint32_t& nxt,
+                                          typename Lay<W>::Val& acc) {
     using L = Lay<W>;
-    const uint32_t c = blockIdx.x * IW_DBL_TPB + threadIdx.x;
-    if (c >= m) return;
-    uint32_t nxt;
-    typename L::Val acc;
     while (!IwRec<W>::template load<true>(nodes, base + c, nxt, acc)) {}
     for (uint32_t hop = 0; !(nxt & TERM) && hop < cap; ++hop) {
         bool bad = nxt >= total;
@@ -1233,6 +1237,19 @@ __global__ __launch_bounds__(IW_DBL_TPB) void k_iw_double(uint64_t* __restrict__
         IwRec<W>::store(nodes, base + c, nxt, acc);
         __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
     }
+}
+
+template <bool W, bool OUTS, class Out>
+__global__ __launch_bounds__(IW_DBL_TPB) void k_iw_double(uint64_t* __restrict__ nodes, uint32_t base, uint32_t total,
+                                                          uint32_t m, uint32_t climit, uint32_t cap, Ctrl* ctrl,
+                                                          Out out, const uint32_t* dm, Gate gate) {
+    if (gate.off()) return;
+    if (dm) m = min(dm[0], m);
+    const uint32_t c = blockIdx.x * IW_DBL_TPB + threadIdx.x;
+    if (c >= m) return;
+    uint32_t nxt;
+    typename Lay<W>::Val acc;
+    iw_double<W>(nodes, base, total, c, climit, cap, ctrl, nxt, acc);
     if constexpr (OUTS) {
         auto cur = out.begin(c);
         out.store(cur, c, acc, nxt & IDX);
@@ -1245,19 +1262,14 @@ __global__ __launch_bounds__(IW_DBL_TPB) void k_iw_double(uint64_t* __restrict__
 // pass over the whole list, which must solve every element (any other may
 // leave some of them to it). PER elements a lane, the loads of all issued
 // before any is used.
-template <bool W, bool OUTS, int PER, class Out>
-__global__ __launch_bounds__(TPB) void k_iw_down(uint64_t* __restrict__ nodes, Sampler smp, uint32_t base,
-                                                 uint32_t basen, uint32_t total, uint32_t m, uint32_t climit,
-                                                 uint32_t last, uint32_t set_mode, Ctrl* ctrl, Out out,
-                                                 const uint32_t* dm, Gate gate) {
-    if (gate.off()) return;
-    if (dm) m = min(dm[0], m);
-    smp.m = m;
+template <bool W, int PER>
+__device__ __forceinline__ void iw_down(uint64_t* __restrict__ nodes, const Sampler& smp, uint32_t base, uint32_t basen,
+                                        uint32_t total, uint32_t m, uint32_t c0, uint32_t climit, uint32_t last,
+                                        uint32_t set_mode, Ctrl* ctrl, uint32_t (&nxt)[PER],
+                                        typename Lay<W>::Val (&acc)[PER]) {
     using L = Lay<W>;
-    const uint32_t c0 = blockIdx.x * (TPB * PER) + threadIdx.x;
-    if (c0 >= m) return;
-    uint32_t nxt[PER], at[PER], nn[PER];
-    typename L::Val acc[PER], v[PER];
+    uint32_t at[PER], nn[PER];
+    typename L::Val v[PER];
     bool ok[PER];
 #pragma unroll
     for (int r = 0; r < PER; ++r) {
@@ -1310,6 +1322,21 @@ __global__ __launch_bounds__(TPB) void k_iw_down(uint64_t* __restrict__ nodes, S
 #pragma unroll
         for (int r = 0; r < PER; ++r) look(r, dbl);
     }
+}
+
+template <bool W, bool OUTS, int PER, class Out>
+__global__ __launch_bounds__(TPB) void k_iw_down(uint64_t* __restrict__ nodes, Sampler smp, uint32_t base,
+                                                 uint32_t basen, uint32_t total, uint32_t m, uint32_t climit,
+                                                 uint32_t last, uint32_t set_mode, Ctrl* ctrl, Out out,
+                                                 const uint32_t* dm, Gate gate) {
+    if (gate.off()) return;
+    if (dm) m = min(dm[0], m);
+    smp.m = m;
+    const uint32_t c0 = blockIdx.x * (TPB * PER) + threadIdx.x;
+    if (c0 >= m) return;
+    uint32_t nxt[PER];
+    typename Lay<W>::Val acc[PER];
+    iw_down<W, PER>(nodes, smp, base, basen, total, m, c0, climit, last, set_mode, ctrl, nxt, acc);
     [[maybe_unused]] typename Out::Cur cur{};
     if constexpr (OUTS) cur = out.begin(c0);
 #pragma unroll
@@ -1319,6 +1346,95 @@ __global__ __launch_bounds__(TPB) void k_iw_down(uint64_t* __restrict__ nodes, S
         if constexpr (OUTS) out.store(cur, c, acc[r], nxt[r] & IDX);
         else IwRec<W>::store(nodes, base + c, nxt[r], acc[r]);
     }
+}
+
+// The same on a level's records, whose results replace them. A call that
+// enqueues more than one path passes the list of each, and the path word
+// selects: the launches are shared by the plain path's list (0), the
+// contracted one's level above its chases (1), and the contracted list itself
+// where it is short (2).
+template <bool W>
+struct IwArg {
+    typename Lay<W>::Rec* rec;  // the records, where this launch reads or replaces them
+    uint64_t* nodes;
+    const uint32_t* dm;         // the level's size, if only the device knows it (m is then a capacity)
+    uint32_t m;                 // 0: nothing to do in this launch
+    uint32_t base, basen, total, log2k, seed, climit;
+};
+template <bool W>
+struct IwArgs {
+    IwArg<W> a[3];
+    const uint32_t* mode;  // null: a[0]
+};
+// f on the list that the path word selects, if it has something to do here.
+// (One copy of f per list: a list picked into a variable would be copied
+// through scratch memory, which cost every launch 20 us.)
+template <bool W, class F>
+__device__ __forceinline__ void iw_pick(const IwArgs<W>& s, F f) {
+    auto on = [&](const IwArg<W>& a) {
+        uint32_t m = a.m;
+        if (m && a.dm) m = min(*a.dm, m);
+        if (m) f(a, m);
+    };
+    const uint32_t md = s.mode ? *s.mode : (uint32_t)MODE_PLAIN;
+    if (md == MODE_PLAIN) on(s.a[0]);
+    else if (md == MODE_LOCAL) on(s.a[1]);
+    else if (md == MODE_LOCAL_SMALL) on(s.a[2]);
+}
+
+template <bool W>
+__global__ __launch_bounds__(TPB) void k_iwl_first(IwArgs<W> s) {
+    iw_pick(s, [](const IwArg<W>& a, uint32_t m) {
+        const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+        if (i >= m) return;
+        const SrcLvl<W> src{a.rec, m};
+        const Sampler smp{m, a.log2k, a.seed};
+        if (a.log2k) iw_first<W, true>(src, smp, a.nodes, a.basen, i, LR_IW_CAP);
+        else iw_first<W, false>(src, smp, a.nodes, a.basen, i, IW_CAP_ALONE);
+    });
+}
+
+template <bool W>
+__global__ __launch_bounds__(TPB) void k_iwl_walk(IwArgs<W> s) {
+    iw_pick(s, [](const IwArg<W>& a, uint32_t m) {
+        const uint32_t c = blockIdx.x * blockDim.x + threadIdx.x;
+        if (c < m) iw_walk<W>(a.nodes, Sampler{m, a.log2k, a.seed}, a.base, a.basen, a.total, c, LR_IW_CAP);
+    });
+}
+
+// rec: the doubling alone, whose results are final (unweighted ones are in
+// place already).
+template <bool W>
+__global__ __launch_bounds__(IW_DBL_TPB) void k_iwl_double(IwArgs<W> s, Ctrl* ctrl) {
+    iw_pick(s, [ctrl](const IwArg<W>& a, uint32_t m) {
+        const uint32_t c = blockIdx.x * IW_DBL_TPB + threadIdx.x;
+        if (c >= m) return;
+        uint32_t nxt;
+        typename Lay<W>::Val acc;
+        iw_double<W>(a.nodes, a.base, a.total, c, a.climit, a.base ? IW_TOP_CAP : NONE, ctrl, nxt, acc);
+        if constexpr (W) {
+            if (a.rec) a.rec[c] = Lay<W>::res(acc, nxt & IDX);
+        }
+    });
+}
+
+template <bool W, int PER>
+__global__ __launch_bounds__(TPB) void k_iwl_down(IwArgs<W> s, Ctrl* ctrl) {
+    iw_pick(s, [ctrl](const IwArg<W>& a, uint32_t m) {
+        const uint32_t c0 = blockIdx.x * (TPB * PER) + threadIdx.x;
+        if (c0 >= m) return;
+        uint32_t nxt[PER];
+        typename Lay<W>::Val acc[PER];
+        iw_down<W, PER>(a.nodes, Sampler{m, a.log2k, a.seed}, a.base, a.basen, a.total, m, c0, a.climit,
+                        a.base ? 0u : 1u, 0u, ctrl, nxt, acc);
+#pragma unroll
+        for (int r = 0; r < PER; ++r) {
+            const uint32_t c = c0 + r * TPB;
+            if (c >= m) continue;
+            if (a.base) IwRec<W>::store(a.nodes, a.base + c, nxt[r], acc[r]);
+            else a.rec[c] = Lay<W>::res(acc[r], nxt[r] & IDX);
+        }
+    });
 }
 
 // --------------------------------------------------------------- resolve --
@@ -2505,10 +2621,12 @@ __global__ __launch_bounds__(LC_TPB) void k_lc_chain(const uint32_t* __restrict_
 // Exclusive scan of the per-tile start counts (one workgroup); publishes the
 // contracted list's size and the sizes of the ruling-set levels above it.
 
-// forced: the contracted path runs alone and this kernel sets its mode
+// forced: the contracted path runs alone and this kernel sets its mode. small: a
+// list of at most that many elements (0: none) is not chased, its levels have
+// the sizes of kss.
 __global__ __launch_bounds__(1024) void k_lc_scan(uint32_t* __restrict__ cnt, uint32_t ntiles, Ctrl* ctrl,
                                                   uint32_t levels, LevelShifts ks, uint32_t cap, uint32_t forced,
-                                                  Gate gate) {
+                                                  uint32_t small, uint32_t slevels, LevelShifts kss, Gate gate) {
     if (gate.off()) return;
     __shared__ uint32_t sh[1024 / 64];
     const uint32_t total = wg_exscan_inplace(cnt, ntiles, sh);
@@ -2527,6 +2645,15 @@ __global__ __launch_bounds__(1024) void k_lc_scan(uint32_t* __restrict__ cnt, ui
             ctrl->dm[l + 1] = m;
         }
         ctrl->single = 0;
+        if (total <= small) {
+            ctrl->mode = MODE_LOCAL_SMALL;
+            m = total;
+            ctrl->dms[0] = m;
+            for (uint32_t l = 0; l < slevels; ++l) {
+                m = (m + (1u << kss.lg[l]) - 1u) >> kss.lg[l];
+                ctrl->dms[l + 1] = m;
+            }
+        }
     }
 }
 
@@ -3073,77 +3200,131 @@ static hipError_t launch_base(Src src, Out out, uint32_t m, uint32_t climit, Ctr
     }
 }
 
-// The lists of level p.run and above, by independent walks: levels run ..
-// top - 1 walk, level top is doubled, then downward. The source's results go
-// to `out`; input: the source is the caller's input, whose first kernel sets
-// the path word.
-constexpr int IW_PER = 4;  // elements per lane of the downward pass: all of a list's lanes are resident
+// The input by independent walks: levels 0 .. top - 1 walk, level top is
+// doubled, then downward.
+constexpr int IW_PER = 4;                   // elements per lane of the downward pass: all of a list's lanes are resident
+constexpr uint32_t IW_PER_MIN = 1u << 18;  // up to here one element a lane fills the chip better
 
 template <bool W, class Src, class Out>
-static hipError_t run_iw(const Plan& p, Src src, Out out, uint32_t climit, bool input, Ctrl* ctrl, char* ws,
-                         hipStream_t st, const uint32_t* dm, Gate gate) {
+static hipError_t run_iw(const Plan& p, Src src, Out out, uint32_t n, Ctrl* ctrl, char* ws, hipStream_t st,
+                         const uint32_t* dm, Gate gate) {
     uint64_t* nodes = reinterpret_cast<uint64_t*>(ws + p.off_nodes);
-    const uint32_t r0 = p.run, T = p.top;
+    const uint32_t T = p.top;
     uint32_t base[LR_MAX_LEVELS + 2] = {};
-    for (uint32_t l = r0; l <= T; ++l) base[l + 1] = base[l] + (uint32_t)p.m[l];
+    for (uint32_t l = 0; l <= T; ++l) base[l + 1] = base[l] + (uint32_t)p.m[l];
     const uint32_t total = base[T + 1];
     auto smp = [&](uint32_t l) { return Sampler{(uint32_t)p.m[l], p.log2k[l], p.lseed[l]}; };
-    auto dml = [&](uint32_t l) { return dm ? dm + (l - r0) : nullptr; };
-    auto grid = [](uint64_t m, uint32_t per) { return dim3((uint32_t)((m + TPB * per - 1) / (TPB * per))); };
-    auto gtop = [](uint64_t m) { return dim3((uint32_t)((m + IW_DBL_TPB - 1) / IW_DBL_TPB)); };
-    const dim3 b(TPB);
-    const uint32_t m0 = (uint32_t)p.m[r0];
-    if (T == r0) {
-        hipLaunchKernelGGL((k_iw_first<W, false, Src>), grid(m0, 1), b, 0, st, src, Sampler{}, nodes, 0u, m0,
-                           IW_CAP_ALONE, ctrl, (uint32_t)input, dm, gate);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_iw_double<W, true, Out>), gtop(m0), dim3(IW_DBL_TPB), 0, st, nodes, 0u, total, m0, climit,
-                           NONE, ctrl, out, dm, gate);
+    auto dml = [&](uint32_t l) { return dm ? dm + l : nullptr; };
+    auto grid = [](uint64_t m, uint32_t per) { return dim3((uint32_t)((m + per - 1) / per)); };
+    const dim3 b(TPB), bd(IW_DBL_TPB);
+    hipError_t e;
+    if (T == 0) {
+        hipLaunchKernelGGL((k_iw_first<W, false, Src>), grid(n, TPB), b, 0, st, src, Sampler{}, nodes, 0u, n,
+                           IW_CAP_ALONE, ctrl, dm, gate);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL((k_iw_double<W, true, Out>), grid(n, IW_DBL_TPB), bd, 0, st, nodes, 0u, total, n, n, NONE,
+                           ctrl, out, dm, gate);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL((k_iw_first<W, true, Src>), grid(m0, 1), b, 0, st, src, smp(r0), nodes, base[r0 + 1], m0,
-                       (uint32_t)LR_IW_CAP, ctrl, (uint32_t)input, dm, gate);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    for (uint32_t l = r0 + 1; l < T; ++l) {
-        hipLaunchKernelGGL((k_iw_walk<W>), grid(p.m[l], 1), b, 0, st, nodes, smp(l), base[l], base[l + 1], total,
+    hipLaunchKernelGGL((k_iw_first<W, true, Src>), grid(n, TPB), b, 0, st, src, smp(0), nodes, base[1], n,
+                       (uint32_t)LR_IW_CAP, ctrl, dm, gate);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    for (uint32_t l = 1; l < T; ++l) {
+        hipLaunchKernelGGL((k_iw_walk<W>), grid(p.m[l], TPB), b, 0, st, nodes, smp(l), base[l], base[l + 1], total,
                            (uint32_t)p.m[l], (uint32_t)LR_IW_CAP, dml(l), gate);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     const OutLvl<W> none{};
-    hipLaunchKernelGGL((k_iw_double<W, false, OutLvl<W>>), gtop(p.m[T]), dim3(IW_DBL_TPB), 0, st, nodes, base[T], total,
-                       (uint32_t)p.m[T], climit, IW_TOP_CAP, ctrl, none, dml(T), gate);
+    hipLaunchKernelGGL((k_iw_double<W, false, OutLvl<W>>), grid(p.m[T], IW_DBL_TPB), bd, 0, st, nodes, base[T], total,
+                       (uint32_t)p.m[T], n, IW_TOP_CAP, ctrl, none, dml(T), gate);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    for (uint32_t l = T - 1; l > r0; --l) {
-        hipLaunchKernelGGL((k_iw_down<W, false, 1, OutLvl<W>>), grid(p.m[l], 1), b, 0, st, nodes, smp(l),
-                           base[l], base[l + 1], total, (uint32_t)p.m[l], climit, 0u, 0u, ctrl, none, dml(l), gate);
+    for (uint32_t l = T - 1; l > 0; --l) {
+        hipLaunchKernelGGL((k_iw_down<W, false, 1, OutLvl<W>>), grid(p.m[l], TPB), b, 0, st, nodes, smp(l), base[l],
+                           base[l + 1], total, (uint32_t)p.m[l], n, 0u, 0u, ctrl, none, dml(l), gate);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    if (m0 <= (1u << 18))
-        hipLaunchKernelGGL((k_iw_down<W, true, 1, Out>), grid(m0, 1), b, 0, st, nodes, smp(r0), 0u,
-                           base[r0 + 1], total, m0, climit, 1u, (uint32_t)input, ctrl, out, dm, gate);
+    if (n <= IW_PER_MIN)
+        hipLaunchKernelGGL((k_iw_down<W, true, 1, Out>), grid(n, TPB), b, 0, st, nodes, smp(0), 0u, base[1], total, n, n,
+                           1u, 1u, ctrl, out, dm, gate);
     else
-        hipLaunchKernelGGL((k_iw_down<W, true, IW_PER, Out>), grid(m0, IW_PER), b, 0, st, nodes, smp(r0), 0u,
-                           base[r0 + 1], total, m0, climit, 1u, (uint32_t)input, ctrl, out, dm, gate);
+        hipLaunchKernelGGL((k_iw_down<W, true, IW_PER, Out>), grid(n, TPB * IW_PER), b, 0, st, nodes, smp(0), 0u,
+                           base[1], total, n, n, 1u, 1u, ctrl, out, dm, gate);
     return hipGetLastError();
 }
 
-// A level's records, ranked in place. Unweighted records that the doubling
-// takes at once are their own nodes.
+// Levels' records, ranked in place: one list per path that the call enqueues
+// (see IwArgs; unused ones have no plan). dm: the list's sizes on the device,
+// level by level, or null.
 template <bool W>
-static hipError_t run_iw_level(const Plan& p, typename Lay<W>::Rec* rec, uint32_t climit, Ctrl* ctrl, char* ws,
-                               hipStream_t st, const uint32_t* dm, Gate gate) {
-    const uint32_t m = (uint32_t)p.m[p.run];
-    if constexpr (!W) {
-        if (p.top == p.run) {
-            hipLaunchKernelGGL((k_iw_double<false, false, OutLvl<false>>), dim3((m + IW_DBL_TPB - 1) / IW_DBL_TPB),
-                               dim3(IW_DBL_TPB), 0, st, reinterpret_cast<uint64_t*>(rec), 0u, m, m, climit, NONE, ctrl,
-                               OutLvl<false>{}, dm, gate);
-            return hipGetLastError();
+struct IwSet {
+    const Plan* p = nullptr;
+    typename Lay<W>::Rec* rec = nullptr;
+    const uint32_t* dm = nullptr;
+};
+
+template <bool W>
+static hipError_t run_iw_levels(const IwSet<W> (&set)[3], const uint32_t* mode, uint32_t climit, Ctrl* ctrl, char* ws,
+                                hipStream_t st) {
+    uint32_t depth = 0;  // most levels of walks
+    for (const auto& q : set)
+        if (q.p) depth = std::max(depth, q.p->top - q.p->run);
+    // the launch on level run + j of every list that has one; top: its last
+    auto args = [&](uint32_t j, bool top, bool rec, uint64_t* most) {
+        IwArgs<W> s{};
+        s.mode = mode;
+        *most = 0;
+        for (int k = 0; k < 3; ++k) {
+            const Plan* p = set[k].p;
+            if (!p) continue;
+            const uint32_t d = p->top - p->run, i = top ? d : j;
+            if (!top && i >= d && !(W && d == 0 && i == 0 && rec)) continue;  // a weighted list's nodes are always made
+            IwArg<W>& a = s.a[k];
+            uint32_t base = 0;
+            for (uint32_t t = 0; t < i; ++t) base += (uint32_t)p->m[p->run + t];
+            a.nodes = (!W && d == 0) ? reinterpret_cast<uint64_t*>(set[k].rec)
+                                     : reinterpret_cast<uint64_t*>(ws + p->off_nodes);
+            a.rec = (rec || d == 0) ? set[k].rec : nullptr;
+            a.dm = set[k].dm ? set[k].dm + i : nullptr;
+            a.m = (uint32_t)p->m[p->run + i];
+            a.base = base;
+            a.basen = base + a.m;
+            a.total = base + a.m;
+            for (uint32_t t = i + 1; t <= d; ++t) a.total += (uint32_t)p->m[p->run + t];
+            a.log2k = i < d ? p->log2k[p->run + i] : 0u;
+            a.seed = i < d ? p->lseed[p->run + i] : 0u;
+            a.climit = climit;
+            *most = std::max<uint64_t>(*most, a.m);
         }
+        return s;
+    };
+    auto grid = [](uint64_t m, uint32_t per) { return dim3((uint32_t)((m + per - 1) / per)); };
+    const dim3 b(TPB);
+    uint64_t most;
+    hipError_t e;
+    IwArgs<W> s = args(0, false, true, &most);
+    if (most) {
+        hipLaunchKernelGGL(k_iwl_first<W>, grid(most, TPB), b, 0, st, s);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    return run_iw<W>(p, SrcLvl<W>{rec, m}, OutLvl<W>{rec}, climit, false, ctrl, ws, st, dm, gate);
+    for (uint32_t j = 1; j < depth; ++j) {
+        s = args(j, false, false, &most);
+        hipLaunchKernelGGL(k_iwl_walk<W>, grid(most, TPB), b, 0, st, s);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    s = args(0, true, false, &most);
+    hipLaunchKernelGGL(k_iwl_double<W>, grid(most, IW_DBL_TPB), dim3(IW_DBL_TPB), 0, st, s, ctrl);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    for (uint32_t j = depth; j-- > 0;) {
+        s = args(j, false, j == 0, &most);
+        if constexpr (W) {
+            for (int k = 0; k < 3; ++k)  // lists that the doubling took alone have nothing left
+                if (set[k].p && set[k].p->top == set[k].p->run) s.a[k].m = 0;
+        }
+        if (most <= IW_PER_MIN) hipLaunchKernelGGL((k_iwl_down<W, 1>), grid(most, TPB), b, 0, st, s, ctrl);
+        else hipLaunchKernelGGL((k_iwl_down<W, IW_PER>), grid(most, TPB * IW_PER), b, 0, st, s, ctrl);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 template <bool W>
@@ -3266,7 +3447,7 @@ static hipError_t run_marks(const RunArgs& a, const Plan& p, uint8_t* hp0, Ctrl*
     char* ws = a.ws;
     hipStream_t st = a.stream;
     const uint32_t n = (uint32_t)p.m[0];
-    const Gate mg{&ctrl->multi, 1u};  // plain path taken and more than one list
+    const Gate mg{&ctrl->multi, 1u << 1};  // plain path taken and more than one list
     uint32_t* fill1 = reinterpret_cast<uint32_t*>(ws + p.off_fill);
     uint32_t* fill2 = fill1 + 2 * (size_t)p.nb1 * FILL_LINE;
     LR_TRY(fill(fill1, fill_words(p.nb1, p.nb2) * 4, 0u, st, nullptr, mg));
@@ -3398,10 +3579,11 @@ static hipError_t run_guess(const RunArgs& a, const Plan& p, uint32_t thr) {
     return hipGetLastError();
 }
 
-// The plain path. With a.prologue the call starts here (validation, head
-// sum); otherwise the caller ran them and a.gate selects this path.
+// The plain path up to the level above its chases. With a.prologue the call
+// starts here (validation, head sum); otherwise the caller ran them and a.gate
+// selects this path. *done: nothing is left (no level is chased).
 template <bool W, int WT, class Out0>
-static hipError_t run_srs_t(const RunArgs& a, Out0 out0) {
+static hipError_t run_srs_up(const RunArgs& a, Out0 out0, bool* done) {
     using L = Lay<W>;
     const Plan& p = *a.plan;
     char* ws = a.ws;
@@ -3420,14 +3602,16 @@ static hipError_t run_srs_t(const RunArgs& a, Out0 out0) {
     if constexpr (std::is_same_v<Out0, OutBatch>) {
         if (batch_direct(p, a.validate)) {  // the requests were not copied together
             SrcBatch srcb{a.desc, a.bases, a.bhdr, n};
-            if (p.iw) LR_TRY((run_iw<W>(p, srcb, out0, n, true, ctrl, ws, st, dm_at(0), g)));
+            if (p.iw) LR_TRY((run_iw<W>(p, srcb, out0, n, ctrl, ws, st, dm_at(0), g)));
             else LR_TRY((launch_base<W>(srcb, out0, n, n, ctrl, st, dm_at(0), g)));
             for (int i = EV_DETECT; i < EV_COUNT; ++i) rec_ev(a, i);
+            *done = true;
             return hipSuccess;
         }
     }
     if (p.run == 0) {
-        if (p.iw) LR_TRY((run_iw<W>(p, src0, out0, n, true, ctrl, ws, st, dm_at(0), g)));
+        *done = true;
+        if (p.iw) LR_TRY((run_iw<W>(p, src0, out0, n, ctrl, ws, st, dm_at(0), g)));
         else LR_TRY((launch_base<W>(src0, out0, n, n, ctrl, st, dm_at(0), g)));
         for (int i = EV_DETECT; i < EV_COUNT; ++i) rec_ev(a, i);
         return hipSuccess;
@@ -3501,17 +3685,19 @@ static hipError_t run_srs_t(const RunArgs& a, Out0 out0) {
             LR_TRY((launch_chase<W, 0, 1>(p, (int)l, src, smp, ctrl, ws, st, dm_at(l), g)));
         }
     }
-    {
-        const uint32_t L_ = p.run;
-        const uint32_t mL = (uint32_t)p.m[L_];
-        auto* top = reinterpret_cast<typename L::Rec*>(ws + p.off_eb[L_ - 1]);
-        if (p.iw) {
-            LR_TRY((run_iw_level<W>(p, top, n, ctrl, ws, st, dm_at(L_), g)));
-        } else {
-            SrcLvl<W> src{top, mL};
-            LR_TRY((launch_base<W>(src, OutLvl<W>{top}, mL, n, ctrl, st, dm_at(L_), g)));
-        }
-    }
+    return hipSuccess;
+}
+
+// From the solved level down to the outputs.
+template <bool W, class Out0>
+static hipError_t run_srs_down(const RunArgs& a, Out0 out0) {
+    using L = Lay<W>;
+    const Plan& p = *a.plan;
+    char* ws = a.ws;
+    hipStream_t st = a.stream;
+    const Gate g = a.gate;
+    Ctrl* ctrl = reinterpret_cast<Ctrl*>(ws + p.off_ctrl);
+    auto dm_at = [&](uint32_t l) -> const uint32_t* { return a.dev_sizes ? &ctrl->dm[l] : nullptr; };
     for (int l = (int)p.run - 1; l >= 0; --l) {
         const uint32_t m = (uint32_t)p.m[l];
         const uint32_t S = (uint32_t)p.m[l + 1];
@@ -3542,11 +3728,11 @@ static hipError_t run_srs_t(const RunArgs& a, Out0 out0) {
     return hipSuccess;
 }
 
-// The ruling-set levels over a contracted list (records at lrec, sizes in
-// Ctrl.dm): on return lrec holds every contracted element's result.
+// The chased levels over a contracted list (records at lrec, sizes in
+// Ctrl.dm).
 template <bool W>
-static hipError_t run_clevels(const RunArgs& a, const Plan& p, typename Lay<W>::Rec* lrec, Ctrl* ctrl, Gate g,
-                              bool ev_chase0) {
+static hipError_t run_clevels_up(const RunArgs& a, const Plan& p, typename Lay<W>::Rec* lrec, Ctrl* ctrl, Gate g,
+                                 bool ev_chase0) {
     using L = Lay<W>;
     char* ws = a.ws;
     hipStream_t st = a.stream;
@@ -3584,17 +3770,31 @@ static hipError_t run_clevels(const RunArgs& a, const Plan& p, typename Lay<W>::
         }
         if (l == 0 && ev_chase0) rec_ev(a, EV_CHASE0);
     }
-    {
-        auto* top = Lv ? reinterpret_cast<typename L::Rec*>(ws + p.off_eb[Lv - 1]) : lrec;
-        const uint32_t climit = (uint32_t)(p.spawn ? p.sp_n : p.lc_n);
-        if (p.iw) {
-            LR_TRY((run_iw_level<W>(p, top, climit, ctrl, ws, st, &ctrl->dm[Lv], g)));
-        } else {
-            SrcLvl<W> src{top, (uint32_t)p.m[Lv]};
-            LR_TRY((launch_base<W>(src, OutLvl<W>{top}, (uint32_t)p.m[Lv], climit, ctrl, st, &ctrl->dm[Lv], g)));
-        }
-    }
-    for (int l = (int)Lv - 1; l >= 0; --l) {
+    return hipSuccess;
+}
+
+// The records of the level above the chased ones (lrec: the contracted list).
+template <bool W>
+static typename Lay<W>::Rec* top_records(const Plan& p, char* ws, typename Lay<W>::Rec* lrec) {
+    return p.run ? reinterpret_cast<typename Lay<W>::Rec*>(ws + p.off_eb[p.run - 1]) : lrec;
+}
+
+// That level by the base case (plans without independent walks).
+template <bool W>
+static hipError_t run_base_level(const Plan& p, typename Lay<W>::Rec* rec, uint32_t climit, Ctrl* ctrl,
+                                 hipStream_t st, const uint32_t* dm, Gate g) {
+    const uint32_t m = (uint32_t)p.m[p.run];
+    return launch_base<W>(SrcLvl<W>{rec, m}, OutLvl<W>{rec}, m, climit, ctrl, st, dm, g);
+}
+
+// From the solved level down: on return lrec holds every contracted element's
+// result.
+template <bool W>
+static hipError_t run_clevels_down(const RunArgs& a, const Plan& p, typename Lay<W>::Rec* lrec, Ctrl* ctrl, Gate g) {
+    using L = Lay<W>;
+    char* ws = a.ws;
+    hipStream_t st = a.stream;
+    for (int l = (int)p.run - 1; l >= 0; --l) {
         const uint32_t m = (uint32_t)p.m[l];
         const uint32_t S = (uint32_t)p.m[l + 1];
         const uint32_t* dm = &ctrl->dm[l];
@@ -3607,7 +3807,9 @@ static hipError_t run_clevels(const RunArgs& a, const Plan& p, typename Lay<W>::
                                : reinterpret_cast<typename L::Res*>(ws + p.off_eb[l - 1]);
         OutLvl<W> out{below};
         if (l == 0 && p.log0) {
-            LR_TRY((run_place<W, OutLvl<W>>(a, p, res, S, ctrl, out, true, dm)));
+            RunArgs b = a;
+            b.gate = g;
+            LR_TRY((run_place<W, OutLvl<W>>(b, p, res, S, ctrl, out, true, dm)));
         } else {
             hipLaunchKernelGGL((k_expand<W, OutLvl<W>>), dim3(grid_for(m, TPB * EXPAND_CH)), dim3(TPB), 0, st, slot,
                                m, res, S, ctrl, l, out, dm, g);
@@ -3617,20 +3819,33 @@ static hipError_t run_clevels(const RunArgs& a, const Plan& p, typename Lay<W>::
     return hipSuccess;
 }
 
-// Tile-local contraction, then the ruling-set levels on the contracted list
-// (sizes from the device), then every element from its chain start. The plan
-// sizes the levels for a contracted list of at most m[0] elements; lc_n is
-// the input's length.
-template <bool W, int WT, class Out0>
-static hipError_t run_local_t(const RunArgs& a, Out0 out0) {
+// Tile-local contraction and the chased levels on the contracted list (sizes
+// from the device). The plan sizes the levels for a contracted list of at most
+// m[0] elements; lc_n is the input's length. Where the plan chases a level and
+// the list turns out to have at most LOCAL_SMALL_MAX elements (a.splan), the
+// scan turns the path to MODE_LOCAL_SMALL: its levels are not chased, the list
+// itself goes to the independent walks.
+struct LocalGates {
+    Gate pre, levels, both;  // up to the scan; the chased levels; whatever the list's length
+};
+static LocalGates local_gates(const RunArgs& a, const Ctrl* ctrl) {
+    // alone (forced), the path's mode is set by the scan: the kernels up to it
+    // run ungated
+    const Gate pre = a.prologue ? Gate{} : a.gate;
+    if (!a.splan) return {pre, a.gate, a.gate};
+    return {pre, Gate{&ctrl->mode, mode_bit(MODE_LOCAL)},
+            Gate{&ctrl->mode, mode_bit(MODE_LOCAL) | mode_bit(MODE_LOCAL_SMALL)}};
+}
+
+template <bool W, int WT>
+static hipError_t run_local_up(const RunArgs& a) {
     using L = Lay<W>;
     const Plan& p = *a.plan;
     char* ws = a.ws;
     hipStream_t st = a.stream;
-    const Gate g = a.gate;
     Ctrl* ctrl = reinterpret_cast<Ctrl*>(ws + p.off_ctrl);
+    const LocalGates g = local_gates(a, ctrl);
     const uint32_t n = (uint32_t)p.lc_n;
-    const uint32_t Lv = p.run;
     if (a.prologue) {
         rec_ev(a, EV_START);
         if (a.validate) LR_TRY(run_validate(a, p, n));
@@ -3641,35 +3856,55 @@ static hipError_t run_local_t(const RunArgs& a, Out0 out0) {
     int64_t* wd = W ? reinterpret_cast<int64_t*>(ws + p.off_lc_wd) : nullptr;
     auto* lrec = reinterpret_cast<typename L::Rec*>(ws + p.off_lrec);
     auto* stage = reinterpret_cast<typename L::Rec*>(ws + p.off_lc_stage);
-    uint8_t* hp0 = Lv ? reinterpret_cast<uint8_t*>(ws + p.off_slot[0]) : nullptr;
+    uint8_t* hp0 = p.run ? reinterpret_cast<uint8_t*>(ws + p.off_slot[0]) : nullptr;
     const uint32_t gc = LR_LC_GRID_PER_CU ? std::min<uint32_t>(p.lc_ntiles, (uint32_t)device_cus() * LR_LC_GRID_PER_CU)
                                           : p.lc_ntiles;
-    // alone (forced), the path's mode is set by the scan: the kernels up to it
-    // run ungated
-    const Gate gpre = a.prologue ? Gate{} : g;
     hipLaunchKernelGGL((k_lc_chain<W, WT>), dim3(gc), dim3(LC_TPB), 0, st, a.succ, a.weight, n, p.lc_ntiles, cnt, dir,
-                       stage, pos, wd, ctrl, gpre);
+                       stage, pos, wd, ctrl, g.pre);
     LR_TRY(hipGetLastError());
-    LevelShifts ks{};
+    LevelShifts ks{}, kss{};
     for (uint32_t l = 0; l < p.levels; ++l) ks.lg[l] = (uint8_t)p.log2k[l];
+    uint32_t small = 0, slevels = 0;
+    if (a.splan) {
+        small = (uint32_t)a.splan->m[0];
+        slevels = a.splan->top;
+        for (uint32_t l = 0; l < slevels; ++l) kss.lg[l] = (uint8_t)a.splan->log2k[l];
+    }
     hipLaunchKernelGGL(k_lc_scan, dim3(1), dim3(1024), 0, st, cnt, p.lc_ntiles, ctrl, p.levels, ks, (uint32_t)p.m[0],
-                       (uint32_t)a.prologue, gpre);
+                       (uint32_t)a.prologue, small, slevels, kss, g.pre);
     LR_TRY(hipGetLastError());
     rec_ev(a, EV_DETECT);
     if (hp0) {
         hipLaunchKernelGGL(k_zero_dyn, dim3(grid_for(p.m[0] / 4 + 1, TPB * 4)), dim3(TPB), 0, st,
-                           reinterpret_cast<uint32_t*>(hp0), (const uint32_t*)&ctrl->dm[0], g);
+                           reinterpret_cast<uint32_t*>(hp0), (const uint32_t*)&ctrl->dm[0], g.levels);
         LR_TRY(hipGetLastError());
     }
     hipLaunchKernelGGL((k_lc_compact<W>), dim3(grid_for((uint64_t)p.lc_ntiles * 64, TPB)), dim3(TPB), 0, st, stage,
-                       cnt, dir, p.lc_ntiles, n, lrec, hp0, g);
+                       cnt, dir, p.lc_ntiles, n, lrec, hp0, g.both);
     LR_TRY(hipGetLastError());
     rec_ev(a, EV_HEADS);
-    LR_TRY(run_clevels<W>(a, p, lrec, ctrl, g, true));
+    return run_clevels_up<W>(a, p, lrec, ctrl, g.levels, true);
+}
+
+// Every element from its chain start.
+template <bool W, class Out0>
+static hipError_t run_local_down(const RunArgs& a, Out0 out0) {
+    using L = Lay<W>;
+    const Plan& p = *a.plan;
+    char* ws = a.ws;
+    hipStream_t st = a.stream;
+    Ctrl* ctrl = reinterpret_cast<Ctrl*>(ws + p.off_ctrl);
+    const LocalGates g = local_gates(a, ctrl);
+    const uint32_t n = (uint32_t)p.lc_n;
+    auto* lrec = reinterpret_cast<typename L::Rec*>(ws + p.off_lrec);
+    LR_TRY(run_clevels_down<W>(a, p, lrec, ctrl, g.levels));
     rec_ev(a, EV_UPPER);
     rec_ev(a, EV_PART);
-    hipLaunchKernelGGL((k_lc_expand<W, Out0>), dim3(grid_for(n, TPB * EXPAND_CH)), dim3(TPB), 0, st, pos, wd, cnt,
-                       reinterpret_cast<const typename L::Res*>(lrec), n, ctrl, out0, g);
+    hipLaunchKernelGGL((k_lc_expand<W, Out0>), dim3(grid_for(n, TPB * EXPAND_CH)), dim3(TPB), 0, a.stream,
+                       reinterpret_cast<const uint32_t*>(ws + p.off_lc_pos),
+                       W ? reinterpret_cast<const int64_t*>(ws + p.off_lc_wd) : nullptr,
+                       reinterpret_cast<const uint32_t*>(ws + p.off_lc_cnt),
+                       reinterpret_cast<const typename L::Res*>(lrec), n, ctrl, out0, g.both);
     LR_TRY(hipGetLastError());
     rec_ev(a, EV_EXPAND);
     return hipSuccess;
@@ -3764,7 +3999,14 @@ static hipError_t run_spawn_t(const RunArgs& a, Out0 out0) {
     hipLaunchKernelGGL(k_sp_publish, dim3(1), dim3(64), 0, st, ctrl, S0, (uint32_t)p.m[0], p.levels, ks, g);
     LR_TRY(hipGetLastError());
     rec_ev(a, EV_CHASE0);
-    LR_TRY(run_clevels<W>(a, p, lrec, ctrl, g, false));
+    LR_TRY(run_clevels_up<W>(a, p, lrec, ctrl, g, false));
+    if (p.iw) {
+        IwSet<W> set[3] = {{&p, top_records<W>(p, ws, lrec), &ctrl->dm[Lv]}, {}, {}};
+        LR_TRY(run_iw_levels<W>(set, nullptr, n, ctrl, ws, st));
+    } else {
+        LR_TRY(run_base_level<W>(p, top_records<W>(p, ws, lrec), n, ctrl, st, &ctrl->dm[Lv], g));
+    }
+    LR_TRY(run_clevels_down<W>(a, p, lrec, ctrl, g));
     rec_ev(a, EV_UPPER);
     rec_ev(a, EV_PART);
     hipLaunchKernelGGL((k_sp_expand<W, Out0>), dim3(grid_for(n, TPB * EXPAND_CH)), dim3(TPB), 0, st, slot, n,
@@ -3781,23 +4023,69 @@ static hipError_t run_spawn_t(const RunArgs& a, Out0 out0) {
 // kernel at once (no host synchronisation, so the call stays capturable).
 template <bool W, int WT, class Out0>
 static hipError_t run_path_t(const RunArgs& a, Out0 out0) {
+    using L = Lay<W>;
     if (a.plan->spawn) return run_spawn_t<W, WT>(a, out0);
-    if (!a.lplan) return a.plan->local ? run_local_t<W, WT>(a, out0) : run_srs_t<W, WT>(a, out0);
+    char* ws = a.ws;
+    hipStream_t st = a.stream;
+    Ctrl* ctrl = reinterpret_cast<Ctrl*>(ws + a.plan->off_ctrl);
+    auto lrec_of = [&](const Plan& p) { return reinterpret_cast<typename L::Rec*>(ws + p.off_lrec); };
+    // the contracted list's sets of the independent walks
+    auto local_sets = [&](const RunArgs& la, IwSet<W>* set) {
+        const Plan& q = *la.plan;
+        if (q.iw) set[1] = {&q, top_records<W>(q, ws, lrec_of(q)), &ctrl->dm[q.run]};
+        if (la.splan) set[2] = {la.splan, lrec_of(q), &ctrl->dms[0]};
+    };
+    IwSet<W> set[3];
+    if (!a.lplan && a.plan->local) {
+        const Plan& q = *a.plan;
+        LR_TRY((run_local_up<W, WT>(a)));
+        local_sets(a, set);
+        if (!q.iw)
+            LR_TRY(run_base_level<W>(q, top_records<W>(q, ws, lrec_of(q)), (uint32_t)q.lc_n, ctrl, st, &ctrl->dm[q.run],
+                                     a.gate));
+        if (q.iw) LR_TRY(run_iw_levels<W>(set, &ctrl->mode, (uint32_t)q.lc_n, ctrl, ws, st));
+        return run_local_down<W>(a, out0);
+    }
     const Plan& p = *a.plan;
-    Ctrl* ctrl = reinterpret_cast<Ctrl*>(a.ws + p.off_ctrl);
+    const uint32_t n = (uint32_t)p.m[0];
+    const uint32_t* dm = a.dev_sizes ? &ctrl->dm[p.run] : nullptr;
+    if (!a.lplan) {
+        bool done = false;
+        LR_TRY((run_srs_up<W, WT>(a, out0, &done)));
+        if (done) return hipSuccess;
+        auto* top = top_records<W>(p, ws, nullptr);
+        if (p.iw) {
+            set[0] = {&p, top, dm};
+            LR_TRY(run_iw_levels<W>(set, nullptr, n, ctrl, ws, st));
+        } else {
+            LR_TRY(run_base_level<W>(p, top, n, ctrl, st, dm, a.gate));
+        }
+        return run_srs_down<W>(a, out0);
+    }
     rec_ev(a, EV_START);
-    if (a.validate) LR_TRY(run_validate(a, p, (uint32_t)p.m[0]));
+    if (a.validate) LR_TRY(run_validate(a, p, n));
     LR_TRY(run_guess(a, p, (uint32_t)local_guess_cap(p.m[0])));
     RunArgs la = a;
     la.plan = a.lplan;
     la.prologue = false;
-    la.gate = Gate{&ctrl->mode, MODE_LOCAL};
-    LR_TRY((run_local_t<W, WT>(la, out0)));  // its scan falls back to mode 0 if the list is too long
+    la.gate = Gate{&ctrl->mode, mode_bit(MODE_LOCAL)};
+    LR_TRY((run_local_up<W, WT>(la)));  // its scan falls back to mode 0 if the list is too long
     RunArgs pa = a;
     pa.prologue = false;
-    pa.gate = Gate{&ctrl->mode, MODE_PLAIN};
+    pa.gate = Gate{&ctrl->mode, mode_bit(MODE_PLAIN)};
     LR_TRY(a.desc ? run_batch_heads(pa, p, pa.gate) : run_headsum(pa, p, pa.gate));
-    return run_srs_t<W, WT>(pa, out0);
+    bool done = false;  // (an input of this size has a chased level)
+    LR_TRY((run_srs_up<W, WT>(pa, out0, &done)));
+    // both paths' lists share the launches of the independent walks
+    const Plan& q = *la.plan;
+    local_sets(la, set);
+    if (p.iw) set[0] = {&p, top_records<W>(p, ws, nullptr), dm};
+    if (!q.iw)
+        LR_TRY(run_base_level<W>(q, top_records<W>(q, ws, lrec_of(q)), n, ctrl, st, &ctrl->dm[q.run], la.gate));
+    if (!p.iw) LR_TRY(run_base_level<W>(p, top_records<W>(p, ws, nullptr), n, ctrl, st, dm, pa.gate));
+    if (p.iw || q.iw) LR_TRY(run_iw_levels<W>(set, &ctrl->mode, n, ctrl, ws, st));
+    LR_TRY((run_local_down<W>(la, out0)));
+    return run_srs_down<W>(pa, out0);
 }
 
 // The bounded fallback over the input (see k_fb_round); every kernel returns
@@ -3810,7 +4098,7 @@ static hipError_t run_fallback_t(const RunArgs& a, Out0 out0) {
     Ctrl* ctrl = reinterpret_cast<Ctrl*>(a.ws + p.off_ctrl);
     const uint64_t n64 = p.spawn ? p.sp_n : (p.local ? p.lc_n : p.m[0]);
     const uint32_t n = (uint32_t)n64;
-    const Gate g{&ctrl->mode, MODE_FALLBACK};
+    const Gate g{&ctrl->mode, mode_bit(MODE_FALLBACK)};
     auto* A = reinterpret_cast<typename L::Rec*>(a.ws + p.off_fb);
     auto* B = reinterpret_cast<typename L::Rec*>(a.ws + p.off_fb + (n64 * sizeof(typename L::Rec) + 16 + ALIGN - 1) /
                                                                      ALIGN * ALIGN);

@@ -16,6 +16,7 @@ enum { EV_START, EV_DETECT, EV_HEADS, EV_CHASE0, EV_UPPER, EV_PART, EV_EXPAND, E
 struct RunArgs {
     const Plan* plan = nullptr;
     const Plan* lplan = nullptr;      // automatic contraction: the contracted path's plan (same workspace)
+    const Plan* splan = nullptr;      // contracted lists that are short enough not to be chased (or null)
     const uint32_t* succ = nullptr;   // level-0 successor array (user's, or the batch concatenation)
     const void* weight = nullptr;
     int wt = 0;                       // 0: unit links, 1: int32, 2: int64

@@ -152,3 +152,38 @@ def test_batch_graph_sizes_from_the_device(cap):
         inputs = [make("forest" if (i + k) % 3 == 2 and n > 100 else "random", n, 31 * k + i) for i, n in enumerate(sizes)]
         run_batch(inputs, g.launch)
     g.close()
+
+
+def local_forest(n, seed, gamma):
+    """Lists stored mostly in id order: the identity order with a share gamma
+    of its positions permuted, cut into lists at random."""
+    order = workloads.gamma_order(n, gamma, seed)
+    rng = np.random.default_rng(seed)
+    ends = rng.random(n) < 1e-4
+    ends[-1] = True
+    succ = np.empty(n, np.uint32)
+    succ[order] = np.where(ends, order, np.roll(order, -1))
+    return succ
+
+
+# contracted lists that are not chased (short), that are, and one handed back
+# to the plain path; around the sizes where the contracted plan gains a level
+@pytest.mark.parametrize("n,gamma", [((1 << 21) + 9, 0.01), (6_710_000, 0.1), (6_720_000, 0.1), (7_000_001, 0.001),
+                                     (1 << 24, 0.05), ((1 << 24) + 3, 0.1), (30_000_001, 0.002), (30_000_001, 0.1)])
+@pytest.mark.parametrize("weighted", [False, True])
+def test_contracted_lists(n, gamma, weighted):
+    if weighted and n > (1 << 24):
+        n = (1 << 24) + 3
+    print(f"case: contracted lists n={n} gamma={gamma} weighted={weighted}", flush=True)
+    succ = local_forest(n, n % 83, gamma)
+    w = workloads.weights(n, seed=4, stream=2, lo=-(1 << 30), hi=1 << 30) if weighted else None
+    check(succ, w)
+    check(succ, w, opts=lr.make_opts(flags=lr.LR_LOCAL))
+
+
+def test_contracted_path_on_a_list_that_is_too_long():
+    """Forced contraction of a random list: nothing contracts, the list has as
+    many elements as the input and its levels are chased."""
+    n = (1 << 22) + 1
+    print("case: contracted random list", flush=True)
+    check(make("random", n, 5), opts=lr.make_opts(flags=lr.LR_LOCAL))
