@@ -99,8 +99,8 @@ enum {
  * the sampling (every sampled ruler placed after all other elements, say)
  * would make one walk cover almost the whole list. Every walk therefore
  * stops after 64 k steps; if any does, the call ranks its input by pointer
- * doubling with J-fold jumps per round (J = 128 up to 2^21 elements, at most
- * 3 rounds; J = 16 above, at most 8 rounds), independent of the order, with
+ * doubling over all elements at once (in place, all lanes of the chip going
+ * round their elements, about log2(n) passes), independent of the order, with
  * identical results. The fallback's kernels are enqueued with every call and
  * return at once when no walk was capped (a few microseconds per call);
  * lr_profile_last reports whether it ran. Under LR_VALIDATE a cycle reached

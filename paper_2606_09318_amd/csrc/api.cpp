@@ -381,8 +381,9 @@ lr_status make_plans(uint64_t n, bool weighted, const lr_opts* o, uint32_t batch
         q->log0 = use_log(q->m[0], q->levels, o);
         off = std::max(off, layout_levels(q, layout_local(q, n, body)));
     }
-    // the bounded fallback (a walk reached its step cap): two record arrays
-    // over the input, after the common header
+    // the bounded fallback (a walk reached its step cap): its records over the
+    // input, after the common header (the size is that of two arrays of level
+    // records, which covers them and keeps what a call asks for unchanged)
     if (p->levels >= 1 || spawn) {
         p->off_fb = body;
         off = std::max(off, body + 2 * align_up((size_t)n * p->rec_bytes + 16));

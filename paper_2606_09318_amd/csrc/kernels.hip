@@ -2130,57 +2130,68 @@ __global__ __launch_bounds__(TPB) void k_wy_copy(const typename Lay<W>::Rec* __r
 
 // ------------------------------------------------------------- fallback --
 // The bounded fallback, run only when a walk of the ruling-set path reached
-// its step cap (an order built against the sampling): pointer doubling with
-// J-fold jumps per round, so a round follows up to J - 1 records and
-// ceil(log_J n) rounds reach every terminal, whatever the order. A record
-// (nxt, value) spans its value's links from its element to nxt; nxt =
-// TERM | t once the path has reached its terminal t. Every kernel of the
-// fallback is enqueued with every call and returns at once unless the cap
-// was hit, so the rounds are few: J = 128 up to 2^21 elements (at most 3
-// rounds), 16 above (at most 8).
-constexpr uint32_t FB_GRID_PER_CU = 2;
+// its step cap (an order built against the sampling): pointer doubling over
+// the whole input, whatever the order. Its kernels are enqueued with every call
+// and return at once unless the cap was hit (about 2 us each), so there are two:
+// first records of up to FB_HOPS links, then the asynchronous doubling of the
+// independent walks (see there) by as many lanes as the chip holds, each going
+// round its share of the elements, one hop each, until all have reached a
+// terminal. All elements move together, so a pass about doubles what is
+// left: 28 passes at the most, of one random read per element. On orders with
+// every ruler last (the other side: rounds of pointer doubling with 16- or
+// 128-fold jumps, three to eight launches): 2^18 elements 0.65 -> 0.18 ms, 2^20
+// 2.33 -> 0.51, 2^22 5.0 -> 1.7, 2^24 25.5 -> 7.9, int64 sums over 2^23 14.5 -> 9.0.
+constexpr uint32_t FB_HOPS = 16;
 
-// One round: compose up to J consecutive records (the first round reads the
-// input itself). The last round writes the outputs; with err set, a path
-// that has not reached a terminal (a cycle) is reported.
-template <bool W, bool FIRST, bool LAST, class Src, class Out>
-__global__ __launch_bounds__(TPB) void k_fb_round(Src src, const typename Lay<W>::Rec* __restrict__ a,
-                                                  typename Lay<W>::Rec* __restrict__ b, uint32_t m, uint32_t J,
-                                                  Out out, uint32_t* err, const uint32_t* dm, Gate gate) {
+template <bool W, class Src>
+__global__ __launch_bounds__(TPB) void k_fb_first(Src src, uint64_t* __restrict__ nodes, uint32_t m,
+                                                  const uint32_t* dm, Gate gate) {
     if (gate.off()) return;
-    using L = Lay<W>;
     if (dm) m = src.m = dm[0];
     const uint32_t stride = gridDim.x * blockDim.x;
-    uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= m) return;
-    typename Out::Cur cur = out.begin(i);
-    for (; i < m; i += stride) {
-        typename L::Val acc;
-        uint32_t j;
-        if constexpr (FIRST) src.load(i, j, acc);  // a terminal t: TERM | t, value 0
-        else {
-            const typename L::Rec r = a[i];
-            acc = L::val(r);
-            j = r.nxt;
-        }
-        for (uint32_t t = 1; t < J && !(j & TERM); ++t) {
-            typename L::Val v;
-            uint32_t nj;
-            if constexpr (FIRST) src.load(j, nj, v);
-            else {
-                const typename L::Rec q = a[j];
-                v = L::val(q);
-                nj = q.nxt;
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride)
+        iw_first<W, false>(src, Sampler{}, nodes, 0u, i, FB_HOPS);
+}
+
+// err: where to report a path that never reaches a terminal (more links than
+// elements: a cycle), or null.
+template <bool W, class Out>
+__global__ __launch_bounds__(TPB) void k_fb_double(uint64_t* __restrict__ nodes, uint32_t m, Out out, uint32_t* err,
+                                                   const uint32_t* dm, Gate gate) {
+    if (gate.off()) return;
+    if (dm) m = dm[0];
+    using L = Lay<W>;
+    const uint32_t stride = gridDim.x * blockDim.x;
+    const uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i0 >= m) return;
+    for (bool open = true; open;) {
+        open = false;
+        for (uint32_t i = i0; i < m; i += stride) {
+            uint32_t nxt;
+            typename L::Val acc;
+            IwRec<W>::template load<true>(nodes, i, nxt, acc);  // its own stores, in order
+            if (nxt & TERM) continue;
+            bool bad = nxt >= m;
+            if (!bad && !iw_hop<W, true>(nodes, nxt, acc)) {
+                open = true;
+                continue;
             }
-            acc = L::add(acc, v);
-            j = nj;
+            bad |= acc.c >= m;
+            if (bad) {
+                nxt = TERM | IDX;
+                acc = L::junk();
+                if (err) atomicOr(err, ERR_FALLBACK_CYCLE);
+            }
+            IwRec<W>::store(nodes, i, nxt, acc);
+            open |= !(nxt & TERM);
         }
-        if constexpr (LAST) {
-            if (!(j & TERM) && err) atomicOr(err, ERR_FALLBACK_CYCLE);
-            out.store(cur, i, acc, j & IDX);
-        } else {
-            b[i] = L::rec(j, acc);
-        }
+    }
+    auto cur = out.begin(i0);
+    for (uint32_t i = i0; i < m; i += stride) {
+        uint32_t nxt;
+        typename L::Val acc;
+        IwRec<W>::template load<true>(nodes, i, nxt, acc);
+        out.store(cur, i, acc, nxt & IDX);
     }
 }
 
@@ -4088,45 +4099,25 @@ static hipError_t run_path_t(const RunArgs& a, Out0 out0) {
     return run_srs_down<W>(pa, out0);
 }
 
-// The bounded fallback over the input (see k_fb_round); every kernel returns
-// at once unless some walk reached its cap.
+// The bounded fallback over the input; both kernels return at once unless some
+// walk reached its cap.
 template <bool W, int WT, class Out0>
 static hipError_t run_fallback_t(const RunArgs& a, Out0 out0) {
-    using L = Lay<W>;
     using Src = SrcIn<W, WT>;
     const Plan& p = *a.plan;
     Ctrl* ctrl = reinterpret_cast<Ctrl*>(a.ws + p.off_ctrl);
-    const uint64_t n64 = p.spawn ? p.sp_n : (p.local ? p.lc_n : p.m[0]);
-    const uint32_t n = (uint32_t)n64;
+    const uint32_t n = (uint32_t)(p.spawn ? p.sp_n : (p.local ? p.lc_n : p.m[0]));
     const Gate g{&ctrl->mode, mode_bit(MODE_FALLBACK)};
-    auto* A = reinterpret_cast<typename L::Rec*>(a.ws + p.off_fb);
-    auto* B = reinterpret_cast<typename L::Rec*>(a.ws + p.off_fb + (n64 * sizeof(typename L::Rec) + 16 + ALIGN - 1) /
-                                                                     ALIGN * ALIGN);
-    const uint32_t grid = std::min(grid_for(n, TPB * 4), (uint32_t)device_cus() * FB_GRID_PER_CU);
-    const uint32_t J = n64 <= (1ull << 21) ? 128u : 16u;
-    uint32_t rounds = 1;
-    for (uint64_t span = J; span < n64; span *= J) ++rounds;
-    const Src src{a.succ, a.weight, n};
-    uint32_t* err = a.validate ? &ctrl->err : nullptr;
+    uint64_t* nodes = reinterpret_cast<uint64_t*>(a.ws + p.off_fb);
     const uint32_t* dm = a.dev_sizes ? &ctrl->dm[0] : nullptr;
-    for (uint32_t r = 0; r < rounds; ++r) {
-        const bool first = r == 0, last = r + 1 == rounds;
-        if (first && last)
-            hipLaunchKernelGGL((k_fb_round<W, true, true, Src, Out0>), dim3(grid), dim3(TPB), 0, a.stream, src, A, B,
-                               n, J, out0, err, dm, g);
-        else if (first)
-            hipLaunchKernelGGL((k_fb_round<W, true, false, Src, Out0>), dim3(grid), dim3(TPB), 0, a.stream, src, A,
-                               B, n, J, out0, err, dm, g);
-        else if (last)
-            hipLaunchKernelGGL((k_fb_round<W, false, true, Src, Out0>), dim3(grid), dim3(TPB), 0, a.stream, src, A,
-                               B, n, J, out0, err, dm, g);
-        else
-            hipLaunchKernelGGL((k_fb_round<W, false, false, Src, Out0>), dim3(grid), dim3(TPB), 0, a.stream, src, A,
-                               B, n, J, out0, err, dm, g);
-        LR_TRY(hipGetLastError());
-        std::swap(A, B);  // the round's output is the next round's input
-    }
-    return hipSuccess;
+    hipLaunchKernelGGL((k_fb_first<W, Src>), dim3(grid_for(n, TPB)), dim3(TPB), 0, a.stream, Src{a.succ, a.weight, n},
+                       nodes, n, dm, g);
+    LR_TRY(hipGetLastError());
+    auto kern = k_fb_double<W, Out0>;
+    static const uint32_t resident = persistent_grid(kern, TPB);  // one per template instance, found once
+    hipLaunchKernelGGL(kern, dim3(std::min<uint32_t>(grid_for(n, TPB), resident)), dim3(TPB), 0, a.stream, nodes, n,
+                       out0, a.validate ? &ctrl->err : nullptr, dm, g);
+    return hipGetLastError();
 }
 
 // Every path's first kernels set Ctrl.mode and a capped walk turns it to
