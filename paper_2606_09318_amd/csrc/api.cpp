@@ -35,10 +35,14 @@ static uint32_t ilog2(uint32_t k) {
 // inputs; upper levels are cache resident and use short walks to keep the
 // longest walk (about k ln(m/k) steps) short. Inputs below 2^25 elements are
 // bound by that longest walk on every level (each step a dependent load), so
-// they take shorter walks: 8 on the first level below 2^23 elements, 16 up to
-// 2^24, 32 beyond; above the first level 4 below 2^17 elements, 8 up to 2^20,
-// 16 beyond (measured per size on MI355X: 6-18 % faster from 2^17 to 2^23;
-// from 2^25 on the longer walks stay ahead). From 2^25 the first level takes
+// they take shorter walks: 8 on the first level below 3 * 2^21 elements, 16 up
+// to 3 * 2^22, 32 beyond; above the first level 4 below 2^17 elements, 8 up to
+// 2^20, 16 beyond (measured per size on MI355X: 6-18 % faster from 2^17 to 2^22;
+// from 2^25 on the longer walks stay ahead). Where the first level's lines lie,
+// us a call, rank alone of a random list / rank and root of a forest:
+//   8 -> 16:  5 M 310 -> 317 / 359 -> 363;  7 M 428 -> 403 / 509 -> 477
+//   16 -> 32: 9 M 485 -> 538 / 593 -> 591; 12 M 622 -> 605 / 781 -> 740;
+//     16 M 823 -> 759 / 1019 -> 980 From 2^25 the first level takes
 // 32 up to 3 * 2^26 elements and 64 beyond (32 is 7 % faster at 2^26 and
 // 2 % at 2^27, 64 is 2 % faster at 2^28); weighted inputs (16 B records)
 // take 64 from 2^27 (32 is 2-6 % faster at 2^26, 2 % slower on a 2^27
@@ -49,7 +53,7 @@ static uint32_t default_spacing(uint32_t l, uint64_t m, uint32_t base_max, bool 
                                 bool capped) {
     uint32_t k;
     if (short_walks) {
-        if (l == 0) k = (m >= (1ull << 24)) ? 32 : (m >= (1ull << 23)) ? 16 : 8;
+        if (l == 0) k = (m >= (3ull << 22)) ? 32 : (m >= (3ull << 21)) ? 16 : 8;
         else k = (m >= (1ull << 20)) ? 16 : (m >= (1ull << 17)) ? 8 : 4;
     } else {
         const uint64_t k64 = capped ? (1ull << 26) : weighted ? (1ull << 27) : (3ull << 26);
