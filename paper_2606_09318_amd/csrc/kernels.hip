@@ -1552,11 +1552,10 @@ struct PlaceArrays {
 template <bool W, bool ROOT>
 constexpr int place_per() { return (int)place_tile_records(W, ROOT) / place_tpb(W, ROOT); }
 
-// LDS bytes of one grouping tile over nb ranges (device and host agree);
-// without values only the element ids are grouped.
-__host__ __device__ constexpr size_t place_lds_bytes(bool weighted, bool root, uint32_t nb, bool vals = true) {
+// LDS bytes of one grouping tile over nb ranges (device and host agree).
+__host__ __device__ constexpr size_t place_lds_bytes(bool weighted, bool root, uint32_t nb) {
     const size_t T = place_tile_records(weighted, root);
-    size_t o = 8 * (size_t)nb + (vals ? (root ? 12 : 8) : 4) * T;
+    size_t o = 8 * (size_t)nb + (root ? 12 : 8) * T;
     if (weighted) o = ((o + 7) & ~(size_t)7) + 8 * T;
     return o;
 }
@@ -1772,7 +1771,7 @@ __global__ __launch_bounds__(place_tpb(W, ROOT)) void k_place1(LogArrays<W> lg, 
 // coarse range is full, and its front and back counts must add up to its
 // length; VALS = false groups element ids only: then a coarse range need not
 // be full and its records are its front and back segments.
-template <bool W, bool ROOT, bool VALS = true>
+template <bool W, bool ROOT>
 __global__ __launch_bounds__(place_tpb(W, ROOT)) void k_place2(PlaceArrays<W> in, Ctrl* ctrl, uint32_t n, uint32_t s1, uint32_t s2,
                                                 uint32_t* __restrict__ fill2, PlaceArrays<W> out, const uint32_t* dm,
                                                 const uint32_t* __restrict__ fill1, Gate gate) {
@@ -1807,29 +1806,16 @@ __global__ __launch_bounds__(place_tpb(W, ROOT)) void k_place2(PlaceArrays<W> in
     uint32_t nx[PER], nr[PER], nt[PER];
     int64_t ns[PER];
     auto load_tile = [&](uint32_t tile) {
-        const uint32_t c = (tile * T) >> s1;
-        const uint32_t lo = c << s1;
-        const uint32_t len = min(1u << s1, n - lo);
-        uint32_t front = len, back_at = len;  // records at [lo, lo + front) and [lo + back_at, lo + len)
-        if constexpr (!VALS) {
-            front = fill1[2 * c * FILL_LINE];
-            const uint32_t back = fill1[(2 * c + 1) * FILL_LINE];
-            back_at = back < len ? len - back : 0u;
-        }
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
             const uint32_t i = tile * T + j * TPB_ + threadIdx.x;
             nx[j] = NONE;
-            if (i < n && (i - lo < front || i - lo >= back_at)) {
-                if constexpr (VALS) {
-                    const uint2 e = in.xr[i];
-                    nx[j] = e.x;
-                    nr[j] = e.y;
-                    if constexpr (ROOT) nt[j] = in.t[i];
-                    if constexpr (W) ns[j] = in.s[i];
-                } else {
-                    nx[j] = in.x[i];
-                }
+            if (i < n) {
+                const uint2 e = in.xr[i];
+                nx[j] = e.x;
+                nr[j] = e.y;
+                if constexpr (ROOT) nt[j] = in.t[i];
+                if constexpr (W) ns[j] = in.s[i];
             }
         }
     };
@@ -1838,22 +1824,20 @@ __global__ __launch_bounds__(place_tpb(W, ROOT)) void k_place2(PlaceArrays<W> in
     while (tile != NONE) {
         const uint32_t c = (tile * T) >> s1;  // coarse range of this tile (T divides 2^s1)
         if (threadIdx.x == 0 && tile % tpc == 0) {
-            // the range's two sides met exactly (more records than ids: some
-            // element was visited twice, or a target has two links)
+            // the range's two sides met exactly (otherwise some element was
+            // visited twice or not at all)
             const uint32_t len = min(1u << s1, n - (c << s1));
             const uint64_t got = (uint64_t)fill1[2 * c * FILL_LINE] + fill1[(2 * c + 1) * FILL_LINE];
-            if (VALS ? got != len : got > len) atomicOr(&ctrl->err, 64u);
+            if (got != len) atomicOr(&ctrl->err, 64u);
         }
         uint32_t xs[PER], rs[PER], ts[PER], bs[PER];
         int64_t ss[PER];
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
             xs[j] = nx[j];
-            if constexpr (VALS) {
-                rs[j] = nr[j];
-                if constexpr (ROOT) ts[j] = nt[j];
-                if constexpr (W) ss[j] = ns[j];
-            }
+            rs[j] = nr[j];
+            if constexpr (ROOT) ts[j] = nt[j];
+            if constexpr (W) ss[j] = ns[j];
         }
         q += step;
         const uint32_t nxt_tile = next_tile();
@@ -1866,7 +1850,7 @@ __global__ __launch_bounds__(place_tpb(W, ROOT)) void k_place2(PlaceArrays<W> in
             }
             if (xs[j] < n) bs[j] = (xs[j] >> s2) - c * fan;
         }
-        place_tile<W, ROOT, PER, VALS>(xs, rs, ts, ss, bs, fan, s2, c * fan, n, fill2, out, ctrl, lds);
+        place_tile<W, ROOT, PER>(xs, rs, ts, ss, bs, fan, s2, c * fan, n, fill2, out, ctrl, lds);
         tile = nxt_tile;
     }
 }
@@ -1958,20 +1942,25 @@ __global__ __launch_bounds__(TPB) void k_pair(const uint32_t* __restrict__ succ,
 
 // ------------------------------------------------- predecessor marks ----
 // Level 0 in log mode with more than one list: instead of one random byte
-// store per link, the link targets are grouped by element range with the
-// placement passes (ids only) and each range of 2^s2 ids writes its marks
-// from LDS in order. Every id is the target of at most one link, so no range
-// receives more targets than it has ids.
+// store per link, the link targets are grouped by element range with the first
+// placement pass (ids only) and written range by range from LDS. Every id is the
+// target of at most one link, so no range receives more targets than it has ids.
+constexpr int MARK_TPB = 1024;
+// ids a lane holds in the grouping: a tile's run in a group is 32 ids on average
+// at 512 groups (2^27 ids: 16 a lane 522 us, 32 360)
+constexpr int MARK_PER = 32;
+constexpr uint32_t MARK_TILE = MARK_PER * place_tpb(false, false);
+static_assert(8 * PLACE_MAX_RANGES + 4 * MARK_TILE <= LDS_MAX, "a tile of targets fits one workgroup's LDS");
 // TGT: the input is a plain list of nin target ids (those not below n are
 // skipped) instead of a successor array of n entries.
-template <bool VEC, bool TGT = false>
+template <bool TGT>
 __global__ __launch_bounds__(place_tpb(false, false)) void k_mark1(const uint32_t* __restrict__ succ, uint32_t n, uint32_t s1,
                                                             uint32_t nb1, uint32_t* __restrict__ fill1,
                                                             PlaceArrays<false> out, Ctrl* ctrl, Gate gate,
                                                             const uint32_t* dm, uint32_t nin = 0) {
     if (gate.off()) return;
     extern __shared__ __align__(16) unsigned char lds[];
-    constexpr int PER = place_per<false, false>();
+    constexpr int PER = MARK_PER;
     constexpr int TPB_ = place_tpb(false, false);
     constexpr uint32_t T = PER * TPB_;
     if (dm) n = dm[0];
@@ -2004,86 +1993,88 @@ __global__ __launch_bounds__(place_tpb(false, false)) void k_mark1(const uint32_
     }
 }
 
-// One workgroup per fine range: the range's targets set bytes in LDS, then
-// the range's marks are written in order (all n bytes get written).
-__global__ __launch_bounds__(place_tpb(false, false)) void k_mark3(const uint32_t* __restrict__ tx, uint32_t n, uint32_t s2,
-                                                            uint32_t nb2, const uint32_t* __restrict__ fill2,
-                                                            uint8_t* __restrict__ hp, Gate gate,
-                                                            const uint32_t* dm) {
+// One workgroup per group of 2^s1 ids: its targets (fill1 holds how many lie at
+// the group's two ends) set bits in LDS, which are then written in order as bytes
+// (hp, all n) or, with DIR, as a bitmap with running counts: word w of `dir` holds
+// the bits of ids [32 w, 32 w + 32) and the marked ids before them in their range
+// of 2^PLACE_FINE_SHIFT ids; cnt[f] is that range's count. With a bit per id a
+// group is 2^18 ids in 32 KB, so one grouping pass is enough. Bound by the LDS
+// atomics: two workgroups a CU take 192 us for 2^27 ids, one (groups of 2^19) 301;
+// loading ahead gains nothing. A second grouping pass (375 us) and byte marks of
+// 8192 ids a workgroup (155) took the place of it: a 2^27 forest 6.28 -> 6.11 ms,
+// int64 sums over it 9.47 -> 9.36, 9 * 10^7 4.39 -> 4.28, a 2^26-vertex tree 8.97 -> 8.71.
+template <bool DIR>
+__global__ __launch_bounds__(MARK_TPB) void k_mark_bits(const uint32_t* __restrict__ tx, uint32_t n, uint32_t s1,
+                                                        uint32_t nb1, const uint32_t* __restrict__ fill1,
+                                                        uint8_t* __restrict__ hp, uint2* __restrict__ dir,
+                                                        uint32_t* __restrict__ cnt, Ctrl* ctrl, Gate gate,
+                                                        const uint32_t* dm) {
     if (gate.off()) return;
     extern __shared__ __align__(16) unsigned char lds[];
-    uint32_t* mk = reinterpret_cast<uint32_t*>(lds);
-    constexpr int TPB_ = place_tpb(false, false);
-    const uint32_t R = 1u << s2;
+    __shared__ uint32_t sh[MARK_TPB / 64];
+    uint32_t* bits = reinterpret_cast<uint32_t*>(lds);
     if (dm) n = dm[0];
-    for (uint32_t f = blockIdx.x; f < nb2; f += gridDim.x) {
-        const uint32_t base = f << s2;
-        if (base >= n) break;  // device-side size: the ranges past it hold no ids
-        const uint32_t len = min(R, n - base);
-        for (uint32_t i = threadIdx.x; i < R / 4; i += TPB_) mk[i] = 0;
+    const uint32_t t = threadIdx.x;
+    for (uint32_t g = blockIdx.x; g < nb1; g += gridDim.x) {
+        const uint32_t lo = g << s1;
+        if (lo >= n) break;  // device-side size: the groups past it hold no ids
+        const uint32_t len = min(1u << s1, n - lo);
+        const uint32_t words = (len + 31) / 32;
+        for (uint32_t i = t; i < words; i += MARK_TPB) bits[i] = 0;
+        const uint32_t f0 = fill1[2 * g * FILL_LINE], f1 = fill1[(2 * g + 1) * FILL_LINE];
+        if (t == 0 && (uint64_t)f0 + f1 > len) atomicOr(&ctrl->err, 64u);  // a target has two links
+        const uint32_t front = min(f0, len), c = front + min(f1, len - front);
+        const uint32_t gap = len - c;  // between the two ends
         __syncthreads();
-        const uint32_t cnt = min(fill2[f], len);
-        uint8_t* mb = reinterpret_cast<uint8_t*>(mk);
-        for (uint32_t i0 = threadIdx.x; i0 < cnt; i0 += 4 * TPB_) {  // four loads in flight per lane
-            uint32_t kk[4];
+        constexpr int U = 8;  // loads in flight per lane
+        for (uint32_t i0 = t; i0 < c; i0 += U * MARK_TPB) {
+            uint32_t u[U];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint32_t i = i0 + u * TPB_;
-                kk[u] = (i < cnt) ? tx[base + i] - base : NONE;
+            for (int j = 0; j < U; ++j) {
+                const uint32_t i = i0 + j * MARK_TPB;
+                u[j] = (i < c) ? tx[lo + i + (i < front ? 0u : gap)] - lo : NONE;
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (kk[u] < len) mb[kk[u]] = 1;
+            for (int j = 0; j < U; ++j)
+                if (u[j] < len) atomicOr(&bits[u[j] >> 5], 1u << (u[j] & 31));
         }
         __syncthreads();
-        if ((len & 3) == 0) {
-            uint32_t* hw = reinterpret_cast<uint32_t*>(hp + base);
-            for (uint32_t i = threadIdx.x; i < len / 4; i += TPB_) hw[i] = mk[i];
+        if constexpr (DIR) {
+            constexpr uint32_t RW = (1u << PLACE_FINE_SHIFT) / 32;  // words of a counted range
+            static_assert(MARK_TPB % RW == 0 && RW % 64 == 0, "whole ranges a round, whole wavefronts a range");
+            for (uint32_t w0 = 0; w0 < words; w0 += MARK_TPB) {
+                const uint32_t w = w0 + t;
+                const uint32_t v = w < words ? bits[w] : 0u;
+                uint32_t in = __popc(v);
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) {
+                    const uint32_t y = __shfl_up(in, o);
+                    if ((t & 63) >= o) in += y;
+                }
+                if ((t & 63) == 63) sh[t >> 6] = in;
+                __syncthreads();
+                uint32_t pre = in - __popc(v);
+                for (uint32_t q = t / RW * (RW / 64); q < (t >> 6); ++q) pre += sh[q];
+                if (w < words) {
+                    dir[(lo >> 5) + w] = make_uint2(v, pre);
+                    if (w % RW == RW - 1 || w == words - 1) cnt[(lo >> PLACE_FINE_SHIFT) + w / RW] = pre + __popc(v);
+                }
+                __syncthreads();  // sh is reused by the next round
+            }
         } else {
-            for (uint32_t i = threadIdx.x; i < len; i += TPB_) hp[base + i] = mb[i];
-        }
-        __syncthreads();
-    }
-}
-
-// One workgroup per fine range, as k_mark3, but the range's marks become a
-// bitmap with running counts: word w of `dir` holds the bits of ids [32 w, 32 w
-// + 32) and the marked ids before them in their range; cnt[f] the range's.
-__global__ __launch_bounds__(place_tpb(false, false)) void k_mark_dir(const uint32_t* __restrict__ tx, uint32_t n,
-                                                                      uint32_t nb2, const uint32_t* __restrict__ fill2,
-                                                                      uint2* __restrict__ dir,
-                                                                      uint32_t* __restrict__ cnt) {
-    constexpr int TPB_ = place_tpb(false, false);
-    constexpr uint32_t R = 1u << PLACE_FINE_SHIFT;
-    static_assert(R / 32 <= TPB_, "one word a lane");
-    __shared__ uint4 mk4[R / 16];
-    __shared__ uint32_t sh[TPB_ / 64];
-    uint8_t* mb = reinterpret_cast<uint8_t*>(mk4);
-    for (uint32_t f = blockIdx.x; f < nb2; f += gridDim.x) {
-        const uint32_t base = f << PLACE_FINE_SHIFT;
-        const uint32_t len = min(R, n - base);
-        for (uint32_t i = threadIdx.x; i < R / 16; i += TPB_) mk4[i] = make_uint4(0, 0, 0, 0);
-        __syncthreads();
-        const uint32_t c = min(fill2[f], len);
-        for (uint32_t i0 = threadIdx.x; i0 < c; i0 += 4 * TPB_) {  // four loads in flight per lane
-            uint32_t kk[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint32_t i = i0 + u * TPB_;
-                kk[u] = (i < c) ? tx[base + i] - base : NONE;
+            for (uint32_t q = t; q < (len + 15) / 16; q += MARK_TPB) {
+                const uint32_t v = bits[q >> 1] >> (16 * (q & 1));
+                // four bits -> four bytes
+                auto four = [](uint32_t x) { return ((x & 15u) * 0x00204081u) & 0x01010101u; };
+                const uint4 o = make_uint4(four(v), four(v >> 4), four(v >> 8), four(v >> 12));
+                if (16 * q + 16 <= len) {
+                    *reinterpret_cast<uint4*>(hp + lo + 16 * q) = o;
+                } else {
+                    for (uint32_t j = 0; 16 * q + j < len; ++j) hp[lo + 16 * q + j] = (uint8_t)((v >> j) & 1u);
+                }
             }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (kk[u] < len) mb[kk[u]] = 1;
+            __syncthreads();  // LDS is reused by the next ids
         }
-        __syncthreads();
-        uint32_t bits = 0;
-        if (threadIdx.x < R / 32) bits = mark_bits(mk4[2 * threadIdx.x], mk4[2 * threadIdx.x + 1]);
-        uint32_t total;
-        const uint32_t pre = block_exscan(__popc(bits), sh, &total);
-        if (threadIdx.x < (len + 31) / 32) dir[(base >> 5) + threadIdx.x] = make_uint2(bits, pre);
-        if (threadIdx.x == 0) cnt[f] = total;
-        __syncthreads();  // LDS is reused by the next range
     }
 }
 
@@ -3455,41 +3446,52 @@ static hipError_t run_place(const RunArgs& a, const Plan& p, const typename Lay<
 }
 
 
+// Groups of the predecessor marks (k_mark1, k_mark_bits): 512 of them, two for
+// each CU, of at most 2^19 ids (64 KB of LDS, so that two fit a CU); from 2^30
+// ids on as many as the grouping can take, of up to 2^20.
+struct MarkShape {
+    uint32_t s1, nb1;
+    explicit MarkShape(uint32_t n) {
+        uint32_t lg = 0;
+        while ((1ull << lg) < n) ++lg;
+        s1 = std::min(19u, std::max(PLACE_FINE_SHIFT, lg > 9 ? lg - 9 : 0u));
+        s1 = std::max(s1, lg > 11 ? lg - 11 : 0u);
+        nb1 = (uint32_t)(((uint64_t)n + (1ull << s1) - 1) >> s1);
+    }
+    size_t lds() const { return (size_t)1 << (s1 - 3); }
+    dim3 grid() const { return dim3(std::min<uint32_t>(nb1, (uint32_t)device_cus() * 8)); }
+};
+static_assert(PLACE_MAX_RANGES >= 1u << 11, "groups of the largest input");
+
+// Groups the targets (a successor array's, or with TGT a list of nin ids) into
+// the log arrays, the groups' counters over the placement's second array: both
+// are free at this point.
+template <bool TGT>
+static hipError_t mark_groups(const MarkShape& ms, const uint32_t* src, uint32_t n, uint32_t nin, char* ws,
+                              const Plan& p, Ctrl* ctrl, const uint32_t* dm, Gate g, hipStream_t st, uint32_t** fill1) {
+    *fill1 = reinterpret_cast<uint32_t*>(ws + p.off_p[1]);
+    LR_TRY(fill(*fill1, 2 * (size_t)ms.nb1 * FILL_LINE * 4, 0u, st, nullptr, g));
+    const PlaceArrays<false> Q = place_arrays<false>(ws, p.off_log);
+    const size_t l1 = 8 * (size_t)ms.nb1 + 4 * MARK_TILE;  // ids only
+    LR_TRY(allow_lds(k_mark1<TGT>, l1));
+    hipLaunchKernelGGL(k_mark1<TGT>, dim3(grid_for(TGT ? nin : n, MARK_TILE)),
+                       dim3(place_tpb(false, false)), l1, st, src, n, ms.s1, ms.nb1, *fill1, Q, ctrl, g, dm, nin);
+    return hipGetLastError();
+}
+
 // Predecessor marks of level 0 in log mode (more than one list): link targets
-// grouped by range in two passes, then written range by range from LDS. The
-// grouping arrays of the placement are free at this point; the marks land on
-// the first of them (hp0), after its grouped targets have been consumed.
+// grouped by range, then marked range by range in LDS. The marks land on the
+// first of the placement's grouping arrays (hp0).
 static hipError_t run_marks(const RunArgs& a, const Plan& p, uint8_t* hp0, Ctrl* ctrl, const uint32_t* dm) {
-    char* ws = a.ws;
-    hipStream_t st = a.stream;
     const uint32_t n = (uint32_t)p.m[0];
     const Gate mg{&ctrl->multi, 1u << 1};  // plain path taken and more than one list
-    uint32_t* fill1 = reinterpret_cast<uint32_t*>(ws + p.off_fill);
-    uint32_t* fill2 = fill1 + 2 * (size_t)p.nb1 * FILL_LINE;
-    LR_TRY(fill(fill1, fill_words(p.nb1, p.nb2) * 4, 0u, st, nullptr, mg));
-    const PlaceArrays<false> P = place_arrays<false>(ws, p.off_p);
-    const PlaceArrays<false> Q = place_arrays<false>(ws, p.off_log);
-    constexpr uint32_t T = place_tile_records(false, false);
-    const dim3 tpb(place_tpb(false, false));
-    const bool vec = ((uintptr_t)a.succ % 16) == 0;
-    const size_t l1 = place_lds_bytes(false, false, p.nb1, false);
-    if (vec) {
-        LR_TRY(allow_lds(k_mark1<true>, l1));
-        hipLaunchKernelGGL(k_mark1<true>, dim3(grid_for(n, T)), tpb, l1, st, a.succ, n, p.s1, p.nb1, fill1, P, ctrl, mg,
-                           dm);
-    } else {
-        LR_TRY(allow_lds(k_mark1<false>, l1));
-        hipLaunchKernelGGL(k_mark1<false>, dim3(grid_for(n, T)), tpb, l1, st, a.succ, n, p.s1, p.nb1, fill1, P, ctrl,
-                           mg, dm);
-    }
-    LR_TRY(hipGetLastError());
-    const size_t l2 = place_lds_bytes(false, false, 1u << (p.s1 - p.s2), false);
-    LR_TRY(allow_lds(k_place2<false, false, false>, l2));
-    hipLaunchKernelGGL((k_place2<false, false, false>), dim3(grid_for(n, T)), tpb, l2, st, P, ctrl, n, p.s1, p.s2,
-                       fill2, Q, dm, fill1, mg);
-    LR_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_mark3, dim3(std::min<uint32_t>(p.nb2, (uint32_t)device_cus() * 8)), tpb,
-                       (size_t)1 << p.s2, st, Q.x, n, p.s2, p.nb2, fill2, hp0, mg, dm);
+    const MarkShape ms(n);
+    uint32_t* fill1;
+    LR_TRY(mark_groups<false>(ms, a.succ, n, n, a.ws, p, ctrl, dm, mg, a.stream, &fill1));
+    LR_TRY(allow_lds(k_mark_bits<false>, ms.lds() + 4 * MARK_TPB / 64));
+    hipLaunchKernelGGL(k_mark_bits<false>, ms.grid(), dim3(MARK_TPB), ms.lds(), a.stream,
+                       reinterpret_cast<const uint32_t*>(a.ws + p.off_log[0]), n, ms.s1, ms.nb1, fill1, hp0,
+                       (uint2*)nullptr, (uint32_t*)nullptr, ctrl, mg, dm);
     return hipGetLastError();
 }
 
@@ -3513,25 +3515,13 @@ hipError_t position_dir(const uint32_t* pos, uint32_t count, uint32_t m, uint2* 
     if (!position_dir_plan(m, opts, &p)) return hipErrorInvalidValue;
     char* base = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(ws) + ALIGN - 1) / ALIGN * ALIGN);
     Ctrl* ctrl = reinterpret_cast<Ctrl*>(base + p.off_ctrl);
-    uint32_t* fill1 = reinterpret_cast<uint32_t*>(base + p.off_fill);
-    uint32_t* fill2 = fill1 + 2 * (size_t)p.nb1 * FILL_LINE;
-    LR_TRY(fill(fill1, fill_words(p.nb1, p.nb2) * 4, 0u, st));
-    const PlaceArrays<false> P = place_arrays<false>(base, p.off_p);
-    const PlaceArrays<false> Q = place_arrays<false>(base, p.off_log);
-    constexpr uint32_t T = place_tile_records(false, false);
-    const dim3 tpb(place_tpb(false, false));
-    const size_t l1 = place_lds_bytes(false, false, p.nb1, false);
-    LR_TRY(allow_lds(k_mark1<false, true>, l1));
-    hipLaunchKernelGGL((k_mark1<false, true>), dim3(grid_for(count, T)), tpb, l1, st, pos, m, p.s1, p.nb1, fill1, P,
-                       ctrl, Gate{}, nullptr, count);
-    LR_TRY(hipGetLastError());
-    const size_t l2 = place_lds_bytes(false, false, 1u << (p.s1 - p.s2), false);
-    LR_TRY(allow_lds(k_place2<false, false, false>, l2));
-    hipLaunchKernelGGL((k_place2<false, false, false>), dim3(grid_for(m, T)), tpb, l2, st, P, ctrl, m, p.s1, p.s2,
-                       fill2, Q, nullptr, fill1, Gate{});
-    LR_TRY(hipGetLastError());
-    hipLaunchKernelGGL(k_mark_dir, dim3(std::min<uint32_t>(p.nb2, (uint32_t)device_cus() * 8)), tpb, 0, st, Q.x, m,
-                       p.nb2, fill2, dir, cnt);
+    const MarkShape ms(m);
+    uint32_t* fill1;
+    LR_TRY(mark_groups<true>(ms, pos, m, count, base, p, ctrl, nullptr, Gate{}, st, &fill1));
+    LR_TRY(allow_lds(k_mark_bits<true>, ms.lds() + 4 * MARK_TPB / 64));
+    hipLaunchKernelGGL(k_mark_bits<true>, ms.grid(), dim3(MARK_TPB), ms.lds(), st,
+                       reinterpret_cast<const uint32_t*>(base + p.off_log[0]), m, ms.s1, ms.nb1, fill1,
+                       (uint8_t*)nullptr, dir, cnt, ctrl, Gate{}, nullptr);
     return hipGetLastError();
 }
 
