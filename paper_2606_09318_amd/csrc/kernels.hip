@@ -3459,39 +3459,48 @@ struct MarkShape {
         nb1 = (uint32_t)(((uint64_t)n + (1ull << s1) - 1) >> s1);
     }
     size_t lds() const { return (size_t)1 << (s1 - 3); }
+    size_t fill_bytes() const { return 2 * (size_t)nb1 * FILL_LINE * 4; }
     dim3 grid() const { return dim3(std::min<uint32_t>(nb1, (uint32_t)device_cus() * 8)); }
 };
 static_assert(PLACE_MAX_RANGES >= 1u << 11, "groups of the largest input");
 
+// Below, outside of log mode, one byte store per link is faster (k_detect: one
+// launch less). Bytes -> groups, us a call, forests (int64 sums): 2.1 M 203 -> 206
+// (2.0 M 218 -> 222), 3 M 246 -> 240, 5 M 361 -> 336 (515 -> 487), 12 M 782 -> 694,
+// 33 M 2096 -> 1854.
+constexpr uint32_t MARKS_GROUPED_MIN = 5u << 19;
+
 // Groups the targets (a successor array's, or with TGT a list of nin ids) into
-// the log arrays, the groups' counters over the placement's second array: both
-// are free at this point.
+// ids, with the groups' counters in fill1.
 template <bool TGT>
-static hipError_t mark_groups(const MarkShape& ms, const uint32_t* src, uint32_t n, uint32_t nin, char* ws,
-                              const Plan& p, Ctrl* ctrl, const uint32_t* dm, Gate g, hipStream_t st, uint32_t** fill1) {
-    *fill1 = reinterpret_cast<uint32_t*>(ws + p.off_p[1]);
-    LR_TRY(fill(*fill1, 2 * (size_t)ms.nb1 * FILL_LINE * 4, 0u, st, nullptr, g));
-    const PlaceArrays<false> Q = place_arrays<false>(ws, p.off_log);
+static hipError_t mark_groups(const MarkShape& ms, const uint32_t* src, uint32_t n, uint32_t nin, void* ids,
+                              uint32_t* fill1, Ctrl* ctrl, const uint32_t* dm, Gate g, hipStream_t st) {
+    LR_TRY(fill(fill1, ms.fill_bytes(), 0u, st, nullptr, g));
+    PlaceArrays<false> Q{};
+    Q.x = static_cast<uint32_t*>(ids);
     const size_t l1 = 8 * (size_t)ms.nb1 + 4 * MARK_TILE;  // ids only
     LR_TRY(allow_lds(k_mark1<TGT>, l1));
-    hipLaunchKernelGGL(k_mark1<TGT>, dim3(grid_for(TGT ? nin : n, MARK_TILE)),
-                       dim3(place_tpb(false, false)), l1, st, src, n, ms.s1, ms.nb1, *fill1, Q, ctrl, g, dm, nin);
+    hipLaunchKernelGGL(k_mark1<TGT>, dim3(grid_for(TGT ? nin : n, MARK_TILE)), dim3(place_tpb(false, false)), l1, st,
+                       src, n, ms.s1, ms.nb1, fill1, Q, ctrl, g, dm, nin);
     return hipGetLastError();
 }
 
-// Predecessor marks of level 0 in log mode (more than one list): link targets
-// grouped by range, then marked range by range in LDS. The marks land on the
-// first of the placement's grouping arrays (hp0).
+// Predecessor marks of level 0 (more than one list) to hp0. In log mode they
+// land on the first of the placement's grouping arrays, with the log arrays and
+// the second grouping array free for the targets and the counters; otherwise all
+// three lie in the slot array, which the chase fills later.
 static hipError_t run_marks(const RunArgs& a, const Plan& p, uint8_t* hp0, Ctrl* ctrl, const uint32_t* dm) {
     const uint32_t n = (uint32_t)p.m[0];
     const Gate mg{&ctrl->multi, 1u << 1};  // plain path taken and more than one list
     const MarkShape ms(n);
-    uint32_t* fill1;
-    LR_TRY(mark_groups<false>(ms, a.succ, n, n, a.ws, p, ctrl, dm, mg, a.stream, &fill1));
+    const size_t nr = ((size_t)n + ALIGN - 1) / ALIGN * ALIGN;
+    char* ids = a.ws + (p.log0 ? p.off_log[0] : p.off_slot[0] + nr);
+    uint32_t* fill1 = reinterpret_cast<uint32_t*>(p.log0 ? a.ws + p.off_p[1] : ids + 4 * nr);
+    LR_TRY(mark_groups<false>(ms, a.succ, n, n, ids, fill1, ctrl, dm, mg, a.stream));
     LR_TRY(allow_lds(k_mark_bits<false>, ms.lds() + 4 * MARK_TPB / 64));
     hipLaunchKernelGGL(k_mark_bits<false>, ms.grid(), dim3(MARK_TPB), ms.lds(), a.stream,
-                       reinterpret_cast<const uint32_t*>(a.ws + p.off_log[0]), n, ms.s1, ms.nb1, fill1, hp0,
-                       (uint2*)nullptr, (uint32_t*)nullptr, ctrl, mg, dm);
+                       reinterpret_cast<const uint32_t*>(ids), n, ms.s1, ms.nb1, fill1, hp0, (uint2*)nullptr,
+                       (uint32_t*)nullptr, ctrl, mg, dm);
     return hipGetLastError();
 }
 
@@ -3516,12 +3525,13 @@ hipError_t position_dir(const uint32_t* pos, uint32_t count, uint32_t m, uint2* 
     char* base = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(ws) + ALIGN - 1) / ALIGN * ALIGN);
     Ctrl* ctrl = reinterpret_cast<Ctrl*>(base + p.off_ctrl);
     const MarkShape ms(m);
-    uint32_t* fill1;
-    LR_TRY(mark_groups<true>(ms, pos, m, count, base, p, ctrl, nullptr, Gate{}, st, &fill1));
+    char* ids = base + p.off_log[0];
+    uint32_t* fill1 = reinterpret_cast<uint32_t*>(base + p.off_p[1]);
+    LR_TRY(mark_groups<true>(ms, pos, m, count, ids, fill1, ctrl, nullptr, Gate{}, st));
     LR_TRY(allow_lds(k_mark_bits<true>, ms.lds() + 4 * MARK_TPB / 64));
     hipLaunchKernelGGL(k_mark_bits<true>, ms.grid(), dim3(MARK_TPB), ms.lds(), st,
-                       reinterpret_cast<const uint32_t*>(base + p.off_log[0]), m, ms.s1, ms.nb1, fill1,
-                       (uint8_t*)nullptr, dir, cnt, ctrl, Gate{}, nullptr);
+                       reinterpret_cast<const uint32_t*>(ids), m, ms.s1, ms.nb1, fill1, (uint8_t*)nullptr, dir, cnt,
+                       ctrl, Gate{}, nullptr);
     return hipGetLastError();
 }
 
@@ -3627,7 +3637,7 @@ static hipError_t run_srs_up(const RunArgs& a, Out0 out0, bool* done) {
     uint8_t* hp0 = reinterpret_cast<uint8_t*>(ws + p.off_slot[0]);
     {
         if (a.prologue) LR_TRY(a.desc ? run_batch_heads(a, p, Gate{}) : run_headsum(a, p, Gate{}));
-        if (p.log0) {
+        if (p.log0 || n >= MARKS_GROUPED_MIN) {
             LR_TRY(run_marks(a, p, hp0, ctrl, dm_at(0)));
         } else {
             LR_TRY(fill(hp0, n, 0u, st, ctrl, g));

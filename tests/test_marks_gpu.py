@@ -56,3 +56,20 @@ def test_few_and_many_targets(n, shape):
     elif shape == "one full group":
         succ[8192:16384] = i[:8192]
     check(succ)
+
+
+@pytest.mark.parametrize("n", [(5 << 19) - 1, 5 << 19, (5 << 19) + 33])
+def test_slot_array_forests(n):
+    """Without the visit log: byte stores below, groups in the slot array from
+    5 * 2^19 elements on."""
+    print(f"case: grouped marks without the log n={n}", flush=True)
+    F = workloads.forest(n, mean=64, n_long=1, long_len=4096, seed=n)
+    d = torch.from_numpy(F.succ.view(np.int32)).to("cuda:0")
+    s, r, t = lr.prefix_sum(d, torch.from_numpy(F.weight).to("cuda:0"))
+    r2, t2 = lr.rank(d, want_root=True)
+    torch.cuda.synchronize()
+    st, er, et, es = oracle.rank(F.succ, F.weight)
+    assert st == 0
+    assert np.array_equal(s.cpu().numpy(), es)
+    for got, ex in ((r, er), (t, et), (r2, er), (t2, et)):
+        assert np.array_equal(got.cpu().numpy().view(np.uint32), ex)
