@@ -278,18 +278,15 @@ __global__ __launch_bounds__(TPB) void k_headsum_final(const uint32_t* __restric
         const bool single = nt == 1 && hs < smp.m;
         ctrl->single = single ? 1u : 0u;
         ctrl->multi = single ? 0u : 1u;
-        if (single) {
-            const uint32_t h = (uint32_t)hs;
-            uint32_t H = 0;
-            if (!smp.sampled(h)) {
-                *reinterpret_cast<uint32_t*>(eb + (size_t)S * rec_bytes) = h;
-                H = 1;
-            }
-            ctrl->lv[lvl].H = H;
-            ctrl->lv[lvl].q = 0;
-            ctrl->chunks = 0;
-            ctrl->conts = 0;
+        uint32_t H = 0;  // more than one list: the marks' pass adds its heads
+        if (single && !smp.sampled((uint32_t)hs)) {
+            *reinterpret_cast<uint32_t*>(eb + (size_t)S * rec_bytes) = (uint32_t)hs;
+            H = 1;
         }
+        ctrl->lv[lvl].H = H;
+        ctrl->lv[lvl].q = 0;
+        ctrl->chunks = 0;
+        ctrl->conts = 0;
     }
 }
 
@@ -1994,26 +1991,32 @@ __global__ __launch_bounds__(place_tpb(false, false)) void k_mark1(const uint32_
 }
 
 // One workgroup per group of 2^s1 ids: its targets (fill1 holds how many lie at
-// the group's two ends) set bits in LDS, which are then written in order as bytes
-// (hp, all n) or, with DIR, as a bitmap with running counts: word w of `dir` holds
-// the bits of ids [32 w, 32 w + 32) and the marked ids before them in their range
-// of 2^PLACE_FINE_SHIFT ids; cnt[f] is that range's count. With a bit per id a
-// group is 2^18 ids in 32 KB, so one grouping pass is enough. Bound by the LDS
-// atomics: two workgroups a CU take 192 us for 2^27 ids, one (groups of 2^19) 301;
-// loading ahead gains nothing. A second grouping pass (375 us) and byte marks of
-// 8192 ids a workgroup (155) took the place of it: a 2^27 forest 6.28 -> 6.11 ms,
-// int64 sums over it 9.47 -> 9.36, 9 * 10^7 4.39 -> 4.28, a 2^26-vertex tree 8.97 -> 8.71.
+// the group's two ends) set bits in LDS. The ids left without one that are no
+// rulers are the level's initial elements: they start walks S + j, j counted up
+// in Ctrl.lv[0].H with one atomic a group. With DIR the bits become a bitmap with
+// running counts instead: word w of `dir` holds the bits of ids [32 w, 32 w + 32)
+// and the marked ids before them in their range of 2^PLACE_FINE_SHIFT ids; cnt[f]
+// is that range's count. With a bit per id a group is 2^18 ids in 32 KB, so one
+// grouping pass is enough. Bound by the LDS atomics: two workgroups a CU take 192
+// us for 2^27 ids, one (groups of 2^19) 301; loading ahead gains nothing. A second
+// grouping pass (375 us) and byte marks of 8192 ids a workgroup (155) took the
+// place of it: a 2^27 forest 6.28 -> 6.11 ms, int64 sums over it 9.51 -> 9.33, 9 *
+// 10^7 4.37 -> 4.27, a 2^26-vertex tree 8.91 -> 8.76. Marks written as bytes and
+// heads counted, scanned and written by three more
+// kernels: a 5 M forest 335 -> 324 us, 33 M 1856 -> 1807, 2^27 int64 9.33 -> 9.17 ms.
 template <bool DIR>
 __global__ __launch_bounds__(MARK_TPB) void k_mark_bits(const uint32_t* __restrict__ tx, uint32_t n, uint32_t s1,
                                                         uint32_t nb1, const uint32_t* __restrict__ fill1,
-                                                        uint8_t* __restrict__ hp, uint2* __restrict__ dir,
+                                                        Sampler smp, char* __restrict__ eb, uint32_t S,
+                                                        uint32_t rec_bytes, uint2* __restrict__ dir,
                                                         uint32_t* __restrict__ cnt, Ctrl* ctrl, Gate gate,
                                                         const uint32_t* dm) {
     if (gate.off()) return;
     extern __shared__ __align__(16) unsigned char lds[];
     __shared__ uint32_t sh[MARK_TPB / 64];
+    __shared__ uint32_t first;
     uint32_t* bits = reinterpret_cast<uint32_t*>(lds);
-    if (dm) n = dm[0];
+    if (dm) { n = smp.m = dm[0]; S = dm[1]; }
     const uint32_t t = threadIdx.x;
     for (uint32_t g = blockIdx.x; g < nb1; g += gridDim.x) {
         const uint32_t lo = g << s1;
@@ -2062,16 +2065,33 @@ __global__ __launch_bounds__(MARK_TPB) void k_mark_bits(const uint32_t* __restri
                 __syncthreads();  // sh is reused by the next round
             }
         } else {
-            for (uint32_t q = t; q < (len + 15) / 16; q += MARK_TPB) {
-                const uint32_t v = bits[q >> 1] >> (16 * (q & 1));
-                // four bits -> four bytes
-                auto four = [](uint32_t x) { return ((x & 15u) * 0x00204081u) & 0x01010101u; };
-                const uint4 o = make_uint4(four(v), four(v >> 4), four(v >> 8), four(v >> 12));
-                if (16 * q + 16 <= len) {
-                    *reinterpret_cast<uint4*>(hp + lo + 16 * q) = o;
-                } else {
-                    for (uint32_t j = 0; 16 * q + j < len; ++j) hp[lo + 16 * q + j] = (uint8_t)((v >> j) & 1u);
+            uint32_t mine = 0;
+            for (uint32_t w = t; w < words; w += MARK_TPB) {
+                const uint32_t x0 = lo + 32 * w, left = n - x0;
+                uint32_t no = bits[w];  // marked ids and rulers
+                const uint32_t blk = x0 >> smp.log2k;
+                const uint32_t blks = smp.log2k < 5 ? 32u >> smp.log2k : 1u;
+                for (uint32_t j = 0; j < blks && ((blk + j) << smp.log2k) < n; ++j) {
+                    const uint32_t d = smp.start(blk + j) - x0;
+                    if (d < 32) no |= 1u << d;
                 }
+                const uint32_t h = ~no & (left < 32 ? (1u << left) - 1u : ~0u);
+                bits[w] = h;
+                mine += __popc(h);
+            }
+            uint32_t total;
+            block_exscan(mine, sh, &total);
+            if (t == 0) first = total ? atomicAdd(&ctrl->lv[0].H, total) : 0u;
+            __syncthreads();
+            uint32_t run = S + first;
+            for (uint32_t w0 = 0; total && w0 < words; w0 += MARK_TPB) {
+                const uint32_t w = w0 + t;
+                uint32_t h = w < words ? bits[w] : 0u, tot;
+                uint32_t pos = run + block_exscan(__popc(h), sh, &tot);
+                for (; h; h &= h - 1)
+                    *reinterpret_cast<uint32_t*>(eb + (size_t)pos++ * rec_bytes) = lo + 32 * w + __ffs(h) - 1;
+                run += tot;
+                __syncthreads();  // sh is reused by the next round
             }
             __syncthreads();  // LDS is reused by the next ids
         }
@@ -2377,6 +2397,10 @@ __global__ __launch_bounds__(1024) void k_batch_heads(const uint2* __restrict__ 
             ctrl->single = 0;
             ctrl->multi = 1;
             ctrl->mode = MODE_PLAIN;
+            ctrl->lv[0].H = 0;  // the marks' pass adds the heads
+            ctrl->lv[0].q = 0;
+            ctrl->chunks = 0;
+            ctrl->conts = 0;
         }
         return;
     }
@@ -3464,11 +3488,11 @@ struct MarkShape {
 };
 static_assert(PLACE_MAX_RANGES >= 1u << 11, "groups of the largest input");
 
-// Below, outside of log mode, one byte store per link is faster (k_detect: one
-// launch less). Bytes -> groups, us a call, forests (int64 sums): 2.1 M 203 -> 206
-// (2.0 M 218 -> 222), 3 M 246 -> 240, 5 M 361 -> 336 (515 -> 487), 12 M 782 -> 694,
-// 33 M 2096 -> 1854.
-constexpr uint32_t MARKS_GROUPED_MIN = 5u << 19;
+// Below, outside of log mode, one byte store per link (k_detect) and the heads'
+// own kernels are as fast. Bytes -> groups, us a call, forests (int64 sums): (1.06 M
+// 154 -> 149), 2.1 M 201 -> 194 (2.0 M 217 -> 207), 5 M 361 -> 324 (515 -> 479), 9 M
+// 594 -> 523, 33 M 2096 -> 1807.
+constexpr uint32_t MARKS_GROUPED_MIN = 1u << 20;
 
 // Groups the targets (a successor array's, or with TGT a list of nin ids) into
 // ids, with the groups' counters in fill1.
@@ -3485,22 +3509,23 @@ static hipError_t mark_groups(const MarkShape& ms, const uint32_t* src, uint32_t
     return hipGetLastError();
 }
 
-// Predecessor marks of level 0 (more than one list) to hp0. In log mode they
-// land on the first of the placement's grouping arrays, with the log arrays and
-// the second grouping array free for the targets and the counters; otherwise all
-// three lie in the slot array, which the chase fills later.
-static hipError_t run_marks(const RunArgs& a, const Plan& p, uint8_t* hp0, Ctrl* ctrl, const uint32_t* dm) {
+// Initial elements of level 0 (more than one list) from grouped predecessor
+// marks. In log mode the log arrays and the second grouping array are free for the
+// targets and the counters; otherwise both lie in the slot array, which the chase
+// fills later.
+static hipError_t run_marks(const RunArgs& a, const Plan& p, Ctrl* ctrl, const uint32_t* dm) {
     const uint32_t n = (uint32_t)p.m[0];
     const Gate mg{&ctrl->multi, 1u << 1};  // plain path taken and more than one list
     const MarkShape ms(n);
-    const size_t nr = ((size_t)n + ALIGN - 1) / ALIGN * ALIGN;
-    char* ids = a.ws + (p.log0 ? p.off_log[0] : p.off_slot[0] + nr);
-    uint32_t* fill1 = reinterpret_cast<uint32_t*>(p.log0 ? a.ws + p.off_p[1] : ids + 4 * nr);
+    const Sampler smp{n, p.log2k[0], p.lseed[0]};
+    char* ids = a.ws + (p.log0 ? p.off_log[0] : p.off_slot[0]);
+    uint32_t* fill1 = reinterpret_cast<uint32_t*>(
+        p.log0 ? a.ws + p.off_p[1] : ids + (4 * (size_t)n + ALIGN - 1) / ALIGN * ALIGN);
     LR_TRY(mark_groups<false>(ms, a.succ, n, n, ids, fill1, ctrl, dm, mg, a.stream));
-    LR_TRY(allow_lds(k_mark_bits<false>, ms.lds() + 4 * MARK_TPB / 64));
+    LR_TRY(allow_lds(k_mark_bits<false>, ms.lds() + 1024));
     hipLaunchKernelGGL(k_mark_bits<false>, ms.grid(), dim3(MARK_TPB), ms.lds(), a.stream,
-                       reinterpret_cast<const uint32_t*>(ids), n, ms.s1, ms.nb1, fill1, hp0, (uint2*)nullptr,
-                       (uint32_t*)nullptr, ctrl, mg, dm);
+                       reinterpret_cast<const uint32_t*>(ids), n, ms.s1, ms.nb1, fill1, smp, a.ws + p.off_eb[0],
+                       (uint32_t)p.m[1], (uint32_t)p.rec_bytes, (uint2*)nullptr, (uint32_t*)nullptr, ctrl, mg, dm);
     return hipGetLastError();
 }
 
@@ -3528,10 +3553,10 @@ hipError_t position_dir(const uint32_t* pos, uint32_t count, uint32_t m, uint2* 
     char* ids = base + p.off_log[0];
     uint32_t* fill1 = reinterpret_cast<uint32_t*>(base + p.off_p[1]);
     LR_TRY(mark_groups<true>(ms, pos, m, count, ids, fill1, ctrl, nullptr, Gate{}, st));
-    LR_TRY(allow_lds(k_mark_bits<true>, ms.lds() + 4 * MARK_TPB / 64));
+    LR_TRY(allow_lds(k_mark_bits<true>, ms.lds() + 1024));
     hipLaunchKernelGGL(k_mark_bits<true>, ms.grid(), dim3(MARK_TPB), ms.lds(), st,
-                       reinterpret_cast<const uint32_t*>(ids), m, ms.s1, ms.nb1, fill1, (uint8_t*)nullptr, dir, cnt,
-                       ctrl, Gate{}, nullptr);
+                       reinterpret_cast<const uint32_t*>(ids), m, ms.s1, ms.nb1, fill1, Sampler{}, (char*)nullptr, 0u,
+                       0u, dir, cnt, ctrl, Gate{}, nullptr);
     return hipGetLastError();
 }
 
@@ -3634,12 +3659,13 @@ static hipError_t run_srs_up(const RunArgs& a, Out0 out0, bool* done) {
     }
     // level 0: initial elements. One list: its head from a streaming sum.
     // Otherwise: predecessor marks (the one-list case skips these kernels).
-    uint8_t* hp0 = reinterpret_cast<uint8_t*>(ws + p.off_slot[0]);
+    const bool grouped = p.log0 || n >= MARKS_GROUPED_MIN;
     {
         if (a.prologue) LR_TRY(a.desc ? run_batch_heads(a, p, Gate{}) : run_headsum(a, p, Gate{}));
-        if (p.log0 || n >= MARKS_GROUPED_MIN) {
-            LR_TRY(run_marks(a, p, hp0, ctrl, dm_at(0)));
+        if (grouped) {
+            LR_TRY(run_marks(a, p, ctrl, dm_at(0)));
         } else {
+            uint8_t* hp0 = reinterpret_cast<uint8_t*>(ws + p.off_slot[0]);
             LR_TRY(fill(hp0, n, 0u, st, ctrl, g));
             const bool vec = ((uintptr_t)a.succ % 16) == 0;
             const uint32_t gd = grid_for(n, TPB * 4 * 4);
@@ -3660,17 +3686,21 @@ static hipError_t run_srs_up(const RunArgs& a, Out0 out0, bool* done) {
         const uint32_t zw = more ? (S + 3) / 4 : 0;
         const uint32_t gt = std::min<uint32_t>(p.ntiles[l], (uint32_t)device_cus() * 8);
         const uint32_t last = p.ntiles[l] <= HEADS_SCAN_LAST_TILES;
-        hipLaunchKernelGGL(k_heads_count, dim3(gt), dim3(TPB), 0, st, hp, smp, tile, p.ntiles[l], zp, zw,
-                           (uint32_t)(l == 0), last, ctrl, (int)l, dm_at(l), g);
-        LR_TRY(hipGetLastError());
-        if (!last) {
-            hipLaunchKernelGGL(k_heads_scan, dim3(1), dim3(1024), 0, st, tile, p.ntiles[l], ctrl, (int)l,
-                               (uint32_t)(l == 0), g);
+        if (l == 0 && grouped) {  // the marks' pass found them
+            if (zw) LR_TRY(fill(zp, 4 * (uint64_t)zw, 0u, st, nullptr, g));
+        } else {
+            hipLaunchKernelGGL(k_heads_count, dim3(gt), dim3(TPB), 0, st, hp, smp, tile, p.ntiles[l], zp, zw,
+                               (uint32_t)(l == 0), last, ctrl, (int)l, dm_at(l), g);
+            LR_TRY(hipGetLastError());
+            if (!last) {
+                hipLaunchKernelGGL(k_heads_scan, dim3(1), dim3(1024), 0, st, tile, p.ntiles[l], ctrl, (int)l,
+                                   (uint32_t)(l == 0), g);
+                LR_TRY(hipGetLastError());
+            }
+            hipLaunchKernelGGL(k_heads_write, dim3(gt), dim3(TPB), 0, st, hp, smp, tile, p.ntiles[l],
+                               ws + p.off_eb[l], S, (uint32_t)p.rec_bytes, (l == 0) ? ctrl : nullptr, dm_at(l), g);
             LR_TRY(hipGetLastError());
         }
-        hipLaunchKernelGGL(k_heads_write, dim3(gt), dim3(TPB), 0, st, hp, smp, tile, p.ntiles[l], ws + p.off_eb[l],
-                           S, (uint32_t)p.rec_bytes, (l == 0) ? ctrl : nullptr, dm_at(l), g);
-        LR_TRY(hipGetLastError());
         if (a.validate && !(l == 0 && p.log0))
             LR_TRY(fill(ws + p.off_slot[l], (uint64_t)m * p.rec_bytes, 0xffffffffu, st, nullptr, g));
         if (l == 0) rec_ev(a, EV_HEADS);

@@ -58,10 +58,10 @@ def test_few_and_many_targets(n, shape):
     check(succ)
 
 
-@pytest.mark.parametrize("n", [(5 << 19) - 1, 5 << 19, (5 << 19) + 33])
+@pytest.mark.parametrize("n", [(1 << 20) - 1, 1 << 20, (1 << 20) + 33, (5 << 19) - 1, 5 << 19, (5 << 19) + 33])
 def test_slot_array_forests(n):
     """Without the visit log: byte stores below, groups in the slot array from
-    5 * 2^19 elements on."""
+    2^20 elements on."""
     print(f"case: grouped marks without the log n={n}", flush=True)
     F = workloads.forest(n, mean=64, n_long=1, long_len=4096, seed=n)
     d = torch.from_numpy(F.succ.view(np.int32)).to("cuda:0")
