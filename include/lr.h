@@ -306,12 +306,14 @@ lr_status lr_prefix_sum_wyllie(const uint32_t* succ, const void* weight, lr_wtyp
 
 /* Tree computations by the Euler-tour technique (the paper ranks Euler tours
  * of BFS trees as an input family, Section 3, and names tree algorithms as
- * the users of list ranking, Section 1). One lr_prefix_sum over the tour with
- * weight +1 on down arcs and -1 on up arcs gives, for every arc a, the number
- * of arcs (rank) and #down - #up (sum) from a to the end of the tour; depth,
- * preorder number and subtree size of every vertex follow from the values at
- * the vertex's two arcs (those of the tour's first arc are fixed by V: rank
- * 2V - 3, sum 1).
+ * the users of list ranking, Section 1). Ranking the tour gives every arc's
+ * position; a vertex's size follows from the positions of its two arcs, its
+ * preorder number is the number of down arcs up to its own, its depth twice
+ * that less the position. With LR_VALIDATE, and for small trees, one
+ * lr_prefix_sum over the tour with weight +1 on down arcs and -1 on up arcs
+ * gives the number of arcs (rank) and #down - #up (sum) from every arc to the
+ * end of the tour instead, and depth, preorder number and size from those (the
+ * first arc's are fixed by V: rank 2V - 3, sum 1).
  *   succ  [m] uint32, m = 2(V-1): the tour as a successor array over its arcs
  *         (one list; its last arc is the terminal). Ignored when V == 1.
  *   down  [V] uint32: down[v] = id of the arc parent(v) -> v.
@@ -328,7 +330,7 @@ lr_status lr_prefix_sum_wyllie(const uint32_t* succ, const void* weight, lr_wtyp
  * and that the tour is one list starting with rank 2V - 3 and sum 1
  * (LR_ERR_BAD_LIST otherwise); without it such
  * input gives unspecified outputs, never an out-of-bounds access. opts apply
- * to the inner lr_prefix_sum. */
+ * to the inner call. */
 size_t lr_euler_tree_workspace_bytes(uint64_t V, const lr_opts* opts);
 lr_status lr_euler_tree(const uint32_t* succ, const uint32_t* down, const uint32_t* up, uint64_t V, uint32_t root,
                         uint32_t* depth, uint32_t* preorder, uint32_t* size,
@@ -337,7 +339,7 @@ lr_status lr_euler_tree(const uint32_t* succ, const uint32_t* down, const uint32
 /* Plan autotuner (the paper fixes its ruler-count constants by a parameter
  * study, Section 3 "Methodology"; this does the same on the caller's input).
  * Times lr_rank (w == LR_W_NONE, weight NULL) or lr_prefix_sum (any other w)
- * on `succ` in three stages, each keeping the fastest so far and varying one
+ * on `succ` with the planner's own plan, then in three stages, each keeping the fastest so far and varying one
  * group: the ruler spacings of the first two levels (16..128 x 8..32), then
  * the base-case size, then walks per lane and the refill threshold. It keeps
  * `base`'s seed and flags other than LR_VALIDATE / LR_PROFILE, writes the

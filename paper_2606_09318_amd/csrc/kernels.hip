@@ -2,7 +2,10 @@
 //
 // Sparse ruling set (Section 2.1, Fig. 1), per level l of the recursion:
 //   detect   (level 0 only) mark every element that has a predecessor;
-//            unmarked elements are the initial elements (findInit).
+//            unmarked elements are the initial elements (findInit). One list:
+//            its head from a streaming sum (headsum). Forests from 2^20
+//            elements on: link targets grouped by range (mark1), marks and
+//            initial elements from LDS bitmaps (mark_bits), no heads pass.
 //   heads    compact the initial elements that are not sampled rulers into a
 //            walk list (tile count -> one-workgroup scan -> tile write).
 //   chase    one lane per walk: from its start, follow succ and record in
@@ -10,8 +13,14 @@
 //            next sampled ruler or a terminal (the ruler chasing loop). The
 //            walk's end and total weight form the next level's element (for a
 //            sampled ruler) or a parked record (for an initial element).
-//   base     the last level (<= base_max elements) is ranked by pointer
-//            doubling in LDS by one workgroup (the base case).
+//   iw       the first level of at most about 2^21 elements and those above it
+//            are ranked by independent walks: every element to the next ruler
+//            (iw_first, iw_walk), asynchronous doubling on the last level
+//            (iw_double), downward passes (iw_down). Inputs of that size take
+//            the same kernels alone.
+//   base     inputs of at most 8192 elements, and the last level of plans that
+//            name their own levels, are ranked by pointer doubling in LDS by
+//            one workgroup (the base case).
 //   resolve  walks of initial elements take the result of the ruler (or
 //            terminal) they ended on.
 //   expand   every element takes rank = rank(walk) - offset and the walk's
@@ -21,9 +30,8 @@
 //
 // Level 0 of large inputs (n >= 2^25) logs the chase's visits and places the
 // results by element range (place1/2/3) instead of storing at random
-// addresses; with more than one list its predecessor marks are grouped by
-// range the same way (mark1, place2 on ids, mark3), and weighted inputs are
-// interleaved into one record per element first (pair).
+// addresses, and weighted inputs are interleaved into one record per element
+// first (pair).
 //
 // Tile-local contraction (Section 2.3): chains of links inside 4096-id tiles
 // are contracted first (lc_chain, lc_scan, lc_compact), the levels above rank

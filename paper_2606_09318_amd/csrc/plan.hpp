@@ -156,9 +156,9 @@ inline size_t batch_table_bytes(uint32_t count) { return 2 * ((size_t)count + 1)
 // are not chased at all.
 // Measured (random lists, rank and root; weighted: int64, every output; us a
 // call, same box), the other side of each line first:
-//   chase and base case -> independent walks: 2^15 83 -> 27, 2^18 117 -> 41,
-//     2^20 185 -> 89, 1.5 * 2^20 150 (one chased level) -> 130; weighted 2^17
-//     113 -> 59, 2^18 136 -> 79, 1.4 * 2^18 133 (one chased level) -> 101, but
+//   chase and base case -> independent walks: 2^15 68 -> 22, 2^18 117 -> 39,
+//     2^20 185 -> 83, 1.5 * 2^20 150 (one chased level) -> 122; weighted 2^17
+//     113 -> 50, 2^18 135 -> 68, 1.4 * 2^18 133 (one chased level) -> 89, but
 //     1.4 * 2^19 152 -> 168: a weighted step reads two arrays
 //   iw_max 2^18 -> 2^20: 1.5 * 2^22 459 -> 414, 1.5 * 2^24 1398 -> 1350; -> 2^21:
 //     block lists of 2^22 (a contracted list of capacity 1.3 M) 155 -> 121, 5 M
