@@ -52,6 +52,7 @@
 #include <algorithm>
 
 #include "device.hpp"
+#include "hop.hpp"
 #include "runner.hpp"
 
 namespace lr {
@@ -806,9 +807,9 @@ __global__ __launch_bounds__(BASE_TPB) void k_base_unweighted(Src src, Out out, 
         for (int j = 0; j < COLS; ++j) w[j] = get(((uint32_t)e[j] & TERM) ? t + j * BASE_TPB : (uint32_t)e[j]);
 #pragma unroll
         for (int j = 0; j < COLS; ++j) {
-            const uint32_t c = (uint32_t)(e[j] >> 32) + (uint32_t)(w[j] >> 32);
+            const uint32_t b = (uint32_t)(e[j] >> 32), c = b + (uint32_t)(w[j] >> 32);
             // more links than the input has: a cycle
-            const uint64_t n = c >= climit ? ~0ull : iw_word((uint32_t)w[j], c);
+            const uint64_t n = hop_stuck(b, c, (uint32_t)w[j] & TERM, climit) ? ~0ull : iw_word((uint32_t)w[j], c);
             e[j] = ((uint32_t)e[j] & TERM) ? e[j] : n;
             put(t + j * BASE_TPB, e[j]);
         }
@@ -893,10 +894,11 @@ __global__ __launch_bounds__(BASE_TPB) void k_base_weighted(Src src, Out out, ui
             const uint32_t i = t + j * BASE_TPB;
             const uint32_t fa = (uint32_t)a[j] & (2 * BW_END - 1);
             if ((f[j] & BW_END) || fa != ((uint32_t)b[j] & (2 * BW_END - 1))) continue;  // ended, or caught half stored
+            const uint32_t before = c[j];
             c[j] += (uint32_t)(a[j] >> 14) & IDX;
             s[j] += (a[j] >> 45) | ((b[j] >> 14) << 19);
             f[j] = fa;
-            if (c[j] >= climit) {  // more links than the input has: a cycle
+            if (hop_stuck(before, c[j], fa & BW_END, climit)) {  // more links than the input has: a cycle
                 cyc |= 1u << j;
                 f[j] = BW_END | i;
                 c[j] = 0;
@@ -1060,7 +1062,8 @@ __global__ __launch_bounds__(BASE_TPB) void k_base_weighted_large(Src src, Out o
 //   - No lane waits for another: a lane alone still moves at least one link a
 //     hop, so the kernels end however their workgroups are scheduled.
 //   - On a cycle (input that is not a forest) the count reaches climit, more
-//     links than a list can have, and the lane stops.
+//     links than a list can have, and the lane stops; so it does where a hop
+//     counts no link (hop_stuck), as unwritten records of such input may.
 //   - An order built against the sampling leaves long stretches without a
 //     ruler. The downward pass over the input then turns into doubling itself:
 //     after IW_PATIENCE hops (a random order needs 1.5 on average and stays
@@ -1231,8 +1234,9 @@ __device__ __forceinline__ void iw_double(uint64_t* __restrict__ nodes, uint32_t
     for (uint32_t hop = 0; !(nxt & TERM) && hop < cap; ++hop) {
         bool bad = nxt >= total;
         if (!bad) {
+            const uint32_t before = acc.c;
             if (!iw_hop<W, true>(nodes, nxt, acc)) continue;
-            bad = acc.c >= climit;
+            bad = hop_stuck(before, acc.c, nxt & TERM, climit);
         }
         if (bad) {  // more links than the input has: a cycle (or no forest at all)
             nxt = TERM | IDX;
@@ -1313,9 +1317,10 @@ __device__ __forceinline__ void iw_down(uint64_t* __restrict__ nodes, const Samp
             // caught between two of its stores (weighted): look again
             if (!bad && !ok[r] && !IwRec<W>::template load<true>(nodes, nxt[r], nn[r], v[r])) continue;
             if (!bad) {
+                const uint32_t before = acc[r].c;
                 acc[r] = L::add(acc[r], v[r]);
                 nxt[r] = nn[r];
-                bad = acc[r].c >= climit;
+                bad = hop_stuck(before, acc[r].c, nxt[r] & TERM, climit);
             }
             if (bad) {
                 nxt[r] = TERM | IDX;
@@ -2196,11 +2201,12 @@ __global__ __launch_bounds__(TPB) void k_fb_double(uint64_t* __restrict__ nodes,
             IwRec<W>::template load<true>(nodes, i, nxt, acc);  // its own stores, in order
             if (nxt & TERM) continue;
             bool bad = nxt >= m;
+            const uint32_t before = acc.c;
             if (!bad && !iw_hop<W, true>(nodes, nxt, acc)) {
                 open = true;
                 continue;
             }
-            bad |= acc.c >= m;
+            bad |= hop_stuck(before, acc.c, nxt & TERM, m);
             if (bad) {
                 nxt = TERM | IDX;
                 acc = L::junk();

@@ -1,0 +1,72 @@
+"""Input that is not a forest, without validation: unspecified outputs, but the
+call ends, whatever the workspace held before it. Chains that merge inside a
+tile of 4096 ids leave the records of the chains that lost the merge unwritten
+in the contracted list, so its ranking reads what the memory held. The call
+after it, on valid input with the same workspace, equals the oracle, and
+LR_VALIDATE refuses the input."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2606_09318_amd as lr
+import workloads
+from gpu_util import dev, host_u32
+
+pytestmark = pytest.mark.gpu
+
+TILE = 4096
+
+
+def merging_chains(n):
+    """Ids in order, cut into lists of 64; in every tile the heads of the
+    first 32 lists link to one element, and so do those lists' ends."""
+    i = np.arange(n, dtype=np.int64)
+    succ = np.minimum(i + 1, n - 1)
+    tile = i // TILE * TILE
+    off = i - tile
+    heads = (off < 2048) & (off % 64 == 0)
+    ends = (off < 2048) & (off % 64 == 63)
+    target = np.minimum(tile + 2100, n - 1)
+    succ[heads] = target[heads]
+    succ[ends] = target[ends]
+    return succ.astype(np.uint32)
+
+
+PLANS = [dict(flags=lr.LR_LOCAL), dict(flags=0),                                   # the planner's plans
+         dict(flags=lr.LR_LOCAL, base_max=4096), dict(flags=lr.LR_LOCAL, base_max=16384)]  # base cases above chased levels
+
+
+# the contracted list alone, one and two levels of walks above it, a chased capacity
+@pytest.mark.parametrize("n", [TILE + 100, 40 * TILE + 17, 300 * TILE, (1 << 22) + 5])
+@pytest.mark.parametrize("plan", range(len(PLANS)))
+@pytest.mark.parametrize("weighted", [False, True])
+def test_merging_chains_end(n, plan, weighted):
+    kw = PLANS[plan]
+    if weighted and kw.get("base_max") == 16384:
+        kw = dict(kw, base_max=8192)  # what one workgroup's LDS holds of weighted records
+    bad, good = merging_chains(n), workloads.block_list(n, 1 << 10, seed=n % 31).succ
+    w_np = workloads.weights(n, seed=3, stream=1, lo=-1000, hi=1000) if weighted else None
+    _, er, et, es = oracle.rank(good, w_np)
+    w = dev(w_np) if weighted else None
+    wt = lr.LR_W_I64 if weighted else lr.LR_W_NONE
+    r, t = (torch.empty(n, dtype=torch.int32, device="cuda") for _ in range(2))
+    s = torch.empty(n, dtype=torch.int64, device="cuda") if weighted else None
+
+    def call(succ, ws, o):
+        st = lr.lr_prefix_sum(succ, w, s, r, t, ws, o) if weighted else lr.lr_rank(succ, r, t, ws, o)
+        torch.cuda.synchronize()
+        return st
+
+    bad, good = dev(bad), dev(good)
+    o, v = lr.make_opts(**kw), lr.make_opts(**dict(kw, flags=kw["flags"] | lr.LR_VALIDATE))
+    ws = lr.workspace(max(lr.lr_workspace_bytes(n, wt, x) for x in (o, v)))
+    for byte in (0, 1, 255):
+        print(f"case: merging chains n={n} {kw} weighted={weighted} workspace bytes {byte}", flush=True)
+        ws.fill_(byte)
+        assert call(bad, ws, o) == lr.LR_OK
+    assert call(good, ws, o) == lr.LR_OK
+    assert np.array_equal(host_u32(r), er) and np.array_equal(host_u32(t), et)
+    if weighted:
+        assert np.array_equal(s.cpu().numpy(), es)
+    assert call(bad, ws, v) == lr.LR_ERR_BAD_LIST
