@@ -2183,12 +2183,14 @@ __global__ __launch_bounds__(TPB) void k_fb_first(Src src, uint64_t* __restrict_
 }
 
 // err: where to report a path that never reaches a terminal (more links than
-// elements: a cycle), or null.
-template <bool W, class Out>
-__global__ __launch_bounds__(TPB) void k_fb_double(uint64_t* __restrict__ nodes, uint32_t m, Out out, uint32_t* err,
-                                                   const uint32_t* dm, Gate gate) {
+// elements: a cycle), or null. An element that catches another's record between
+// two of its stores (weighted) takes one link from the input instead, so every
+// element moves in every pass and the end waits for no other lane's stores.
+template <bool W, class Src, class Out>
+__global__ __launch_bounds__(TPB) void k_fb_double(Src src, uint64_t* __restrict__ nodes, uint32_t m, Out out,
+                                                   uint32_t* err, const uint32_t* dm, Gate gate) {
     if (gate.off()) return;
-    if (dm) m = dm[0];
+    if (dm) m = src.m = dm[0];
     using L = Lay<W>;
     const uint32_t stride = gridDim.x * blockDim.x;
     const uint32_t i0 = blockIdx.x * blockDim.x + threadIdx.x;
@@ -2203,8 +2205,11 @@ __global__ __launch_bounds__(TPB) void k_fb_double(uint64_t* __restrict__ nodes,
             bool bad = nxt >= m;
             const uint32_t before = acc.c;
             if (!bad && !iw_hop<W, true>(nodes, nxt, acc)) {
-                open = true;
-                continue;
+                typename L::Val v;
+                uint32_t nn;
+                src.load(nxt, nn, v);
+                acc = L::add(acc, v);
+                nxt = nn;
             }
             bad |= hop_stuck(before, acc.c, nxt & TERM, m);
             if (bad) {
@@ -4159,13 +4164,13 @@ static hipError_t run_fallback_t(const RunArgs& a, Out0 out0) {
     const Gate g{&ctrl->mode, mode_bit(MODE_FALLBACK)};
     uint64_t* nodes = reinterpret_cast<uint64_t*>(a.ws + p.off_fb);
     const uint32_t* dm = a.dev_sizes ? &ctrl->dm[0] : nullptr;
-    hipLaunchKernelGGL((k_fb_first<W, Src>), dim3(grid_for(n, TPB)), dim3(TPB), 0, a.stream, Src{a.succ, a.weight, n},
-                       nodes, n, dm, g);
+    const Src src{a.succ, a.weight, n};
+    hipLaunchKernelGGL((k_fb_first<W, Src>), dim3(grid_for(n, TPB)), dim3(TPB), 0, a.stream, src, nodes, n, dm, g);
     LR_TRY(hipGetLastError());
-    auto kern = k_fb_double<W, Out0>;
+    auto kern = k_fb_double<W, Src, Out0>;
     static const uint32_t resident = persistent_grid(kern, TPB);  // one per template instance, found once
-    hipLaunchKernelGGL(kern, dim3(std::min<uint32_t>(grid_for(n, TPB), resident)), dim3(TPB), 0, a.stream, nodes, n,
-                       out0, a.validate ? &ctrl->err : nullptr, dm, g);
+    hipLaunchKernelGGL(kern, dim3(std::min<uint32_t>(grid_for(n, TPB), resident)), dim3(TPB), 0, a.stream, src, nodes,
+                       n, out0, a.validate ? &ctrl->err : nullptr, dm, g);
     return hipGetLastError();
 }
 
