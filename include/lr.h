@@ -364,9 +364,10 @@ lr_status lr_autotune(const uint32_t* succ, const void* weight, lr_wtype w, uint
  * bucket floor(log2 n) and whether the call is weighted.
  *   lr_autotune_arch: the device key lookups use.
  *   lr_autotune_cache_save / _load: a text file, one entry per line
- *     (arch log2n weighted k0 k1 base_max lane_walks refill ms); loading
- *     checks every value as the planner checks user options, adds or
- *     replaces entries, and changes nothing on LR_ERR_INVALID_ARG. */
+ *     (arch log2n weighted k0 k1 base_max lane_walks refill ms; k0 and k1 0:
+ *     the planner's spacings); loading checks every value as the planner
+ *     checks user options, adds or replaces entries, and changes nothing on
+ *     LR_ERR_INVALID_ARG. */
 const char* lr_autotune_arch(void);
 int lr_autotune_cache_entries(void);
 void lr_autotune_cache_clear(void);

@@ -141,9 +141,10 @@ lr_status lr_autotune_cache_load(const char* path) {
             break;
         }
         k.arch = arch;
-        // the same checks the planner makes on user options
+        // the same checks the planner makes on user options (no first spacing: the
+        // planner's, then no second one either)
         auto pow2 = [](uint32_t x, uint32_t lo, uint32_t hi) { return x >= lo && x <= hi && !(x & (x - 1)); };
-        if (!pow2(v.k0, 2, 4096) || (v.k1 && !pow2(v.k1, 2, 4096)) || v.base_max > BASE_MAX_LIMIT ||
+        if ((v.k0 && !pow2(v.k0, 2, 4096)) || (v.k1 && (!v.k0 || !pow2(v.k1, 2, 4096))) || v.base_max > BASE_MAX_LIMIT ||
             v.lane_walks > 2 || v.refill > 64 * (v.lane_walks ? v.lane_walks : 1) || k.weighted > 1 || k.log2n > 31) {
             ok = false;
             break;
