@@ -349,7 +349,9 @@ lr_status lr_euler_tree(const uint32_t* succ, const uint32_t* down, const uint32
  * spacing[0], base_max, lane_walks and refill at 0 (NULL options included)
  * and do not ask for LR_SPAWN takes the cached entry; its results are the
  * same whatever the plan, but its workspace size may change, so query
- * *_workspace_bytes after tuning. The trial calls write their outputs to
+ * *_workspace_bytes after tuning. Where the planner's own levels win, the
+ * entry says so, and each call of the bucket plans its own; the levels of a
+ * contracted list are always the planner's then. The trial calls write their outputs to
  * the tail of `ws` (n x 4 B, weighted n x 8 B) and use the rest as their
  * workspace; candidates that do not fit are skipped (LR_ERR_WORKSPACE if
  * none fits). `ms` (may be NULL) receives up to `cap` timings, in the order

@@ -141,19 +141,29 @@ static bool use_log(uint64_t m0, uint32_t levels, const lr_opts* o) {
     return m0 >= LOG_MIN_N || (o && (o->flags & LR_VISIT_LOG) && m0 >= LOG_FORCE_MIN_N);
 }
 
+// Whether p has the levels that default options give.
+static bool planners_levels(const Plan& p, uint32_t max_levels, bool capped) {
+    Plan q;
+    if (plan_levels(p.m[0], p.weighted, nullptr, false, &q, max_levels, capped) != LR_OK) return false;
+    if (q.levels != p.levels || q.base_max != p.base_max) return false;
+    for (uint32_t l = 0; l < q.levels; ++l)
+        if (q.log2k[l] != p.log2k[l]) return false;
+    return true;
+}
+
+bool names_planners_levels(uint64_t n, bool weighted, const lr_opts& o) {
+    Plan p;
+    return plan_levels(n, weighted, &o, true, &p) == LR_OK && planners_levels(p, LR_MAX_LEVELS, false);
+}
+
 // Which levels are chased and which are ranked by independent walks: only
 // with the planner's own levels (options that name others are followed level
 // by level down to the base case). input: level 0 is the caller's input.
 static void plan_iw(const lr_opts* o, bool user_spacing, bool capped, bool input, uint32_t max_levels, Plan* p) {
     p->run = p->levels;
     p->iw = false;
-    if (o && ((user_spacing && o->spacing[0]) || o->base_max)) {
-        Plan q;
-        if (plan_levels(p->m[0], p->weighted, nullptr, false, &q, max_levels, capped) != LR_OK) return;
-        if (q.levels != p->levels || q.base_max != p->base_max) return;
-        for (uint32_t l = 0; l < q.levels; ++l)
-            if (q.log2k[l] != p->log2k[l]) return;
-    }
+    const bool named = o && ((user_spacing && o->spacing[0]) || o->base_max);
+    if (named && !planners_levels(*p, max_levels, capped)) return;
     uint32_t r = 0;
     if (input) {
         const bool direct = !use_log(p->m[0], p->levels, o) && p->m[0] > LR_IW_DIRECT_MIN &&
@@ -328,9 +338,10 @@ lr_status make_plans(uint64_t n, bool weighted, const lr_opts* o, uint32_t batch
     // plan options left at their defaults take the autotune cache's entry
     // for this device and size bucket, if there is one
     lr_opts tuned;
+    bool cached = false;
     if (!(o && ((o->flags & LR_SPAWN) || o->spacing[0] || o->base_max || o->lane_walks || o->refill))) {
         tuned = o ? *o : lr_opts{};
-        if (tune_lookup(n, weighted, &tuned)) o = &tuned;
+        if ((cached = tune_lookup(n, weighted, &tuned))) o = &tuned;
     }
     const bool force = o && (o->flags & LR_LOCAL);
     const bool never = o && (o->flags & LR_NO_LOCAL);
@@ -377,6 +388,10 @@ lr_status make_plans(uint64_t n, bool weighted, const lr_opts* o, uint32_t batch
         Plan* q = &ps->lp;
         lr_opts lo = o ? *o : lr_opts{};
         for (int l = 0; l < LR_MAX_LEVELS; ++l) lo.spacing[l] = 0;  // user spacing describes the plain levels
+        // and so does a base size from the cache, or one that goes with the
+        // planner's own plain levels: the contracted list's size, and with it the
+        // planner's choice for it, is another
+        if (cached || (lo.base_max && planners_levels(*p, max_levels, false))) lo.base_max = 0;
         s = plan_levels(local_auto_cap(n), weighted, &lo, false, q, LR_MAX_LEVELS, true);
         if (s != LR_OK) return s;
         plan_iw(&lo, false, true, false, LR_MAX_LEVELS, q);

@@ -281,7 +281,12 @@ lr_status make_plan(uint64_t n, bool weighted, const lr_opts* o, uint32_t batch_
 // Autotune cache (tune.cpp): fills o's plan options (spacing of the first
 // two levels, base size, walks per lane, refill) from the entry of the
 // current device, n's size bucket (floor(log2 n)) and weighted, if any.
+// An entry that names no levels leaves the planner's own.
 bool tune_lookup(uint64_t n, bool weighted, lr_opts* o);
+// Sets that entry from a plan's options.
+void tune_store(uint64_t n, bool weighted, const lr_opts& best, double ms);
+// Whether o's levels for n elements are those that default options give.
+bool names_planners_levels(uint64_t n, bool weighted, const lr_opts& o);
 
 // Base-case shared memory bytes for m elements.
 inline size_t base_lds_bytes(uint64_t m, bool weighted) {

@@ -84,10 +84,13 @@ bool tune_lookup(uint64_t n, bool weighted, lr_opts* o) {
     return true;
 }
 
-static void tune_store(uint64_t n, bool weighted, const lr_opts& best, double ms) {
+// The planner's own levels are stored as such (zeros): they change inside a size
+// bucket, and only they are ranked by independent walks from a level on.
+void tune_store(uint64_t n, bool weighted, const lr_opts& best, double ms) {
+    TuneVal v{best.spacing[0], best.spacing[1], best.base_max, best.lane_walks, best.refill, ms};
+    if (names_planners_levels(n, weighted, best)) v.k0 = v.k1 = v.base_max = 0;
     std::lock_guard<std::mutex> lock(g_mu);
-    g_cache[TuneKey{arch_key(), floor_log2(n), weighted ? 1u : 0u}] =
-        TuneVal{best.spacing[0], best.spacing[1], best.base_max, best.lane_walks, best.refill, ms};
+    g_cache[TuneKey{arch_key(), floor_log2(n), weighted ? 1u : 0u}] = v;
 }
 
 }  // namespace lr
