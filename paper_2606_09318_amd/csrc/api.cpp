@@ -318,9 +318,11 @@ static size_t layout_spawn(Plan* p, uint64_t n, size_t off) {
 // The contracted path's plan for a short list (see PlanSet): only where its own
 // plan is the planner's and chases a level. Its nodes lie over the arrays of the
 // levels that are then not chased.
-static bool plan_small(const Plan& local, size_t end, Plan* sp) {
+static bool plan_small(const Plan& local, uint64_t seed, size_t end, Plan* sp) {
     if (!local.iw || local.run == 0) return false;
-    if (plan_levels(std::min(local.m[0], LOCAL_SMALL_MAX), local.weighted, nullptr, false, sp) != LR_OK) return false;
+    lr_opts o{};
+    o.seed = seed;
+    if (plan_levels(std::min(local.m[0], LOCAL_SMALL_MAX), local.weighted, &o, false, sp) != LR_OK) return false;
     sp->iw = true;
     sp->run = 0;
     sp->top = 0;
@@ -410,7 +412,7 @@ lr_status make_plans(uint64_t n, bool weighted, const lr_opts* o, uint32_t batch
     }
     place_iw(body, off, p);
     if (ps->autol) place_iw(body, off, &ps->lp);
-    if (force || ps->autol) ps->small = plan_small(force ? *p : ps->lp, off, &ps->sp);
+    if (force || ps->autol) ps->small = plan_small(force ? *p : ps->lp, o ? o->seed : 0, off, &ps->sp);
     if (batch_count) {
         p->batch_count = batch_count;
         p->off_batch_succ = off;

@@ -1,8 +1,10 @@
 // Prints the plans of one call (host code of liblr.so): levels, how many of them
-// are chased, whether the rest is ranked by independent walks, spacings, base.
+// are chased, whether the rest is ranked by independent walks, spacings, base,
+// the first level's sampling seed.
 //   plan_probe load FILE n weighted          after loading a cache file
 //   plan_probe store n0 n weighted k0 k1 bm  after storing that plan, tuned at n0
 //   plan_probe opts n weighted flags bm k... with explicit options
+//   plan_probe seed n weighted seed          with another sampling seed
 #include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
@@ -14,7 +16,7 @@ using namespace lr;
 static void show(const char* name, const Plan& p) {
     printf("%s levels=%u run=%u iw=%d top=%u base=%u k=", name, p.levels, p.run, p.iw, p.iw ? p.top : 0, p.base_max);
     for (uint32_t l = 0; l < p.levels; ++l) printf("%s%u", l ? "," : "", 1u << p.log2k[l]);
-    printf(" lw=%u refill=%u\n", p.lane_walks, p.refill);
+    printf(" lw=%u refill=%u seed=%08x\n", p.lane_walks, p.refill, p.levels ? p.lseed[0] : 0u);
 }
 
 int main(int argc, char** argv) {
@@ -41,6 +43,9 @@ int main(int argc, char** argv) {
     } else if (argc > 5 && !strcmp(argv[1], "opts")) {
         n = num(2), weighted = num(3) != 0, o.flags = (uint32_t)num(4), o.base_max = (uint32_t)num(5);
         for (int i = 6; i < argc && i - 6 < LR_MAX_LEVELS; ++i) o.spacing[i - 6] = (uint32_t)num(i);
+        named = true;
+    } else if (argc > 4 && !strcmp(argv[1], "seed")) {
+        n = num(2), weighted = num(3) != 0, o.seed = num(4);
         named = true;
     } else {
         return 3;

@@ -93,3 +93,11 @@ def test_options_that_spell_out_the_planners_levels_take_its_route(probe):
     # a base size that changes the levels is followed by both paths
     other = probe("opts", n, 0, 0, 2048).splitlines()
     assert len(other) >= 2 and all(" iw=0 " in ln and "base=2048" in ln for ln in other)
+
+
+@pytest.mark.parametrize("weighted", [0, 1])
+def test_every_path_samples_with_the_seed_of_the_call(probe, weighted):
+    """Another seed samples other rulers: the way out of an order against the
+    sampling, on short contracted lists too."""
+    seeds = [[ln.split("seed=")[1] for ln in probe("seed", 1 << 24, weighted, s).splitlines()] for s in (0, 12345)]
+    assert len(seeds[0]) == 3 and all(len(set(x)) == 1 for x in seeds) and seeds[0] != seeds[1]
