@@ -2572,9 +2572,12 @@ __global__ __launch_bounds__(LC_TPB) void k_lc_chain(const uint32_t* __restrict_
             // consistent (target, count) pair, so an older one only jumps less
             // far, and a wavefront stops when its own elements have reached
             // their starts (entries that point to themselves) or, on a cycle
-            // inside the tile, counted more links than a tile has. Bound by the
-            // LDS gathers (2^26 ids: 342 us with two barriers a round, 285 so)
-            for (;;) {
+            // inside the tile, counted more links than a tile has. An element
+            // that has not moves at least one link a turn, so LC_T turns are
+            // enough; on a cycle they are the end of counts that outgrow their
+            // 16 bits. Bound by the LDS gathers (2^26 ids: 342 us with two
+            // barriers a round, 285 so)
+            for (uint32_t turn = 0; turn < LC_T; ++turn) {
                 uint32_t u[LC_PER];
                 bool open = false;
 #pragma unroll

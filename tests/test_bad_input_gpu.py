@@ -74,3 +74,27 @@ def test_merging_chains_end(n, plan, weighted):
     if weighted:
         assert np.array_equal(s.cpu().numpy(), es)
     assert call(bad, ws, v) == lr.LR_ERR_BAD_LIST
+
+
+@pytest.mark.parametrize("length", [2, 3, 63, 1000, 2047, 4095, 4096])
+def test_cycles_inside_a_tile_end(length):
+    """Cycles inside tiles, in id order (one wavefront's elements follow each
+    other) and shuffled over the tile: the tile's jumping counts links round and
+    round and ends."""
+    print(f"case: cycles of {length} inside tiles", flush=True)
+    n = 64 * TILE
+    rng = np.random.default_rng(length)
+    succ = np.empty(n, np.uint32)
+    for t in range(n // TILE):
+        ids = t * TILE + (np.arange(TILE) if t % 2 else rng.permutation(TILE))
+        succ[ids] = np.roll(ids, -1)
+        succ[ids[-1]] = min(t * TILE + TILE, n - 1) if length < TILE else ids[0]
+        if length < TILE:
+            succ[ids[length - 1]] = ids[0]
+    d = dev(succ)
+    r = torch.empty(n, dtype=torch.int32, device="cuda")
+    for flags, expect in ((lr.LR_LOCAL, lr.LR_OK), (lr.LR_LOCAL | lr.LR_VALIDATE, lr.LR_ERR_BAD_LIST)):
+        o = lr.make_opts(flags=flags)
+        ws = lr.workspace(lr.lr_workspace_bytes(n, lr.LR_W_NONE, o))
+        assert lr.lr_rank(d, r, None, ws, o) == expect
+        torch.cuda.synchronize()
