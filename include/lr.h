@@ -44,8 +44,11 @@
  * element, a predecessor mark per element), synchronise, and return
  * LR_ERR_BAD_LIST unless every slot was written exactly once and every mark
  * at most once, also without LR_VALIDATE. Their workspaces are larger
- * (*_workspace_bytes of that library), automatic contraction is off, and
- * calls must not run on several streams at once.
+ * (*_workspace_bytes of that library), automatic contraction is off, every
+ * level is chased (no independent walks), and calls must not run on several
+ * streams at once. Inputs that the base case takes whole (up to 8192 elements,
+ * 16384 where it saves a level; weighted half of that) store no slot and no
+ * mark.
  */
 #ifndef LR_H
 #define LR_H

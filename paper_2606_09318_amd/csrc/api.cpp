@@ -158,10 +158,13 @@ bool names_planners_levels(uint64_t n, bool weighted, const lr_opts& o) {
 
 // Which levels are chased and which are ranked by independent walks: only
 // with the planner's own levels (options that name others are followed level
-// by level down to the base case). input: level 0 is the caller's input.
+// by level down to the base case). Debug builds chase every level: there a
+// slot and a mark have one writer each only where the input is a forest.
+// input: level 0 is the caller's input.
 static void plan_iw(const lr_opts* o, bool user_spacing, bool capped, bool input, uint32_t max_levels, Plan* p) {
     p->run = p->levels;
     p->iw = false;
+    if (LR_DEBUG_WRITES) return;
     const bool named = o && ((user_spacing && o->spacing[0]) || o->base_max);
     if (named && !planners_levels(*p, max_levels, capped)) return;
     uint32_t r = 0;

@@ -1997,6 +1997,7 @@ __global__ __launch_bounds__(place_tpb(false, false)) void k_mark1(const uint32_
             if constexpr (TGT) xs[j] = s < n ? s : NONE;  // a target id
             else xs[j] = (s != i && s < n) ? s : NONE;    // the target of a link
             bs[j] = xs[j] >> s1;
+            if constexpr (!TGT) if (xs[j] != NONE) LR_DBG_COUNT(mark, 0, xs[j]);
         }
         if (tile + gridDim.x < tiles) load_tile(tile + gridDim.x);
         place_tile<false, false, PER, false, true>(xs, rs, ts, ss, bs, nb1, s1, 0, n, fill1, out, ctrl, lds, tile & 1u);
