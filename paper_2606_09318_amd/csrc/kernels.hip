@@ -2578,7 +2578,7 @@ __global__ __launch_bounds__(LC_TPB) void k_lc_chain(const uint32_t* __restrict_
             // enough; on a cycle they are the end of counts that outgrow their
             // 16 bits. Bound by the LDS gathers (2^26 ids: 342 us with two
             // barriers a round, 285 so)
-            for (uint32_t turn = 0; turn < LC_T; ++turn) {
+            for (uint32_t left = LC_T; left;) {
                 uint32_t u[LC_PER];
                 bool open = false;
 #pragma unroll
@@ -2595,7 +2595,7 @@ __global__ __launch_bounds__(LC_TPB) void k_lc_chain(const uint32_t* __restrict_
                         open = true;
                     }
                 }
-                if (!__any(open)) break;
+                left = __any(open) ? left - 1u : 0u;
             }
             __syncthreads();  // DIR, and the starts' entries, before the next use
         } else {
