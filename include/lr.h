@@ -312,7 +312,7 @@ lr_status lr_prefix_sum_wyllie(const uint32_t* succ, const void* weight, lr_wtyp
  * the users of list ranking, Section 1). Ranking the tour gives every arc's
  * position; a vertex's size follows from the positions of its two arcs, its
  * preorder number is the number of down arcs up to its own, its depth twice
- * that less the position. With LR_VALIDATE, and for small trees, one
+ * that less one and the position (from 0) of its down arc. With LR_VALIDATE, and for small trees, one
  * lr_prefix_sum over the tour with weight +1 on down arcs and -1 on up arcs
  * gives the number of arcs (rank) and #down - #up (sum) from every arc to the
  * end of the tour instead, and depth, preorder number and size from those (the

@@ -42,12 +42,14 @@ static uint32_t ilog2(uint32_t k) {
 // us a call, rank alone of a random list / rank and root of a forest:
 //   8 -> 16:  5 M 310 -> 317 / 359 -> 363;  7 M 428 -> 403 / 509 -> 477
 //   16 -> 32: 9 M 485 -> 538 / 593 -> 591; 12 M 622 -> 605 / 781 -> 740;
-//     16 M 823 -> 759 / 1019 -> 980 From 2^25 the first level takes
-// 32 up to 3 * 2^26 elements and 64 beyond (32 is 7 % faster at 2^26 and
-// 2 % at 2^27, 64 is 2 % faster at 2^28); weighted inputs (16 B records)
-// take 64 from 2^27 (32 is 2-6 % faster at 2^26, 2 % slower on a 2^27
-// forest), a plan sized for a capacity (capped) from 2^26. The last level
-// takes the smallest spacing that brings it under base_max.
+//     16 M 823 -> 759 / 1019 -> 980.
+// From 2^25 the first level takes 32 up to 3 * 2^26 elements and 64 beyond;
+// weighted inputs (16 B records) take 64 from 2^27, a plan sized for a capacity
+// (capped) from 2^26. 32 -> 64, ms a call: random lists 2^25 1.51 -> 1.71, 2^26 2.64
+// -> 2.76, 2^27 4.78 -> 4.82, 3 * 2^26 7.38 -> 7.29, 2^28 10.18 -> 9.95; forests 2^27
+// 5.93 -> 5.87, 3 * 2^26 9.23 -> 8.99; int64 sums 2^26 4.46 -> 4.77, forest 4.69 -> 4.67,
+// 2^27 8.80 -> 8.77, forest 9.31 -> 9.18. The last level takes the smallest spacing
+// that brings it under base_max.
 constexpr uint64_t SHORT_WALKS_BELOW = 1ull << 25;
 static uint32_t default_spacing(uint32_t l, uint64_t m, uint32_t base_max, bool short_walks, bool weighted,
                                 bool capped) {

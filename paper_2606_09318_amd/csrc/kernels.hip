@@ -1068,9 +1068,11 @@ __global__ __launch_bounds__(BASE_TPB) void k_base_weighted_large(Src src, Out o
 //     ruler. The downward pass over the input then turns into doubling itself:
 //     after IW_PATIENCE hops (a random order needs 1.5 on average and stays
 //     below 16) a lane stores its progress after every further hop and reads
-//     device-scope, and its stretch's lanes, all of them resident, halve the
-//     rest with every hop. The last level's doubling stops after IW_TOP_CAP
-//     hops for the same reason and leaves the rest to that pass.
+//     device-scope, and its stretch's lanes halve the rest with every hop: all
+//     of them are resident, but for weighted contracted lists above 3 * 2^19
+//     elements (see IW_PER), of which the rest is followed at about 12 links a
+//     hop. The last level's doubling stops after IW_TOP_CAP hops for the same
+//     reason and leaves the rest to that pass.
 // Bound by latency: cap cached reads, about log2(m) device-scope reads (0.7 us
 // each up to 2^15 lanes, then 50 G/s), a few cached reads, and a launch (4.5
 // us) for each kernel. A cap of 12 steps (random lists of 1.5 * 2^18 elements:
@@ -1777,10 +1779,8 @@ __global__ __launch_bounds__(place_tpb(W, ROOT)) void k_place1(LogArrays<W> lg, 
     }
 }
 
-// fill1: the coarse ranges' two-sided counters. With values (VALS) every
-// coarse range is full, and its front and back counts must add up to its
-// length; VALS = false groups element ids only: then a coarse range need not
-// be full and its records are its front and back segments.
+// fill1: the coarse ranges' two-sided counters. Every coarse range is full: its
+// front and back counts must add up to its length.
 template <bool W, bool ROOT>
 __global__ __launch_bounds__(place_tpb(W, ROOT)) void k_place2(PlaceArrays<W> in, Ctrl* ctrl, uint32_t n, uint32_t s1, uint32_t s2,
                                                 uint32_t* __restrict__ fill2, PlaceArrays<W> out, const uint32_t* dm,
@@ -1955,6 +1955,7 @@ __global__ __launch_bounds__(TPB) void k_pair(const uint32_t* __restrict__ succ,
 // store per link, the link targets are grouped by element range with the first
 // placement pass (ids only) and written range by range from LDS. Every id is the
 // target of at most one link, so no range receives more targets than it has ids.
+// The grouping counts a link's target in debug builds.
 constexpr int MARK_TPB = 1024;
 // ids a lane holds in the grouping: a tile's run in a group is 32 ids on average
 // at 512 groups (2^27 ids: 16 a lane 522 us, 32 360)
@@ -2012,12 +2013,12 @@ __global__ __launch_bounds__(place_tpb(false, false)) void k_mark1(const uint32_
 // and the marked ids before them in their range of 2^PLACE_FINE_SHIFT ids; cnt[f]
 // is that range's count. With a bit per id a group is 2^18 ids in 32 KB, so one
 // grouping pass is enough. Bound by the LDS atomics: two workgroups a CU take 192
-// us for 2^27 ids, one (groups of 2^19) 301; loading ahead gains nothing. A second
-// grouping pass (375 us) and byte marks of 8192 ids a workgroup (155) took the
-// place of it: a 2^27 forest 6.28 -> 6.11 ms, int64 sums over it 9.51 -> 9.33, 9 *
-// 10^7 4.37 -> 4.27, a 2^26-vertex tree 8.91 -> 8.76. Marks written as bytes and
-// heads counted, scanned and written by three more
-// kernels: a 5 M forest 335 -> 324 us, 33 M 1856 -> 1807, 2^27 int64 9.33 -> 9.17 ms.
+// us for 2^27 ids, one (groups of 2^19) 301; loading ahead gains nothing.
+// Against a second grouping pass (375 us) and byte marks of 8192 ids a workgroup
+// (155): a 2^27 forest 6.28 -> 6.11 ms, int64 sums over it 9.51 -> 9.33, a forest of
+// 9 * 10^7 4.37 -> 4.27, a 2^26-vertex tree 8.91 -> 8.76. Against marks written as
+// bytes, with the heads counted, scanned and written by three more kernels: a 5 M
+// forest 335 -> 324 us, 33 M 1856 -> 1807, 2^27 int64 9.33 -> 9.17 ms.
 template <bool DIR>
 __global__ __launch_bounds__(MARK_TPB) void k_mark_bits(const uint32_t* __restrict__ tx, uint32_t n, uint32_t s1,
                                                         uint32_t nb1, const uint32_t* __restrict__ fill1,
@@ -2577,7 +2578,7 @@ __global__ __launch_bounds__(LC_TPB) void k_lc_chain(const uint32_t* __restrict_
             // that has not moves at least one link a turn, so LC_T turns are
             // enough; on a cycle they are the end of counts that outgrow their
             // 16 bits. Bound by the LDS gathers (2^26 ids: 342 us with two
-            // barriers a round, 285 so)
+            // barriers a round, 275 without, 278 with the turns counted)
             for (uint32_t left = LC_T; left;) {
                 uint32_t u[LC_PER];
                 bool open = false;
@@ -3256,8 +3257,16 @@ static hipError_t launch_base(Src src, Out out, uint32_t m, uint32_t climit, Ctr
 
 // The input by independent walks: levels 0 .. top - 1 walk, level top is
 // doubled, then downward.
-constexpr int IW_PER = 4;                   // elements per lane of the downward pass: all of a list's lanes are resident
-constexpr uint32_t IW_PER_MIN = 1u << 18;  // up to here one element a lane fills the chip better
+//
+// Elements per lane of the downward pass: one is faster wherever it was timed
+// (one / four, us a call: 262,144 elements 39.5 / 41.9, 300,007 43.5 / 46.9, 2^20
+// 81.6 / 83.5; int64 sums of 262,144 68.7 / 73.6, of 500,003 103 / 108), but with it
+// no more than 2^19 of a list's elements have a resident lane, and an order
+// against the sampling is halved only among those. With four all 2^21 have one
+// (60 registers, 8 waves a SIMD), weighted levels' 3 * 2^19 (74 registers, 6 waves; held to
+// 64 registers the kernel spills).
+constexpr int IW_PER = 4;
+constexpr uint32_t IW_PER_MIN = 1u << 18;  // up to here one element a lane
 
 template <bool W, class Src, class Out>
 static hipError_t run_iw(const Plan& p, Src src, Out out, uint32_t n, Ctrl* ctrl, char* ws, hipStream_t st,

@@ -22,7 +22,11 @@ constexpr uint32_t LOG_MAX_WAVES = 8192;     // chase waves in log mode (caps th
 #define LR_LOG_MIN_LOG2 25
 #endif
 static_assert(LR_LOG_MIN_LOG2 >= 16 && LR_LOG_MIN_LOG2 <= 31, "visit-log threshold: 2^16 .. 2^31 elements");
-constexpr uint64_t LOG_MIN_N = 1ull << LR_LOG_MIN_LOG2;  // smallest level 0 that uses the visit log
+// Smallest level 0 that uses the visit log. By time alone the line would lie near
+// 2.7 * 10^7 elements (slots -> log, us a call: random lists of 2^24 803 -> 981, forests
+// of 2 * 10^7 1236 -> 1251, of 3 * 10^7 1875 -> 1627), but the log asks for twice the
+// workspace, which stays within 2^25's.
+constexpr uint64_t LOG_MIN_N = 1ull << LR_LOG_MIN_LOG2;
 constexpr uint64_t LOG_FORCE_MIN_N = 1ull << 16;          // smallest level 0 LR_VISIT_LOG applies to
 // Packed visit-log records (one 64-bit word) up to 2^28 elements: then the
 // element field takes at most 29 bits and the walk field (walks plus
@@ -153,7 +157,9 @@ inline size_t batch_table_bytes(uint32_t count) { return 2 * ((size_t)count + 1)
 // levels above it are ranked by independent walks, from the first level of at
 // most iw_top elements on by asynchronous doubling. Inputs of more than
 // IW_DIRECT_MIN (what the base case takes) and fewer than iw_direct elements
-// are not chased at all.
+// are not chased at all. (Forests of lists of one or two elements would be
+// faster in the base case up to its 16384 elements, one launch of 9.0 us for two
+// of 12.8; random lists there take 24.7 for 17.8.)
 // Measured (random lists, rank and root; weighted: int64, every output; us a
 // call, same box), the other side of each line first:
 //   chase and base case -> independent walks: 2^15 68 -> 22, 2^18 117 -> 39,
@@ -191,7 +197,7 @@ constexpr uint64_t iw_max(uint32_t log2k) { return log2k >= 4 ? (5ull << 18) : (
 constexpr uint64_t iw_direct(bool weighted) { return 1ull << (weighted ? LR_IW_DIRECT_LOG2_W : LR_IW_DIRECT_LOG2); }
 constexpr uint64_t iw_top(bool weighted) { return 1ull << (weighted ? LR_IW_TOP_LOG2_W : LR_IW_TOP_LOG2); }
 constexpr size_t iw_node_bytes(bool weighted) { return weighted ? 24 : 8; }
-static_assert(LR_IW_MAX_LOG2 <= 21, "every lane of the downward pass is resident at once");
+static_assert(LR_IW_MAX_LOG2 <= 21, "four elements a lane: an unweighted level's downward pass is resident at once");
 static_assert(iw_direct(false) <= LOCAL_AUTO_MIN_N && iw_direct(true) <= LOCAL_AUTO_MIN_N,
               "an input ranked by independent walks alone has no contracted path beside it");
 

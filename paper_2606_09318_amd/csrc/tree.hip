@@ -19,10 +19,12 @@
 // Two ways to get there:
 //   ranks     the tour is ranked without weights, which gives every arc its
 //             position p = m - 1 - rank. One pass over the vertices reads the
-//             ranks of their two arcs, writes the sizes and sets a byte at
-//             every down arc's position; the bytes become a bitmap with
-//             running counts, and the down arcs before p give preorder and
-//             depth (up arcs before p = p - those).
+//             ranks of their two arcs and writes the sizes and the down arcs'
+//             positions; a second one sets a byte at each position (large
+//             tours group the positions by range instead). That becomes a
+//             bitmap with running counts, and the b down arcs before p give
+//             preorder(v) = b + 1 and depth(v) = 2 b + 1 - p (up arcs before
+//             p = p - b).
 //   weights   a weighted ranking, which writes rank and sum of an arc as one
 //             16-byte record. Validation checks its sums; tours that the
 //             weighted base case ranks in one launch need fewer launches this

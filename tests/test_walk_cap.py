@@ -96,8 +96,8 @@ def test_rulers_last_falls_back_and_matches_oracle(flags):
 
 @pytest.mark.gpu
 def test_rulers_last_above_2p21_sixteen_fold_rounds():
-    """Above 2^21 elements the fallback jumps 16 records per round (6 rounds
-    here) instead of 128; level 0 through the visit log as well."""
+    """An input whose first level is chased: the fallback's two launches (the
+    rounds of the name are gone); level 0 through the visit log as well."""
     n = (1 << 22) + 5
     print(f"case: rulers last, n={n}", flush=True)
     L = rulers_last(n, plan_spacings(n)[0])
