@@ -672,7 +672,8 @@ def autotune_bench(args, stream):
 
     lr.autotune_cache_clear()
     default_ms, default_plan = timed()
-    tws = lr.workspace(lr.lr_workspace_bytes(n, lr.LR_W_NONE, lr.make_opts(spacing=(16, 8))) + n * 4 + 4096)
+    tws = lr.workspace(max(lr.lr_workspace_bytes(n), lr.lr_workspace_bytes(n, lr.LR_W_NONE, lr.make_opts(spacing=(16, 8))))
+                       + n * 4 + 4096)
     t0 = time.time()
     st, best, trials = lr.lr_autotune(succ, None, tws, None, stream)
     tune_s = time.time() - t0

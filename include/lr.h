@@ -342,9 +342,10 @@ lr_status lr_euler_tree(const uint32_t* succ, const uint32_t* down, const uint32
 /* Plan autotuner (the paper fixes its ruler-count constants by a parameter
  * study, Section 3 "Methodology"; this does the same on the caller's input).
  * Times lr_rank (w == LR_W_NONE, weight NULL) or lr_prefix_sum (any other w)
- * on `succ` with the planner's own plan, then in three stages, each keeping the fastest so far and varying one
- * group: the ruler spacings of the first two levels (16..128 x 8..32), then
- * the base-case size, then walks per lane and the refill threshold. It keeps
+ * on `succ` with the planner's own plan, then in three stages, each keeping
+ * the fastest so far and varying one group: the ruler spacings of the first
+ * two levels (16..128 x 8..32), then the base-case size, then walks per lane
+ * and the refill threshold. It keeps
  * `base`'s seed and flags other than LR_VALIDATE / LR_PROFILE, writes the
  * fastest option set to *best (its spacing list filled for every level) and
  * stores it in the autotune cache under (device, floor(log2 n), weighted):
@@ -357,7 +358,9 @@ lr_status lr_euler_tree(const uint32_t* succ, const uint32_t* down, const uint32
  * contracted list are always the planner's then. The trial calls write their outputs to
  * the tail of `ws` (n x 4 B, weighted n x 8 B) and use the rest as their
  * workspace; candidates that do not fit are skipped (LR_ERR_WORKSPACE if
- * none fits). `ms` (may be NULL) receives up to `cap` timings, in the order
+ * none fits). If the planner's own plan (lr_workspace_bytes with default
+ * options) does not fit, *best is the fastest of the others and nothing is
+ * stored. `ms` (may be NULL) receives up to `cap` timings, in the order
  * the candidates were tried; *tried (may be NULL) their number. Synchronises
  * `stream`. */
 lr_status lr_autotune(const uint32_t* succ, const void* weight, lr_wtype w, uint64_t n, void* ws, size_t ws_bytes,
